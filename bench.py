@@ -52,8 +52,9 @@ if ROOT not in sys.path:
 N_CU, CLOCK_HZ = 256, 2.4e9
 FLOPS_PER_EVAL = 12
 PEAK_FP32_TFLOPS = 157.3
-# Secondary figure, the issue model of the kernel's own instruction stream:
-# an evaluation issues 7 unpacked FP32 VALU instructions and 2 v_exp_f32 (the
+# Secondary figure, the issue model of the kernel's separate sample loop (its
+# shared loop issues 6 VALU instructions and 1.5 v_exp_f32 an evaluation and
+# runs above this model): an evaluation issues 7 unpacked FP32 VALU instructions and 2 v_exp_f32 (the
 # log of a product is taken once per 32 samples), so it costs
 # 7 / R_fma + 2 / R_exp seconds per lane, with R_fma and R_exp the FP32 FMA
 # and v_exp_f32 lane-operation rates that the probe library measures live.

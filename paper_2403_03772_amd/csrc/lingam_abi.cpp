@@ -189,7 +189,7 @@ struct Plan {
 
 size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
 
-Plan make_plan(const std::vector<HostJob>& jobs, int cu, const Learn& lc = Learn{}) {
+Plan make_plan(const std::vector<HostJob>& jobs, int cu, const Learn& lc, bool share = true) {
   Plan P;
   P.njobs = (int)jobs.size();
   P.cu = cu;
@@ -204,13 +204,23 @@ Plan make_plan(const std::vector<HostJob>& jobs, int cu, const Learn& lc = Learn
     off = align256(off + sizeof(lg::PropDev));
   }
   for (const HostJob& j : jobs) {
-    P.L.push_back(lg::make_layout(j.n, j.d, cu, lc.proposer ? lc.K : 0));
+    P.L.push_back(lg::make_layout(j.n, j.d, cu, lc.proposer ? lc.K : 0, share));
     P.job_off.push_back(off);
     off = align256(off + P.L.back().total);
     P.max_d = std::max(P.max_d, (int)j.d);
   }
   P.total = off;
   return P;
+}
+
+// The plan for a workspace of `avail` bytes: without the regions the pair
+// kernels can do without where only that fits (never larger than avail says,
+// if either does).
+Plan plan_for(const std::vector<HostJob>& jobs, int cu, const Learn& lc, size_t avail) {
+  Plan P = make_plan(jobs, cu, lc);
+  if (P.total <= avail) return P;
+  Plan lean = make_plan(jobs, cu, lc, false);
+  return lean.total <= avail ? lean : P;
 }
 
 std::vector<lg::JobDev> device_jobs(const Plan& P, const std::vector<HostJob>& jobs, char* ws,
@@ -240,6 +250,7 @@ std::vector<lg::JobDev> device_jobs(const Plan& P, const std::vector<HostJob>& j
     J.n_src = (int32_t)std::min<int64_t>(h.n_src, INT32_MAX);
     J.zd = reinterpret_cast<double*>(b + L.zd);
     J.z = reinterpret_cast<float*>(b + L.z);
+    J.g = L.g ? reinterpret_cast<float*>(b + L.g) : nullptr;
     J.mu = reinterpret_cast<double*>(b + L.mu);
     J.sig = reinterpret_cast<double*>(b + L.sig);
     J.rho = reinterpret_cast<double*>(b + L.rho);
@@ -455,7 +466,11 @@ int enqueue_steps(const Plan& P, const std::vector<HostJob>& jobs, char* ws, hip
 // launch-shape autotuner
 // --------------------------------------------------------------------------
 
-const lg::Tune kDefaultTune{16, 8, 4, 4};
+// Default: 8 (tile, direction) items a CU, that is 4 workgroups (3 are resident),
+// each at least 4 sample blocks long.  k_pair at d = 331, n = 4801: 65 us a
+// launch, against 67 with 16 items; d = 97, n = 1999: 14.7 us against 15.3 with
+// 8 blocks and 18.9 with 16; d = 1024, n = 8192 and the uneven batch move by 1%.
+const lg::Tune kDefaultTune{8, 4, 4, 4};
 // split policies (target workgroups per CU, least sample iterations per split)
 const int32_t kSplitCandidates[][2] = {{8, 8}, {16, 8}, {16, 4}, {32, 4}, {8, 16}, {16, 16}};
 const int32_t kWaveChoices[] = {4, 2, 1};
@@ -941,7 +956,8 @@ int causal_order_impl(const float* X, int64_t n, int64_t d, int64_t ldx, int32_t
   const HostJob j{X,     nullptr, n, ldx, n, d, order, opts->step_measures, opts->step_gap,
                   opts->forced_order, opts->forced_len, opts->record_features, opts->step_log};
   const std::vector<HostJob> jobs{j};
-  const Plan P = make_plan(jobs, cu, learn_of(opts));
+  const Plan P = plan_for(jobs, cu, learn_of(opts),
+                          noalloc ? (size_t)LINGAM_NOALLOC_SCRATCH_BYTES : ws_bytes);
   if (noalloc) {
     if (P.total > (size_t)LINGAM_NOALLOC_SCRATCH_BYTES)
       return fail(LINGAM_E_UNSUPPORTED,
@@ -1026,7 +1042,7 @@ int lingam_batch_causal_order(const lingam_job* jobs, int32_t n_jobs, int32_t* j
   int cu = 0;
   rc = num_cu_of_current(&cu);
   if (rc != LINGAM_OK) return rc;
-  const Plan P = make_plan(hj, cu, learn_of(opts));
+  const Plan P = plan_for(hj, cu, learn_of(opts), ws_bytes);
   if (!ws || ws_bytes < P.total)
     return fail(LINGAM_E_WORKSPACE, "workspace of %zu bytes needed (got %zu)", P.total,
                 ws ? ws_bytes : (size_t)0);
@@ -1081,8 +1097,9 @@ int varlingam_fit(const float* X, int64_t T, int64_t d, int64_t ldx, int32_t lag
                   opts->step_measures, opts->step_gap, opts->forced_order, opts->forced_len,
                   opts->record_features, opts->step_log};
   const std::vector<HostJob> jobs{j};
-  const Plan P = make_plan(jobs, cu, learn_of(opts));
   const lg::VarLayout V = lg::make_var_layout(T, d, lags, cu);
+  const Plan P = plan_for(jobs, cu, learn_of(opts),
+                          ws_bytes > V.total ? (ws_bytes - V.total) / 256 * 256 : 0);
   const size_t var_off = align256(P.total);
   if (!ws || ws_bytes < var_off + V.total)
     return fail(LINGAM_E_WORKSPACE, "workspace of %zu bytes needed (got %zu)",
@@ -1094,7 +1111,8 @@ int varlingam_fit(const float* X, int64_t T, int64_t d, int64_t ldx, int32_t lag
   return run_engine(
       P, jobs, opts, nullptr, w, st,
       [&]() -> int {
-        LG_TRY(lg::launch_var_fit(V, vw, job, X, ldx, resid, M, st), "var fit");
+        float* G = P.L[0].g ? reinterpret_cast<float*>(job + P.L[0].g) : nullptr;
+        LG_TRY(lg::launch_var_fit(V, vw, job, G, X, ldx, resid, M, st), "var fit");
         return LINGAM_OK;
       },
       [&] { return B0 ? lg::launch_save_rho(V, vw, job, st) : hipSuccess; },

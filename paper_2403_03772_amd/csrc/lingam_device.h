@@ -18,7 +18,12 @@ constexpr double kLn2 = 0.69314718055994530942;
 constexpr double kLog2e = 1.44269504088896340736;
 constexpr double kCollinear = 1e-12;  // |rho| >= 1 - kCollinear is degenerate
 constexpr int kLogBlock = 32;         // samples per lane folded into one log2 (product <= 2^32)
+constexpr int kSumBlock = 16;         // ... in the pair kernels' separate form
 constexpr float kS1Start = 9.0f;      // start value (negated) of each lane's log cosh sum
+
+// beside a variable's five moments: the largest |z|, and the sum of its FP32 copy
+constexpr int kMomTop = 5;
+constexpr int kMomSum = 6;
 
 constexpr int32_t kStInvalid = -1;
 constexpr int32_t kStDegenerate = -2;
@@ -42,22 +47,6 @@ __device__ __forceinline__ void eval_dir(float x, float y, float r, float c1h, f
   const float t = fmaf(-r, y, x);
   const float at = fabsf(t);
   const float m1 = fmaf(c1h, at, c1l * at);
-  const float e1 = __builtin_amdgcn_exp2f(m1);
-  P = fmaf(P, e1, P);
-  S1 = fmaf(m1, -0.5f, S1);
-  const float m2 = (kM2 * m1) * m1;
-  const float e2 = __builtin_amdgcn_exp2f(m2);
-  S2 = fmaf(t, e2, S2);
-}
-
-// One evaluation with the pair's scale constant c1 held per lane (pair_item
-// dithers it between its two FP32 neighbours so that its mean over the 64
-// lanes is the FP64 value): one multiply instead of the hi + lo product.
-__device__ __forceinline__ void eval_dir_lane(float x, float y, float r, float c1, float& P,
-                                              float& S1, float& S2) {
-  const float kM2 = (float)(-1.0 / (8.0 * kLog2e));  // rounds with relative error 2.7e-9
-  const float t = fmaf(-r, y, x);
-  const float m1 = c1 * fabsf(t);
   const float e1 = __builtin_amdgcn_exp2f(m1);
   P = fmaf(P, e1, P);
   S1 = fmaf(m1, -0.5f, S1);
@@ -196,14 +185,20 @@ __device__ double block_sum_256(double v, double* sh) {
 // z exp(-z^2/2), z^3, z^4, |z|.  log cosh z = |z| + log(1 + e^{-2|z|}) - ln 2;
 // the logs are taken as the log of a running product (each factor in (1, 2],
 // flushed every 512 samples), one FP64 log per 512 samples.
+// Also what the pair kernels' shared form needs: the largest |z| and the sum
+// of the FP32 copies.
 struct MomAcc {
   double abs_sum = 0.0, log_sum = 0.0, g = 0.0, z3 = 0.0, z4 = 0.0, prod = 1.0;
+  double top = 0.0, copy = 0.0;
   int cnt = 0, tot = 0;
-  __device__ inline void add(double z) {
+  __device__ inline double add(double z) {  // returns exp(-z^2 / 2)
     const double a = fabs(z), z2 = z * z;
+    const double e = exp_nonpos(-0.5 * z2);
     abs_sum += a;
+    top = fmax(top, a);
+    copy += (double)(float)z;
     prod *= 1.0 + exp_nonpos(-2.0 * a);
-    g += z * exp_nonpos(-0.5 * z2);
+    g += z * e;
     z3 += z2 * z;
     z4 += z2 * z2;
     ++tot;
@@ -212,42 +207,81 @@ struct MomAcc {
       prod = 1.0;
       cnt = 0;
     }
+    return e;
   }
-  // the five sums in the order of store_moments
-  __device__ inline void sums(double (&acc)[5]) const {
+  // in the order of store_moments
+  __device__ inline void sums(double (&acc)[7]) const {
     acc[0] = abs_sum + (log_sum + log(prod)) - (double)tot * kLn2;
     acc[1] = g;
     acc[2] = z3;
     acc[3] = z4;
     acc[4] = abs_sum;
+    acc[kMomTop] = top;
+    acc[kMomSum] = copy;
   }
 };
 
-// Block-wide deterministic sum of five FP64 values (256 threads): wave
-// butterflies, then the four wave totals in order.  `sh` holds 20 doubles.
-// The result is valid in thread 0.
-__device__ inline void block_sum_5(double (&v)[5], double* sh) {
+// Block-wide deterministic sums (256 threads; of value kMomTop the maximum):
+// wave butterflies, then the four wave totals in order.  `sh` holds 28
+// doubles.  The result is valid in thread 0.
+__device__ inline void block_moments(double (&v)[7], double* sh) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
 #pragma unroll
-  for (int k = 0; k < 5; ++k)
+  for (int k = 0; k < 7; ++k)
 #pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) v[k] += __shfl_xor(v[k], off);
+    for (int off = 32; off >= 1; off >>= 1) {
+      const double o = __shfl_xor(v[k], off);
+      v[k] = k == kMomTop ? fmax(v[k], o) : v[k] + o;
+    }
   if (lane == 0)
 #pragma unroll
-    for (int k = 0; k < 5; ++k) sh[k * 4 + wave] = v[k];
+    for (int k = 0; k < 7; ++k) sh[k * 4 + wave] = v[k];
   __syncthreads();
   if (threadIdx.x == 0)
 #pragma unroll
-    for (int k = 0; k < 5; ++k) v[k] = ((sh[k * 4] + sh[k * 4 + 1]) + sh[k * 4 + 2]) + sh[k * 4 + 3];
+    for (int k = 0; k < 7; ++k) {
+      const double* w = sh + k * 4;
+      v[k] = k == kMomTop ? fmax(fmax(w[0], w[1]), fmax(w[2], w[3]))
+                          : ((w[0] + w[1]) + w[2]) + w[3];
+    }
 }
 
-// Means of the five moments of variable `slot` and its marginal entropy.
-__device__ inline void store_moments(const JobDev& J, int slot, const double (&acc)[5], int n) {
+// Means of the five moments of variable `slot`, its largest |z|, the sum of
+// its FP32 copy, and its marginal entropy.
+__device__ inline void store_moments(const JobDev& J, int slot, const double (&acc)[7], int n) {
   const double inv = 1.0 / (double)n;
   double* mo = J.mom + (int64_t)slot * 8;
 #pragma unroll
   for (int k = 0; k < 5; ++k) mo[k] = acc[k] * inv;
+  mo[kMomTop] = acc[kMomTop];
+  mo[kMomSum] = acc[kMomSum];
   J.hm[slot] = entropy_from_moments(acc[0] * inv, acc[1] * inv);
+}
+
+// A job whose pair kernels may take the shared form: their log2 cosh sums then
+// leave out the sum of the (signed) residuals, in units of log2(e), which
+// measure_from_sums adds for the whole sample.
+__device__ inline bool shared_job(const JobDev& J) { return J.g != nullptr && J.tie_on; }
+
+// R(si, sj) from the pair kernels' sums over all samples: s[0], s[1] of the
+// residual of si on sj, s[2], s[3] of sj on si.  diag: a pair of one 4 x 4
+// sub-block of the all-pairs kernel, whose sums are complete.
+__device__ inline double measure_from_sums(const JobDev& J, int si, int sj,
+                                           const double (&s)[4], bool diag = false) {
+  const double inv_n = 1.0 / (double)J.n;
+  double r = J.rho[(int64_t)si * J.d + sj];
+  const double lim = 1.0 - kCollinear;
+  r = r > lim ? lim : (r < -lim ? -lim : r);
+  const double al = 1.0 / sqrt(1.0 - r * r);
+  double ui = 0.0, uj = 0.0;  // sums of either residual over the FP32 copies
+  if (shared_job(J) && !diag) {
+    const double zi = J.mom[(int64_t)si * 8 + kMomSum], zj = J.mom[(int64_t)sj * 8 + kMomSum];
+    ui = al * (zi - r * zj);
+    uj = al * (zj - r * zi);
+  }
+  const double h_ij = entropy_from_moments((kLn2 * s[0] + ui) * inv_n, al * s[1] * inv_n);
+  const double h_ji = entropy_from_moments((kLn2 * s[2] + uj) * inv_n, al * s[3] * inv_n);
+  return (J.hm[sj] + h_ij) - (J.hm[si] + h_ji);
 }
 
 // Row-major upper-triangular tile index -> (bi, bj), bi <= bj < nb.
@@ -349,19 +383,65 @@ __device__ __forceinline__ void for_blocks(const int32_t* __restrict__ pre, int 
   }
 }
 
-// Pair moments (the hot loop), shared by the all-pairs kernel and the
-// candidate-row kernel of the learned form.  Grid: per job ntiles * 2 * nsplit
-// workgroups of 4 waves (all pairs: upper-triangular 8 x 8 tiles of positions;
+// Pair moments (the hot loop), shared by the all-pairs kernel and the row
+// kernels of the learned form.  Grid: per job ntiles * nsplit * (4 / W)
+// workgroups of W waves (all pairs: upper-triangular 8 x 8 tiles of positions;
 // candidate rows: (K / 8) x nblk tiles whose i side lists candidates).  A
-// workgroup owns an 8 x 8 block of (i, j) variables, one residual direction
-// and one range of samples; wave (wi, wj) owns the 4 x 4 sub-block (i in block
-// bi, j in block bj).  Lanes stride over samples (coalesced 256 B loads per
-// variable row) and every lane keeps 48 running values (16 pairs x {P, S1, S2})
-// for its direction.  The wave ends with an FP64 reduction after which lane
-// L < 32 holds the total of sum L, stored at
+// workgroup owns an 8 x 8 block of (i, j) variables and one range of samples,
+// both residual directions of each pair; wave (wi, wj) owns the 4 x 4
+// sub-block (i in block bi, j in block bj).  Lanes stride over samples
+// (coalesced 256 B loads per variable row).  The wave ends with an FP64
+// reduction of every sum over its lanes, stored at
 // part[((split * ntiles + tile) * 4 + wave) * 64 + pair * 4 + dir * 2 + which],
-// which 0 = S1 (log cosh, offset as described in the header), 1 = S2;
-// dir 0 = residual of i on j, dir 1 = of j on i.
+// which 0 = S1 (log2 cosh), 1 = S2; dir 0 = residual of i on j, dir 1 = of j
+// on i.
+//
+// Two forms of the sample loop:
+//
+// Separate (pair_dir, one direction at a time): 7 VALU instructions and 2
+// v_exp_f32 an evaluation (see the header).  It holds for any data.  Its sum of
+// |u| log2(e) runs over kSumBlock samples at a time, from -kS1Start, so its
+// rounding stays that of values below 16.
+//
+// Shared (pair_both, both directions of a pair at once): 12 VALU and 3
+// v_exp_f32 for the two evaluations.
+//   * sum log2 cosh u = sum log2(1 + 2^m) - count + log2(e) sum u, m = -2 u
+//     log2(e): no |u|, whose sum would cost an instruction.  sum u over all
+//     samples follows from the rows' sums, which are kept with the moments (of
+//     the FP32 copies: next to 0, but their rounding would otherwise count), so
+//     this form leaves it out and measure_from_sums adds it; a wave of such a
+//     job that takes the separate form takes its range's share out.  P = prod
+//     (1 + 2^m) is unbounded then: every kRenorm samples its exponent is moved
+//     to an integer, which is exact and needs no log in the loop, and a P that
+//     has overflowed is noticed there; the wave then measures its pairs again
+//     in the separate form.
+//   * u^2 + y^2 = w^2 + x^2 for the residuals u = (x - rho y) alpha and w =
+//     (y - rho x) alpha: with E = e^{(x^2 - u^2) / 2} and the stored g = e^{-z^2
+//     / 2}, e^{-u^2 / 2} = E g(x) and e^{-w^2 / 2} = E g(y): one exponential
+//     for both.  E stays below 2^122 while |x| <= kShareTop; past that in y,
+//     g(y) loses bits only where e^{-w^2 / 2} is below 1e-8.  So the wave
+//     takes as x the side whose four variables stay within kShareTop.
+// What bounds both is instruction issue.  Measured on the forms alone, cycles a
+// SIMD per evaluation of 64 samples: v_exp_f32 takes 8.2 and lets nothing else
+// issue; other FP32 instructions take 4, but down to 2.4 where two waves can
+// issue together.  With every wave alternating freely between the two kinds
+// they hardly ever do (44 in the separate form, 39 in the shared one).  So the
+// arguments, the exponentials and the sums of a pair are kept apart, and a
+// wave's exponentials issue at a raised priority: they leave one wave in a run,
+// and the others' FP32 instructions meet between the runs (27 in the shared
+// form; 38 with the priority on the sums instead; how many pairs share a run
+// moves it by 1%).
+// FP32 MFMA for the residuals (4x4x1 and 16x16x1 tiles, lanes over pairs)
+// keeps VALU instructions from issuing as long as it runs (8 and 32 cycles):
+// no gain.  With the rows of the next block loaded while one is evaluated the
+// kernel takes 148 registers, three waves a SIMD; without, at four waves, it
+// measured the same.  d = 1024, n = 8192: 868 us a launch in the separate form
+// (one direction a wave, no priority) to 623 us, 44.7 to 32 cycles.
+//
+// Without FP64 tie resolution (tie_on 0) every kernel takes the separate
+// form, which gives a pair the same bits whatever tile it falls in.  So does a
+// job without the g region (a workspace too small for it).
+//
 // Work items of the pair kernels.  With kLoop false the grid is the schedule
 // and workgroup p (after the XCD remap) takes item p.  With kLoop true (gated
 // launches whose size the host only bounds) a smaller grid walks the items:
@@ -372,13 +452,31 @@ __device__ __forceinline__ void for_blocks(const int32_t* __restrict__ pre, int 
 // (ceil(nsus / 8) x ceil(ne / 8) tiles whose j side lists positions too).
 enum PairMode : int { kModeAll = 0, kModeCand = 1, kModeSusp = 2, kModeExt = 3 };
 
+constexpr float kM2 = (float)(-1.0 / (8.0 * kLog2e));  // rounds with relative error 2.7e-9
+
+// Around a run of v_exp_f32: issued at a raised wave priority (see above).
+__device__ __forceinline__ void exp_first() {
+  __builtin_amdgcn_sched_barrier(0);
+  __builtin_amdgcn_s_setprio(1);
+}
+__device__ __forceinline__ void exp_done() {
+  __builtin_amdgcn_sched_barrier(0);
+  __builtin_amdgcn_s_setprio(0);
+}
+
+constexpr double kShareTop = 13.0;  // largest |x| of the shared form's x side
+constexpr int kRenorm = 16;         // samples per lane between renormalisations
+// most samples per lane of the shared form: the exponents of P and Q share a
+// 32-bit register, 16 bits each, and add at most 254 every kRenorm samples
+constexpr int kShareMaxIters = 4096;
+
 template <int kMode, int W>
 __device__ __forceinline__ void pair_item(const JobDev& J, const JobStep& S, int local,
                                           int wave, int lane);
 
-// W waves per workgroup (1, 2 or 4): every (tile, direction, split) item is
-// cut into 4 / W consecutive workgroup items, and the wave's quadrant of the
-// tile is (workgroup item mod 4 / W) * W + its wave in the workgroup.
+// W waves per workgroup (1, 2 or 4): every (tile, split) item is cut into
+// 4 / W consecutive workgroup items, and the wave's quadrant of the tile is
+// (workgroup item mod 4 / W) * W + its wave in the workgroup.
 template <int kMode, bool kLoop, int W>
 __device__ __forceinline__ void pair_tiles(const JobDev* __restrict__ jobs, int njobs,
                                            const JobStep* __restrict__ js,
@@ -388,8 +486,8 @@ __device__ __forceinline__ void pair_tiles(const JobDev* __restrict__ jobs, int 
   const int lane = threadIdx.x & 63;
   const int lw = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   // Workgroups are dispatched round-robin over the 8 XCDs; give every XCD a
-  // contiguous range of (job, tile, direction, split) work so that the rows a
-  // tile reads are shared in that XCD's L2.
+  // contiguous range of (job, tile, split) work so that the rows a tile reads
+  // are shared in that XCD's L2.
   const int b = blockIdx.x;
   const int Q = G >> 3, R = G & 7, x = b & 7, idx = b >> 3;
   const int p = x * Q + (x < R ? x : R) + idx;
@@ -411,6 +509,290 @@ __device__ __forceinline__ void pair_tiles(const JobDev* __restrict__ jobs, int 
   }
 }
 
+// One wave's 4 x 4 sub-block over its range of samples.
+struct PairWave {
+  // coefficients of pair (lane >> 2 & 3, lane & 3) of the sub-block: rho and
+  // the scale c1 = -2 log2(e) / sqrt(1 - rho^2).  c1 is not rounded to one
+  // FP32 value (that would scale every sample of the pair by the same rounding
+  // error and bias its log cosh moment): lanes below n_hi take the FP32 value
+  // above c1, the others the one below, so the lanes' mean is c1 to 1/128 of a
+  // float spacing and the sample-to-lane assignment carries no bias (a lane's
+  // samples are s = lane, lane + 64, ...).
+  float r, lo, hi;
+  int n_hi;
+  int si[4], sj[4];  // variables of either side (d: padding), wave-uniform
+  int row;           // variable lane >> 3 of the two sides
+  int s_begin, nk;   // first sample, 64-sample blocks
+  int lane;
+  bool diag;         // both sides hold the same variables
+  double* out;       // the wave's 64 partial sums
+  float (*lds)[68];  // 32 rows of the wave's own (16-byte aligned, spread banks)
+};
+
+// The sums of both moments over the 64 lanes, in FP64, through the wave's own
+// LDS block: lane l writes its 32 sums as column l, then lane L adds, in FP64
+// and in lane order, sum L & 31 of lanes 32 (L >> 5) .. 32 (L >> 5) + 31, and
+// the two halves are added with one exchange; afterwards lane L < 32 holds sum
+// L = (a * 4 + c) * 2 + which of the walk (a, c): residual of a on c, a on the
+// j side if `transposed` (on a diagonal sub-block direction 1 of pair (c, a)
+// where a > c).  `bias` (of that walk index) is added to the log2 cosh sum.  No
+// barrier: a wave's LDS operations complete in the order it issues them, and
+// no other wave touches the block.
+__device__ __forceinline__ void pair_store(const PairWave& w, const float (&A)[16],
+                                           const float (&B)[16], double bias, bool transposed,
+                                           bool dir1) {
+  __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+#pragma unroll
+  for (int q = 0; q < 16; ++q) {
+    w.lds[2 * q][w.lane] = A[q];
+    w.lds[2 * q + 1][w.lane] = B[q];
+  }
+  __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+  double v0 = 0.0;
+  const float4* row = reinterpret_cast<const float4*>(&w.lds[w.lane & 31][(w.lane >> 5) * 32]);
+#pragma unroll
+  for (int j = 0; j < 8; ++j) {
+    const float4 f = row[j];
+    v0 += (double)f.x;
+    v0 += (double)f.y;
+    v0 += (double)f.z;
+    v0 += (double)f.w;
+  }
+  v0 += __shfl_xor(v0, 32);
+  if (w.lane < 32) {
+    const int a = w.lane >> 3, c = (w.lane >> 1) & 3, which = w.lane & 1;
+    const bool low = w.diag && a > c;
+    const int q = (transposed || low) ? c * 4 + a : a * 4 + c;  // i-major pair index
+    w.out[q * 4 + ((dir1 || low) ? 2 : 0) + which] = which ? v0 : v0 + bias;
+  }
+}
+
+// Row bases (wave-uniform) of one side; with a 32-bit per-lane byte offset
+// loads use the scalar-base + vector-offset form.
+__device__ __forceinline__ void pair_rows(const JobDev& J, const float* base, const int (&s)[4],
+                                          gchar_t* (&row)[4]) {
+#pragma unroll
+  for (int a = 0; a < 4; ++a) row[a] = (gchar_t*)(base + (int64_t)s[a] * J.ldz);
+}
+
+// One residual direction of the sub-block, the separate form.  The wave walks
+// its 4 x 4 block as (a, c): dir 0 scores residual i|j with i = a, j = c; dir 1
+// scores residual j|i with j = a, i = c.  Every lane keeps 64 running values
+// (16 pairs x {P, A, S1, S2}).
+__device__ __forceinline__ void pair_dir(const JobDev& J, const PairWave& w, int dir) {
+  gchar_t *zr[4], *zx[4];  // the regressed variables, the regressors
+  pair_rows(J, J.z, dir == 0 ? w.si : w.sj, zr);
+  pair_rows(J, J.z, dir == 0 ? w.sj : w.si, zx);
+  // each lane lost 1.5 a sample, of which the log2 of the halved cosh accounts
+  // for 1
+  double bias = 32.0 * (double)w.nk;
+  if (shared_job(J) && !w.diag) {
+    // the other waves of this pair may take the shared form, whose sums leave
+    // out the signed residuals': take this range's out too (al (sum of a - rho
+    // sum of c), the eight rows summed in FP64 by eight lanes each)
+    const float4* z = reinterpret_cast<const float4*>(J.z + (int64_t)w.row * J.ldz + w.s_begin) +
+                      (w.lane & 7);
+    double v = 0.0;
+#pragma unroll 8
+    for (int k = 0; k < 2 * w.nk; ++k) {
+      const float4 f = z[8 * k];
+      v += ((double)f.x + (double)f.y) + ((double)f.z + (double)f.w);
+    }
+#pragma unroll
+    for (int off = 4; off >= 1; off >>= 1) v += __shfl_xor(v, off);
+    const int a = (w.lane >> 3) & 3, c = (w.lane >> 1) & 3;
+    const double sa = __shfl(v, dir == 0 ? a * 8 : 32 + a * 8);
+    const double sc = __shfl(v, dir == 0 ? 32 + c * 8 : c * 8);
+    const int from = dir == 0 ? a * 4 + c : c * 4 + a;
+    // w.lo = -2 log2(e) al to a float's precision
+    bias += 0.5 * (double)__shfl(w.lo, from) * (sa - (double)__shfl(w.r, from) * sc);
+  }
+  float kr[16], kc[16];
+#pragma unroll
+  for (int q = 0; q < 16; ++q) {
+    const int from = dir == 0 ? q : (q & 3) * 4 + (q >> 2);
+    kr[q] = readlane_f(w.r, from);
+    const float lo = readlane_f(w.lo, from), hi = readlane_f(w.hi, from);
+    const int n_hi = __builtin_amdgcn_readlane(w.n_hi, from);
+    kc[q] = w.lane < n_hi ? hi : lo;
+  }
+  float P[16], A[16], S1[16], S2[16];  // A: this block's sum of |u| log2(e)
+#pragma unroll
+  for (int q = 0; q < 16; ++q) {
+    P[q] = 1.f;
+    A[q] = -kS1Start;
+    S1[q] = S2[q] = 0.f;
+  }
+  uint32_t voff = (uint32_t)(w.s_begin + w.lane) * 4u;
+  float xa[4], xb[4];
+#pragma unroll
+  for (int a = 0; a < 4; ++a) {
+    xa[a] = *(gfloat_t*)(zr[a] + voff);
+    xb[a] = *(gfloat_t*)(zx[a] + voff);
+  }
+  int kb = 0;
+  for (int k = 0; k < w.nk; ++k) {
+    // prefetch the next sample of every row; on the last iteration the stride
+    // is 0 and the current sample is re-read (always in bounds, no branch)
+    const bool more = k + 1 < w.nk;
+    voff += more ? 256u : 0u;
+    float na[4], nb[4];
+#pragma unroll
+    for (int a = 0; a < 4; ++a) {
+      na[a] = *(gfloat_t*)(zr[a] + voff);
+      nb[a] = *(gfloat_t*)(zx[a] + voff);
+    }
+#pragma unroll
+    for (int a = 0; a < 4; ++a) {
+      float t[4], m1[4], e1[4], e2[4];
+#pragma unroll
+      for (int c = 0; c < 4; ++c) {
+        const int q = a * 4 + c;
+        t[c] = fmaf(-kr[q], xb[c], xa[a]);
+        m1[c] = kc[q] * fabsf(t[c]);
+        e2[c] = (kM2 * m1[c]) * m1[c];
+      }
+      exp_first();
+#pragma unroll
+      for (int c = 0; c < 4; ++c) {
+        e1[c] = __builtin_amdgcn_exp2f(m1[c]);
+        e2[c] = __builtin_amdgcn_exp2f(e2[c]);
+      }
+      exp_done();
+#pragma unroll
+      for (int c = 0; c < 4; ++c) {
+        const int q = a * 4 + c;
+        P[q] = fmaf(P[q], e1[c], P[q]);
+        A[q] = fmaf(m1[c], -0.5f, A[q]);
+        S2[q] = fmaf(t[c], e2[c], S2[q]);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    if (++kb == kSumBlock || !more) {
+      const float off = 1.5f * (float)kb - kS1Start;  // exact
+#pragma unroll
+      for (int q = 0; q < 16; ++q) {
+        S1[q] += (A[q] - off) + __builtin_amdgcn_logf(P[q]);
+        P[q] = 1.f;
+        A[q] = -kS1Start;
+      }
+      kb = 0;
+    }
+#pragma unroll
+    for (int a = 0; a < 4; ++a) {
+      xa[a] = na[a];
+      xb[a] = nb[a];
+    }
+  }
+  pair_store(w, S1, S2, bias, dir == 1, dir == 1);
+}
+
+// Both residual directions, the shared form; side 0 takes the i variables as
+// x, side 1 the j variables.  False (nothing stored) if a product overflowed.
+__device__ __forceinline__ bool pair_both(const JobDev& J, const PairWave& w, int side) {
+  constexpr float kX2 = (float)(0.5 * kLog2e);  // rounds with relative error 1.3e-8
+  float kr[16], kc[16];
+#pragma unroll
+  for (int q = 0; q < 16; ++q) {
+    const int from = side == 0 ? q : (q & 3) * 4 + (q >> 2);
+    kr[q] = readlane_f(w.r, from);
+    const float lo = readlane_f(w.lo, from), hi = readlane_f(w.hi, from);
+    const int n_hi = __builtin_amdgcn_readlane(w.n_hi, from);
+    kc[q] = w.lane < n_hi ? hi : lo;
+  }
+  gchar_t *zx[4], *zy[4], *gx[4], *gy[4];
+  pair_rows(J, J.z, side == 0 ? w.si : w.sj, zx);
+  pair_rows(J, J.z, side == 0 ? w.sj : w.si, zy);
+  pair_rows(J, J.g, side == 0 ? w.si : w.sj, gx);
+  pair_rows(J, J.g, side == 0 ? w.sj : w.si, gy);
+  // u = residual of a (x side) on c: P, S; w = of c on a: Q, T
+  float P[16], Q[16], S[16], T[16];
+  uint32_t ex[16];  // sums of the biased exponents of P (low half) and Q
+  uint32_t top = 0;
+#pragma unroll
+  for (int q = 0; q < 16; ++q) {
+    P[q] = Q[q] = 1.f;
+    S[q] = T[q] = 0.f;
+    ex[q] = 0;
+  }
+  // the four pairs of variable a at one sample
+  auto shared_row = [&](int a, float x, float g, const float (&y)[4], const float (&h)[4]) {
+    const float x2 = (kX2 * x) * x;
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      const int q = a * 4 + c;
+      const float t = fmaf(-kr[q], y[c], x), v = fmaf(-kr[q], x, y[c]);
+      const float mu = kc[q] * t, mw = kc[q] * v, mg = fmaf(kM2 * mu, mu, x2);
+      exp_first();
+      const float eu = __builtin_amdgcn_exp2f(mu);
+      const float ew = __builtin_amdgcn_exp2f(mw);
+      const float e = __builtin_amdgcn_exp2f(mg);
+      exp_done();
+      P[q] = fmaf(P[q], eu, P[q]);
+      Q[q] = fmaf(Q[q], ew, Q[q]);
+      S[q] = fmaf(t, e * g, S[q]);
+      T[q] = fmaf(v, e * h[c], T[q]);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  };
+  struct Rows {
+    float x[4], y[4], gx[4], gy[4];
+  };
+  uint32_t voff = (uint32_t)(w.s_begin + w.lane) * 4u;
+  const uint32_t vlast = voff + (uint32_t)(w.nk - 1) * 256u;
+  auto load = [&](Rows& r) {  // past the last block: the last one again
+    const uint32_t v = voff < vlast ? voff : vlast;
+#pragma unroll
+    for (int a = 0; a < 4; ++a) {
+      r.x[a] = *(gfloat_t*)(zx[a] + v);
+      r.y[a] = *(gfloat_t*)(zy[a] + v);
+      r.gx[a] = *(gfloat_t*)(gx[a] + v);
+      r.gy[a] = *(gfloat_t*)(gy[a] + v);
+    }
+    voff += 256u;
+  };
+  auto eval = [&](const Rows& r) {
+#pragma unroll
+    for (int a = 0; a < 4; ++a) shared_row(a, r.x[a], r.gx[a], r.y, r.gy);
+  };
+  // two blocks a turn, each loaded while the other is evaluated
+  Rows r0, r1;
+  load(r0);
+  int nf = 0;
+  for (int left = w.nk; left > 0; left -= kRenorm, ++nf) {
+    const int cnt = left < kRenorm ? left : kRenorm;
+    for (int k = 0; k + 1 < cnt; k += 2) {
+      load(r1);
+      eval(r0);
+      load(r0);
+      eval(r1);
+    }
+    if (cnt & 1) eval(r0);  // the last block of the range (kRenorm is even)
+#pragma unroll
+    for (int q = 0; q < 16; ++q) {
+      const uint32_t p = __float_as_uint(P[q]), o = __float_as_uint(Q[q]);
+      top = max(top, max(p, o));  // both positive: ordered as integers
+      ex[q] += ((o >> 23) << 16) + (p >> 23);
+      P[q] = __uint_as_float((p & 0x7fffffu) | 0x3f800000u);
+      Q[q] = __uint_as_float((o & 0x7fffffu) | 0x3f800000u);
+    }
+  }
+  if (__any(top >= 0x7f800000u)) return false;
+  // log2 of each lane's product less 1.5 a sample (its mean is near that, so
+  // FP32 holds the difference to 1e-6), put back less the count in FP64
+  const int mid = w.nk + (w.nk >> 1);
+  const int base = 127 * nf + mid;
+#pragma unroll
+  for (int q = 0; q < 16; ++q) {
+    P[q] = (float)((int)(ex[q] & 0xffffu) - base) + __builtin_amdgcn_logf(P[q]);
+    Q[q] = (float)((int)(ex[q] >> 16) - base) + __builtin_amdgcn_logf(Q[q]);
+  }
+  const double bias = 64.0 * (double)(mid - w.nk);
+  pair_store(w, P, S, bias, side == 1, side == 1);
+  pair_store(w, Q, T, bias, side == 1, side == 0);
+  return true;
+}
+
 template <int kMode, int W>
 __device__ __forceinline__ void pair_item(const JobDev& J, const JobStep& S, int local,
                                           int wave, int lane) {
@@ -427,9 +809,7 @@ __device__ __forceinline__ void pair_item(const JobDev& J, const JobStep& S, int
   const int split_len = kMode == kModeCand ? S.split_len_c
                         : kMode == kModeSusp ? S.split_len_s
                                              : S.split_len;
-  const int per_tile = 2 * nsplit;
-  const int tile = local / per_tile, rem = local - tile * per_tile;
-  const int dir = rem / nsplit, split = rem - dir * nsplit;
+  const int tile = local / nsplit, split = local - tile * nsplit;
   int bi, bj;
   if (kCand) {
     const int ncol = kMode == kModeExt ? cdiv(S.ne, kTileVars) : S.nblk;
@@ -440,163 +820,62 @@ __device__ __forceinline__ void pair_item(const JobDev& J, const JobStep& S, int
   }
   const int wi = wave >> 1, wj = wave & 1;
   if (!kCand && bi == bj && wi > wj) return;  // mirror image of quadrant (wj, wi)
-  // A quadrant on the diagonal has the same variables on both sides, so its
-  // direction-0 walk (a, c) with a != c already holds both residual
-  // directions of each of its 6 pairs (a > c: the larger position regressed
-  // on the smaller, which is direction 1 of pair (c, a)); its direction-1
-  // item has nothing left to do.  Same rows, coefficients and samples per
-  // lane as that item would use, so the sums are the same bits.
-  const bool diagq = !kCand && bi == bj && wi == wj;
-  if (diagq && dir == 1) return;
   // i side: positions bi * 8 + .. (all pairs) or list entries (candidate /
   // suspect rows; list padding holds position m)
   const int i0 = bi * kTileVars + wi * kWaveVars, pj0 = bj * kTileVars + wj * kWaveVars;
   const int32_t* act = J.act;
   const int32_t* list = kMode == kModeCand ? J.cand : J.cand2;
-  const int64_t ldz = J.ldz, ldr = J.d;
   auto ipos = [&](int a) { return kCand ? list[i0 + a] : i0 + a; };
   auto jpos = [&](int a) { return kMode == kModeExt ? J.ext[pj0 + a] : pj0 + a; };
 
-  // The wave walks its 4 x 4 block as (a, c): dir 0 scores residual i|j with
-  // i = pi0 + a, j = pj0 + c; dir 1 scores residual j|i with j = pj0 + a,
-  // i = pi0 + c.  Lane q < 16 computes the coefficients of walk index q.
-  // The scale c1 = -2 log2(e) / sqrt(1 - r^2) of a pair is not rounded to one
-  // FP32 value (that would scale every sample of the pair by the same
-  // rounding error and bias its log cosh moment): lanes below n_hi take the
-  // FP32 value above c1, the others the one below, so the lanes' mean is c1
-  // to 1/128 of a float spacing and the sample-to-lane assignment carries no
-  // bias (a lane's samples are s = lane, lane + 64, ...).
-  float my_r = 0.f, my_lo = 0.f, my_hi = 0.f;
-  int my_n = 0;
+  __shared__ __align__(16) float red[W][32][68];
+  PairWave w;
+  w.lane = lane;
+  w.lds = red[threadIdx.x >> 6];
+  // opaque: where the compiler knows it to be 0 (the row modes) it merges paths
+  // and spills 85 registers
+  int diag = !kCand && bi == bj && wi == wj;
+  asm("" : "+v"(diag));
+  w.diag = __builtin_amdgcn_readfirstlane(diag);
+  double* part = kMode == kModeAll ? J.part : (kMode == kModeCand ? J.partc : J.parts);
+  w.out = part + (((int64_t)split * ntiles + tile) * 4 + wave) * 64;
+  w.s_begin = split * split_len;
+  w.nk = (min(w.s_begin + split_len, J.n_pad) - w.s_begin) / 64;
+  w.r = w.lo = w.hi = 0.f;
+  w.n_hi = 0;
   {
-    const int q = lane & 15, a = q >> 2, c = q & 3;
-    const int pi = ipos(dir == 0 ? a : c), pj = jpos(dir == 0 ? c : a);
-    const bool valid = pi < m && pj < m && pi != pj;
-    if (valid) {
-      double r = J.rho[(int64_t)act[pi] * ldr + act[pj]];
+    const int pi = ipos((lane >> 2) & 3), pj = jpos(lane & 3);
+    if (pi < m && pj < m && pi != pj) {
+      double r = J.rho[(int64_t)act[pi] * J.d + act[pj]];
       const double lim = 1.0 - kCollinear;
       r = r > lim ? lim : (r < -lim ? -lim : r);
       const double c1 = -2.0 * kLog2e * rsqrt(1.0 - r * r);
-      my_r = (float)r;
-      dither_float(c1, my_lo, my_hi, my_n);
+      w.r = (float)r;
+      dither_float(c1, w.lo, w.hi, w.n_hi);
     }
   }
-  float kr[16], kc[16];
-#pragma unroll
-  for (int q = 0; q < 16; ++q) {
-    kr[q] = readlane_f(my_r, q);
-    const float lo = readlane_f(my_lo, q), hi = readlane_f(my_hi, q);
-    const int n_hi = __builtin_amdgcn_readlane(my_n, q);
-    kc[q] = lane < n_hi ? hi : lo;
-  }
-  // Row bases (wave-uniform) and a 32-bit per-lane byte offset, so loads use
-  // the scalar-base + vector-offset form.  zr = rows of the regressed
-  // variables (the residual's own variable), zx = rows of the regressors.
-  gchar_t* zr[4];
-  gchar_t* zx[4];
-#pragma unroll
-  for (int a = 0; a < 4; ++a) {
-    const int pi = ipos(a), pj = jpos(a);
-    const int pr = dir == 0 ? pi : pj, px = dir == 0 ? pj : pi;
-    // the row ids are wave-uniform: keep them (and the row bases) in SGPRs
-    const int sr = __builtin_amdgcn_readfirstlane(pr < m ? act[pr] : J.d);
-    const int sx = __builtin_amdgcn_readfirstlane(px < m ? act[px] : J.d);
-    zr[a] = (gchar_t*)(J.z + (int64_t)sr * ldz);
-    zx[a] = (gchar_t*)(J.z + (int64_t)sx * ldz);
-  }
-
-  const int s_begin = split * split_len;
-  const int s_end = min(s_begin + split_len, J.n_pad);
-  const int nk = (s_end - s_begin) / 64;
-
-  float P[16], S1[16], S2[16];
-#pragma unroll
-  for (int q = 0; q < 16; ++q) {
-    P[q] = 1.f;
-    S1[q] = -kS1Start;
-    S2[q] = 0.f;
-  }
-  uint32_t voff = (uint32_t)(s_begin + lane) * 4u;
-  float xa[4], xb[4];
-#pragma unroll
-  for (int a = 0; a < 4; ++a) {
-    xa[a] = *(gfloat_t*)(zr[a] + voff);
-    xb[a] = *(gfloat_t*)(zx[a] + voff);
-  }
-  int kb = 0;
-  for (int k = 0; k < nk; ++k) {
-    // prefetch the next sample of every row; on the last iteration the stride
-    // is 0 and the current sample is re-read (always in bounds, no branch)
-    const bool more = k + 1 < nk;
-    voff += more ? 256u : 0u;
-    float na[4], nb[4];
-#pragma unroll
-    for (int a = 0; a < 4; ++a) {
-      na[a] = *(gfloat_t*)(zr[a] + voff);
-      nb[a] = *(gfloat_t*)(zx[a] + voff);
-    }
-#pragma unroll
-    for (int a = 0; a < 4; ++a) {
-#pragma unroll
-      for (int c = 0; c < 4; ++c) {
-        const int q = a * 4 + c;
-        eval_dir_lane(xa[a], xb[c], kr[q], kc[q], P[q], S1[q], S2[q]);
-      }
-    }
-    if (++kb == kLogBlock || !more) {
-      const float off = 1.5f * (float)kb;  // exact
-#pragma unroll
-      for (int q = 0; q < 16; ++q) {
-        S1[q] += __builtin_amdgcn_logf(P[q]) - off;
-        P[q] = 1.f;
-      }
-      kb = 0;
-    }
-#pragma unroll
-    for (int a = 0; a < 4; ++a) {
-      xa[a] = na[a];
-      xb[a] = nb[a];
-    }
-  }
-
-  // FP64 sums over the 64 lanes through the wave's own LDS block: lane l
-  // writes its 32 sums as column l, then lane L adds, in FP64 and in lane
-  // order, sum L & 31 of lanes 32 (L >> 5) .. 32 (L >> 5) + 31, and the two
-  // halves are added with one exchange; afterwards lane L < 32 holds sum L.
-  // No barrier: a wave's LDS operations complete in the order it issues
-  // them, and no other wave touches the block.
-  constexpr int kPitch = 68;  // floats per row: 16-byte aligned rows, spread banks
-  __shared__ __align__(16) float red[W][32][kPitch];
-  float(*T)[kPitch] = red[threadIdx.x >> 6];
-#pragma unroll
-  for (int q = 0; q < 16; ++q) {
-    T[2 * q][lane] = S1[q];
-    T[2 * q + 1][lane] = S2[q];
-  }
-  __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-  double v0 = 0.0;
   {
-    const float4* row = reinterpret_cast<const float4*>(&T[lane & 31][(lane >> 5) * 32]);
+    const int e = (lane >> 3) & 3, p = lane < 32 ? ipos(e) : jpos(e);
+    w.row = p < m ? act[p] : J.d;
+  }
 #pragma unroll
-    for (int j = 0; j < 8; ++j) {
-      const float4 f = row[j];
-      v0 += (double)f.x;
-      v0 += (double)f.y;
-      v0 += (double)f.z;
-      v0 += (double)f.w;
-    }
+  for (int a = 0; a < 4; ++a) {  // wave-uniform: the row bases stay in SGPRs
+    w.si[a] = __builtin_amdgcn_readlane(w.row, a * 8);
+    w.sj[a] = __builtin_amdgcn_readlane(w.row, 32 + a * 8);
   }
-  v0 += __shfl_xor(v0, 32);
-  if (lane < 32) {
-    // sum L = (a * 4 + c) * 2 + which, (a, c) in this direction's walk order;
-    // on a diagonal quadrant the walk's lower half is direction 1
-    const int a = lane >> 3, c = (lane >> 1) & 3, which = lane & 1;
-    const bool flip = dir == 1 || (diagq && a > c);
-    const int q = flip ? c * 4 + a : a * 4 + c;  // pair index (i-major) of the tile
-    double* part = kMode == kModeAll ? J.part : (kMode == kModeCand ? J.partc : J.parts);
-    part[(((int64_t)split * ntiles + tile) * 4 + wave) * 64 + q * 4 + (flip ? 2 : 0) + which] =
-        v0;
+  if (!w.diag && shared_job(J) && w.nk <= kShareMaxIters) {
+    // does either side (i: the lower lanes) reach past kShareTop?
+    const double top = w.row < J.d ? J.mom[(int64_t)w.row * 8 + kMomTop] : 0.0;
+    const uint64_t far = __ballot(!(top <= kShareTop));
+    const int side = (uint32_t)far == 0 ? 0 : (far >> 32 == 0 ? 1 : -1);
+    if (side >= 0 && pair_both(J, w, side)) return;
   }
+  // A quadrant on the diagonal has the same variables on both sides, so its
+  // direction-0 walk (a, c) with a != c already holds both residual
+  // directions of each of its 6 pairs.
+  const int ndir = w.diag ? 1 : 2;
+#pragma clang loop unroll(disable)
+  for (int dir = 0; dir < ndir; ++dir) pair_dir(J, w, dir);
 }
 
 }  // namespace

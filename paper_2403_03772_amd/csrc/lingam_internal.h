@@ -28,10 +28,9 @@ constexpr int kTileVars = 8;
 constexpr int kWaveVars = 4;
 // Samples are padded to a multiple of this (one wavefront of samples).
 constexpr int kSampleQuantum = 64;
-// Resident waves per CU of the pair kernels (their register budget allows 5
-// waves per SIMD): the bounded grids of the gated full step and of the
-// suspect and extension passes launch kPairWavesPerCu / w workgroups of w
-// waves per CU.
+// The bounded grids of the gated full step and of the suspect and extension
+// passes launch kPairWavesPerCu / w workgroups of w waves per CU (the pair
+// kernels hold 12 waves a CU: 3 a SIMD by their registers).
 constexpr int kPairWavesPerCu = 16;
 // Steps with at most this many active variables run the FP64 pair kernel.
 constexpr int kFp64MaxM = 64;
@@ -134,7 +133,8 @@ struct Layout {
   size_t part;   // double [part_elems] pair-kernel partial sums
   size_t rmat;   // double [d * d]  pairwise measure R by position
   size_t mvec;   // double [d]      per-position measure -k
-  size_t mom;    // double [d * 8]  moments of z by original id (E lc, E g, E z^3, E z^4, E|z|)
+  size_t mom;    // double [d * 8]  moments of z by original id (E lc, E g, E z^3, E z^4, E|z|,
+                 // max |z|)
   // learned form (K > 0 only)
   int32_t K;
   size_t feat;   // float  [d * kFeat] features by position
@@ -157,6 +157,9 @@ struct Layout {
   // FP64 tie resolution (every job)
   size_t tie;      // int32  [kMaxTie] near-tied positions of the current step
   size_t tie_r;    // double [kMaxTie * d] their FP64 measure rows, then their k [kMaxTie]
+  // exp(-z^2 / 2) of the FP32 copy's samples for the pair kernels' shared form
+  // (0: the layout has no such region, the kernels take the separate form)
+  size_t g;        // float  [(d + 1) * ldz]
   size_t total;
   size_t part_elems;
   size_t partc_elems;
@@ -176,6 +179,7 @@ struct JobDev {
   int32_t forced_len, n_src;  // n_src: rows of X (bounds of `rows`)
   double* zd;
   float* z;
+  float* g;              // exp(-z^2 / 2), laid out as z; NULL: not kept
   double* mu;
   double* sig;
   double* rho;
@@ -201,9 +205,9 @@ struct JobDev {
   double* lb;
   int32_t* wit;
   int32_t* ext;
-  int32_t ne_max;        // extension columns per learned step (0: none)
   int32_t* steplog;
   int32_t cap_s;
+  int32_t ne_max;        // extension columns per learned step (0: none)
   int32_t* cand2;
   double* parts;
   double* rc2;
@@ -267,7 +271,7 @@ __host__ __device__ inline int32_t step_topk(int32_t m, int32_t K) {
 
 // Workgroup-count kinds with a prefix array each.
 enum Kind : int {
-  kKPair = 0,   // k_pair: ntiles * 2 * nsplit * q_all
+  kKPair = 0,   // k_pair: ntiles * nsplit * q_all
   kKComb,       // k_combine: ceil(ntiles / 4)
   kKP64,        // k_pair64: ceil(m (m - 1) / 2 / 4)
   kKRowk,       // k_rowk: ceil(m / 4)
@@ -276,16 +280,16 @@ enum Kind : int {
   kKFeat,       // k_features: ceil(m / 4)
   kKMlp,        // k_mlp: ceil(m / 16)
   kKTopk,       // k_topk: 1
-  kKPairC,      // k_pair_cand: nct * 2 * nsplit_c * q_rows
+  kKPairC,      // k_pair_cand: nct * nsplit_c * q_rows
   kKCombC,      // k_combine_cand: ceil(nct / 4)
   kKRowkC,      // k_cand_k rows: K / 4
   kKColC,       // k_cand_k columns: ceil(m / 64)
   kKLsel,       // k_lselect: 1
   kKWit,        // k_pair_wit: m
-  kKPairE,      // k_pair_ext: nct3 * 2 * nsplit * q_rows (after the learned decision)
+  kKPairE,      // k_pair_ext: nct3 * nsplit * q_rows (after the learned decision)
   kKBoundE,     // k_ext_bound: ceil(nsus / 4) when nct3 > 0
   kKCompE,      // k_ext_compact: 1 when nct3 > 0
-  kKPairS,      // k_pair_susp: nct2 * 2 * nsplit_s * q_rows (after the learned decision)
+  kKPairS,      // k_pair_susp: nct2 * nsplit_s * q_rows (after the learned decision)
   kKCombS,      // k_combine_susp: ceil(nct2 / 4)
   kKRowkS,      // k_susp_rowk: ceil(nsus / 4)
   kKLsel2,      // k_lselect2: 1 when nsus > 0
@@ -452,7 +456,7 @@ __host__ __device__ inline int32_t kind_count(const JobStep& s, int kind) {
   if (s.m < 2) return 0;
   if (s.gate && gated_kind(kind)) return 0;
   switch (kind) {
-    case kKPair: return s.fp64 ? 0 : s.ntiles * 2 * s.nsplit * s.q_all;
+    case kKPair: return s.fp64 ? 0 : s.ntiles * s.nsplit * s.q_all;
     case kKComb: return s.fp64 ? 0 : cdiv(s.ntiles, 4);
     case kKP64: return s.fp64 ? cdiv((int64_t)s.m * (s.m - 1) / 2, 4) : 0;
     case kKRowk: return cdiv(s.m, 4);
@@ -461,16 +465,16 @@ __host__ __device__ inline int32_t kind_count(const JobStep& s, int kind) {
     case kKFeat: return s.feat ? cdiv(s.m, 4) : 0;
     case kKMlp: return s.learned ? cdiv(s.m, 16) : 0;
     case kKTopk: return s.learned ? 1 : 0;
-    case kKPairC: return s.learned ? s.nct * 2 * s.nsplit_c * s.q_rows : 0;
+    case kKPairC: return s.learned ? s.nct * s.nsplit_c * s.q_rows : 0;
     case kKCombC: return s.learned ? cdiv(s.nct, 4) : 0;
     case kKRowkC: return s.learned ? cdiv(s.k, 4) : 0;
     case kKColC: return s.learned ? cdiv(s.m, 64) : 0;
     case kKLsel: return s.learned ? 1 : 0;
     case kKWit: return s.learned ? s.m : 0;
-    case kKPairE: return s.nct3 * 2 * s.nsplit * s.q_rows;
+    case kKPairE: return s.nct3 * s.nsplit * s.q_rows;
     case kKBoundE: return s.nct3 > 0 ? cdiv(s.nsus, 4) : 0;
     case kKCompE: return s.nct3 > 0 ? 1 : 0;
-    case kKPairS: return s.nct2 * 2 * s.nsplit_s * s.q_rows;
+    case kKPairS: return s.nct2 * s.nsplit_s * s.q_rows;
     case kKCombS: return cdiv(s.nct2, 4);
     case kKRowkS: return cdiv(s.nsus, 4);
     case kKLsel2: return s.nsus > 0 ? 1 : 0;
@@ -491,7 +495,8 @@ __host__ __device__ inline int32_t setup_count(int32_t n_pad, int32_t d, int kin
 }
 
 // K > 0 adds the regions of the learned form.
-Layout make_layout(int64_t n, int64_t d, int num_cu, int K = 0);
+// share: with the region of exp(-z^2 / 2) (the last one).
+Layout make_layout(int64_t n, int64_t d, int num_cu, int K = 0, bool share = true);
 
 // Schedule buffer of a batch (device): per step, JobStep[njobs] and
 // kNumKinds prefix arrays of njobs + 1 entries; for the set-up,
@@ -599,8 +604,10 @@ struct VarLayout {
 };
 
 VarLayout make_var_layout(int64_t T, int64_t d, int lags, int num_cu);
-// `ws` is the VAR block, `job` the base of the ordering job's regions.
-hipError_t launch_var_fit(const VarLayout& V, char* ws, char* job, const float* X, int64_t ldx,
+// `ws` is the VAR block, `job` the base of the ordering job's regions, G its
+// exp(-z^2 / 2) region or NULL.
+hipError_t launch_var_fit(const VarLayout& V, char* ws, char* job, float* G, const float* X,
+                          int64_t ldx,
                           float* resid_out, double* M_out, hipStream_t st);
 hipError_t launch_save_rho(const VarLayout& V, char* ws, char* job, hipStream_t st);
 hipError_t launch_b0(const VarLayout& V, char* ws, char* job, const int32_t* order, double* B0,

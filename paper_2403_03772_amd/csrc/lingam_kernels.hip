@@ -25,8 +25,9 @@
 // which is what a fresh Gram of the updated (standardized) residuals gives in
 // exact arithmetic, at O(m^2) instead of O(n m^2) per step.
 //
-// Arithmetic of the hot loop (per sample, per direction), with u = alpha t,
-// t = x - rho y, alpha = 1/sqrt(1 - rho^2):
+// Arithmetic of the hot loop (per sample, per direction; its separate form, the
+// shared form for both directions at once stands with the loop), with u = alpha
+// t, t = x - rho y, alpha = 1/sqrt(1 - rho^2):
 //   log cosh u = ln2 * ( |u| log2(e) + log2((1 + e^{-2|u|}) / 2) )
 //   m1 = -2 alpha log2(e) |t|    (the pair constant dithered over the lanes
 //                                 between its two FP32 neighbours: one FP32
@@ -35,11 +36,11 @@
 //   e1 = 2^m1 = e^{-2|u|};  m2 = -m1^2 / (8 log2 e) = -u^2 log2(e) / 2;
 //   e2 = 2^m2 = e^{-u^2/2}
 //   S1 += -m1/2 ;  P *= (1 + e1) ;  S2 += t e2
-// and every kLogBlock samples S1 += log2(P) - 1.5 count, P = 1.  The sum of
-// the logs is taken as the log of the product, which leaves two hardware
+// and every few samples S1 += log2(P) - 1.5 count, P = 1.  The sum of the logs
+// is taken as the log of the product, which leaves two hardware
 // transcendentals (v_exp_f32) per evaluation instead of three; subtracting
-// 1.5 per sample (exact in FP32) keeps the running sum near its start value
-// -kS1Start, so its rounding stays small.  Lane sums are combined in FP64.
+// 1.5 per sample (exact in FP32) keeps the running sum near its start value,
+// so its rounding stays small.  Lane sums are combined in FP64.
 //
 // Precision: the residuals are kept in FP64 (Zd) and the hot loop reads an
 // FP32 copy (Z) rounded afresh at every step; marginal entropies and every
@@ -267,7 +268,10 @@ __global__ __launch_bounds__(256) void k_ingest(const JobDev* __restrict__ jobs,
     const int vl = ty * 16 + i, v = v0 + vl, s = s0 + tx;
     if (v <= J.d && s < J.n_pad) {
       J.zd[(int64_t)v * J.ldz + s] = (double)tile[tx][vl];
-      if (v == J.d) J.z[(int64_t)v * J.ldz + s] = 0.f;
+      if (v == J.d) {
+        J.z[(int64_t)v * J.ldz + s] = 0.f;
+        if (J.g) J.g[(int64_t)v * J.ldz + s] = 1.f;
+      }
     }
   }
   if (bad) set_status(J.ctrl, kStDegenerate);
@@ -371,12 +375,13 @@ __global__ __launch_bounds__(256) void k_gram(const JobDev* __restrict__ jobs, i
 // entropy H(z) of every variable (FP64).
 __global__ __launch_bounds__(256) void k_standardize(const JobDev* __restrict__ jobs, int njobs,
                                                      const int32_t* __restrict__ spre) {
-  __shared__ double sh[5 * 4];
+  __shared__ double sh[7 * 4];
   int j, v;
   if (!locate(spre, njobs, blockIdx.x, j, v)) return;
   const JobDev& J = jobs[j];
   double* zd = J.zd + (int64_t)v * J.ldz;
   float* zf = J.z + (int64_t)v * J.ldz;
+  float* zg = J.g ? J.g + (int64_t)v * J.ldz : nullptr;
   const double m = J.mu[v], is = 1.0 / J.sig[v];
   const int n = J.n;
   MomAcc ma;
@@ -385,14 +390,16 @@ __global__ __launch_bounds__(256) void k_standardize(const JobDev* __restrict__ 
       const double z = (zd[k] - m) * is;
       zd[k] = z;
       zf[k] = (float)z;
-      ma.add(z);
+      const double e = ma.add(z);
+      if (zg) zg[k] = (float)e;
     } else {
       zf[k] = 0.f;
+      if (zg) zg[k] = 1.f;
     }
   }
-  double acc[5];
+  double acc[7];
   ma.sums(acc);
-  block_sum_5(acc, sh);
+  block_moments(acc, sh);
   if (threadIdx.x == 0) store_moments(J, v, acc, n);
 }
 
@@ -401,7 +408,7 @@ __global__ __launch_bounds__(256) void k_standardize(const JobDev* __restrict__ 
 // ---------------------------------------------------------------------------
 
 template <int W>
-__global__ __launch_bounds__(64 * W) void k_pair(const JobDev* __restrict__ jobs, int njobs,
+__global__ __launch_bounds__(64 * W, 3) void k_pair(const JobDev* __restrict__ jobs, int njobs,
                                                  const JobStep* __restrict__ js,
                                                  const int32_t* __restrict__ pre, int G) {
   pair_tiles<kModeAll, false, W>(jobs, njobs, js, pre, G);
@@ -410,7 +417,7 @@ __global__ __launch_bounds__(64 * W) void k_pair(const JobDev* __restrict__ jobs
 // The same kernel for gated launches (learned form): a bounded grid walks the
 // step's items.
 template <int W>
-__global__ __launch_bounds__(64 * W) void k_pair_loop(const JobDev* __restrict__ jobs,
+__global__ __launch_bounds__(64 * W, 3) void k_pair_loop(const JobDev* __restrict__ jobs,
                                                          int njobs,
                                                          const JobStep* __restrict__ js,
                                                          const int32_t* __restrict__ pre,
@@ -420,7 +427,6 @@ __global__ __launch_bounds__(64 * W) void k_pair_loop(const JobDev* __restrict__
 
 // Sum the sample splits (FP64, fixed order), form both residual entropies and
 // the likelihood ratio of every pair, write R by position (antisymmetric).
-// The S1 sums carry an offset of nsplit * 64 * kS1Start + 0.5 n_pad.
 __global__ __launch_bounds__(256) void k_combine(const JobDev* __restrict__ jobs, int njobs,
                                                  const JobStep* __restrict__ js,
                                                  const int32_t* __restrict__ pre) {
@@ -443,16 +449,7 @@ __global__ __launch_bounds__(256) void k_combine(const JobDev* __restrict__ jobs
 #pragma unroll
     for (int c = 0; c < 4; ++c) s[c] += src[c];
   }
-  const double s1_bias = (double)S.nsplit * 64.0 * (double)kS1Start + 0.5 * (double)J.n_pad;
-  const double inv_n = 1.0 / (double)J.n;
-  const int si = J.act[pi], sj = J.act[pj];
-  double r = J.rho[(int64_t)si * J.d + sj];
-  const double lim = 1.0 - kCollinear;
-  r = r > lim ? lim : (r < -lim ? -lim : r);
-  const double al = 1.0 / sqrt(1.0 - r * r);
-  const double h_ij = entropy_from_moments(kLn2 * (s[0] + s1_bias) * inv_n, al * s[1] * inv_n);
-  const double h_ji = entropy_from_moments(kLn2 * (s[2] + s1_bias) * inv_n, al * s[3] * inv_n);
-  const double Rv = (J.hm[sj] + h_ij) - (J.hm[si] + h_ji);
+  const double Rv = measure_from_sums(J, J.act[pi], J.act[pj], s, bi == bj && wi == wj);
   J.rmat[(int64_t)pi * J.d + pj] = Rv;
   J.rmat[(int64_t)pj * J.d + pi] = -Rv;
   });
@@ -715,7 +712,7 @@ __global__ __launch_bounds__(256) void k_tie(const JobDev* __restrict__ jobs, in
 __global__ __launch_bounds__(256) void k_resid(const JobDev* __restrict__ jobs, int njobs,
                                                const JobStep* __restrict__ js,
                                                const int32_t* __restrict__ pre) {
-  __shared__ double sh[5 * 4];
+  __shared__ double sh[7 * 4];
   int jb, p;
   if (!locate(pre, njobs, blockIdx.x, jb, p)) return;
   const JobDev& J = jobs[jb];
@@ -733,6 +730,7 @@ __global__ __launch_bounds__(256) void k_resid(const JobDev* __restrict__ jobs, 
   double* zp = J.zd + (int64_t)sp * ldz;
   const double* ze = J.zd + (int64_t)se * ldz;
   float* zf = J.z + (int64_t)sp * ldz;
+  float* zg = J.g ? J.g + (int64_t)sp * ldz : nullptr;
   const int n = J.n;
   MomAcc ma;
   // four samples per thread in flight: all loads are issued before the stores
@@ -754,13 +752,14 @@ __global__ __launch_bounds__(256) void k_resid(const JobDev* __restrict__ jobs, 
         const double z = al * (a[u] - r * b[u]);  // padded samples stay 0
         zp[k] = z;
         zf[k] = (float)z;
-        if (k < n) ma.add(z);
+        const double e = k < n ? ma.add(z) : 1.0;
+        if (zg) zg[k] = (float)e;
       }
     }
   }
-  double acc[5];
+  double acc[7];
   ma.sums(acc);
-  block_sum_5(acc, sh);
+  block_moments(acc, sh);
   if (threadIdx.x == 0) store_moments(J, sp, acc, n);
   double* rho_p = J.rho + (int64_t)sp * ldr;
   for (int q = threadIdx.x; q < m_after; q += 256) {
@@ -906,8 +905,10 @@ __global__ __launch_bounds__(64) void k_var_resid(const double* __restrict__ Xd,
   }
 }
 
-// Zero the sample padding of Zd rows 0..d-1 and all of row d of Zd and Z.
-__global__ void k_zero_pad(double* Zd, float* Z, int64_t ldz, int d, int n, int n_pad) {
+// Zero the sample padding of Zd rows 0..d-1 and all of row d of Zd and Z (1 in
+// row d of G, if given).
+__global__ void k_zero_pad(double* Zd, float* Z, float* G, int64_t ldz, int d, int n,
+                           int n_pad) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   const int64_t tail = (int64_t)(n_pad - n);
   if (i < (int64_t)d * tail) {
@@ -917,6 +918,7 @@ __global__ void k_zero_pad(double* Zd, float* Z, int64_t ldz, int d, int n, int 
   if (i < n_pad) {
     Zd[(int64_t)d * ldz + i] = 0.0;
     Z[(int64_t)d * ldz + i] = 0.f;
+    if (G) G[(int64_t)d * ldz + i] = 1.f;
   }
 }
 
@@ -1055,7 +1057,7 @@ __global__ void k_fill_i32(int32_t* __restrict__ p, int64_t n, int32_t v) {
 
 static size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
 
-Layout make_layout(int64_t n, int64_t d, int num_cu, int K) {
+Layout make_layout(int64_t n, int64_t d, int num_cu, int K, bool share) {
   Layout L{};
   L.n = n;
   L.d = d;
@@ -1141,6 +1143,8 @@ Layout make_layout(int64_t n, int64_t d, int num_cu, int K) {
     L.rc2 = take(sizeof(double) * (size_t)(L.cap_s > 0 ? L.cap_s : 1) * (size_t)d);
     L.kc2 = take(sizeof(double) * (size_t)(L.cap_s > 0 ? L.cap_s : 1));
   }
+  // last, so that every other region lies where it lies without it
+  if (share) L.g = take(sizeof(float) * (size_t)(d + 1) * (size_t)L.ldz);
   L.total = off;
   return L;
 }
@@ -1358,7 +1362,7 @@ VarLayout make_var_layout(int64_t T, int64_t d, int lags, int num_cu) {
   return V;
 }
 
-hipError_t launch_var_fit(const VarLayout& V, char* ws, char* job, const float* X,
+hipError_t launch_var_fit(const VarLayout& V, char* ws, char* job, float* G, const float* X,
                           int64_t ldx_in, float* resid_out, double* M_out, hipStream_t st) {
   const Layout& L = V.ord;
   Ctrl* ctrl = at<Ctrl>(job, L.ctrl);
@@ -1387,7 +1391,7 @@ hipError_t launch_var_fit(const VarLayout& V, char* ws, char* job, const float* 
                      W, V.q, at<double>(job, L.zd), L.ldz, resid_out, M_out);
   const int64_t zn = (L.d * (L.n_pad - L.n) > L.n_pad) ? L.d * (L.n_pad - L.n) : L.n_pad;
   hipLaunchKernelGGL(k_zero_pad, dim3((unsigned)((zn + 255) / 256)), dim3(256), 0, st,
-                     at<double>(job, L.zd), at<float>(job, L.z), L.ldz, (int)L.d, (int)L.n,
+                     at<double>(job, L.zd), at<float>(job, L.z), G, L.ldz, (int)L.d, (int)L.n,
                      (int)L.n_pad);
   return hipGetLastError();
 }

@@ -617,7 +617,7 @@ __global__ __launch_bounds__(1024) void k_topk(const JobDev* __restrict__ jobs, 
 // ---------------------------------------------------------------------------
 
 template <int W>
-__global__ __launch_bounds__(64 * W) void k_pair_cand(const JobDev* __restrict__ jobs, int njobs,
+__global__ __launch_bounds__(64 * W, 3) void k_pair_cand(const JobDev* __restrict__ jobs, int njobs,
                                                       const JobStep* __restrict__ js,
                                                       const int32_t* __restrict__ pre, int G) {
   pair_tiles<kModeCand, false, W>(jobs, njobs, js, pre, G);
@@ -815,16 +815,7 @@ __global__ __launch_bounds__(256) void k_combine_cand(const JobDev* __restrict__
 #pragma unroll
     for (int c = 0; c < 4; ++c) s[c] += src[c];
   }
-  const double s1_bias = (double)S.nsplit_c * 64.0 * (double)kS1Start + 0.5 * (double)J.n_pad;
-  const double inv_n = 1.0 / (double)J.n;
-  const int si = J.act[pi], sj = J.act[pj];
-  double r = J.rho[(int64_t)si * J.d + sj];
-  const double lim = 1.0 - kCollinear;
-  r = r > lim ? lim : (r < -lim ? -lim : r);
-  const double al = 1.0 / sqrt(1.0 - r * r);
-  const double h_ij = entropy_from_moments(kLn2 * (s[0] + s1_bias) * inv_n, al * s[1] * inv_n);
-  const double h_ji = entropy_from_moments(kLn2 * (s[2] + s1_bias) * inv_n, al * s[3] * inv_n);
-  *out = (J.hm[sj] + h_ij) - (J.hm[si] + h_ji);
+  *out = measure_from_sums(J, J.act[pi], J.act[pj], s);
 }
 
 // Exact k of every candidate (kc[c] = sum_j min(0, R(c, j))^2, one wave per
@@ -1106,7 +1097,7 @@ __global__ __launch_bounds__(1024) void k_susp_schedule(const JobDev* __restrict
 // The bounded-grid pair kernels (suspect and extension rows) walk their items
 // in a loop.
 template <int W>
-__global__ __launch_bounds__(64 * W) void k_pair_susp(const JobDev* __restrict__ jobs,
+__global__ __launch_bounds__(64 * W, 3) void k_pair_susp(const JobDev* __restrict__ jobs,
                                                          int njobs,
                                                          const JobStep* __restrict__ js,
                                                          const int32_t* __restrict__ pre,
@@ -1115,7 +1106,7 @@ __global__ __launch_bounds__(64 * W) void k_pair_susp(const JobDev* __restrict__
 }
 
 template <int W>
-__global__ __launch_bounds__(64 * W) void k_pair_ext(const JobDev* __restrict__ jobs,
+__global__ __launch_bounds__(64 * W, 3) void k_pair_ext(const JobDev* __restrict__ jobs,
                                                         int njobs,
                                                         const JobStep* __restrict__ js,
                                                         const int32_t* __restrict__ pre,
@@ -1142,10 +1133,6 @@ __global__ __launch_bounds__(256) void k_ext_bound(const JobDev* __restrict__ jo
     int wl[kWit];
 #pragma unroll
     for (int q = 0; q < kWit; ++q) wl[q] = J.wit[(int64_t)l * kWit + q];
-    const double s1_bias =
-        (double)S.nsplit * 64.0 * (double)kS1Start + 0.5 * (double)J.n_pad;
-    const double inv_n = 1.0 / (double)J.n;
-    const double lim = 1.0 - kCollinear;
     double acc = 0.0;
     for (int e = lane; e < S.ne; e += 64) {
       const int j = J.ext[e];
@@ -1163,15 +1150,7 @@ __global__ __launch_bounds__(256) void k_ext_bound(const JobDev* __restrict__ jo
 #pragma unroll
         for (int c = 0; c < 4; ++c) sm[c] += src[c];
       }
-      const int sj = J.act[j];
-      double r = J.rho[(int64_t)sl * J.d + sj];
-      r = r > lim ? lim : (r < -lim ? -lim : r);
-      const double al = 1.0 / sqrt(1.0 - r * r);
-      const double h_lj =
-          entropy_from_moments(kLn2 * (sm[0] + s1_bias) * inv_n, al * sm[1] * inv_n);
-      const double h_jl =
-          entropy_from_moments(kLn2 * (sm[2] + s1_bias) * inv_n, al * sm[3] * inv_n);
-      const double R = (J.hm[sj] + h_lj) - (J.hm[sl] + h_jl);
+      const double R = measure_from_sums(J, sl, J.act[j], sm);
       if (R < 0.0) acc += R * R;
     }
 #pragma unroll
@@ -1280,19 +1259,7 @@ __global__ __launch_bounds__(256) void k_combine_susp(const JobDev* __restrict__
 #pragma unroll
       for (int c = 0; c < 4; ++c) sm[c] += src[c];
     }
-    const double s1_bias =
-        (double)S.nsplit_s * 64.0 * (double)kS1Start + 0.5 * (double)J.n_pad;
-    const double inv_n = 1.0 / (double)J.n;
-    const int si = J.act[pi], sj = J.act[pj];
-    double r = J.rho[(int64_t)si * J.d + sj];
-    const double lim = 1.0 - kCollinear;
-    r = r > lim ? lim : (r < -lim ? -lim : r);
-    const double al = 1.0 / sqrt(1.0 - r * r);
-    const double h_ij =
-        entropy_from_moments(kLn2 * (sm[0] + s1_bias) * inv_n, al * sm[1] * inv_n);
-    const double h_ji =
-        entropy_from_moments(kLn2 * (sm[2] + s1_bias) * inv_n, al * sm[3] * inv_n);
-    *out = (J.hm[sj] + h_ij) - (J.hm[si] + h_ji);
+    *out = measure_from_sums(J, J.act[pi], J.act[pj], sm);
   });
 }
 
