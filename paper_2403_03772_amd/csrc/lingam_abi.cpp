@@ -303,15 +303,17 @@ StepTotals step_totals(const std::vector<HostJob>& jobs, const Plan& P, int t, l
   StepTotals T;
   std::vector<lg::JobStep> js(P.njobs);
   const int K = P.lc.proposer ? P.lc.K : 0;
-  int64_t items = 0, items_c = 0;
+  int64_t items = 0, items_c = 0, pairs = 0;
   for (int k = 0; k < P.njobs; ++k) {
     js[k] = lg::job_step_base((int32_t)jobs[k].d, t, K, P.lc.min_m, jobs[k].record != nullptr);
     if (js[k].m >= 2 && !js[k].fp64) items += 2LL * js[k].ntiles;
     if (js[k].learned) items_c += 2LL * js[k].nct;
+    pairs += lg::pairs64(js[k]);
   }
   for (int k = 0; k < P.njobs; ++k) {
     lg::job_split(js[k], (int32_t)P.L[k].n_pad, items, P.cu, tu);
     lg::job_split_cand(js[k], (int32_t)P.L[k].n_pad, items_c, P.cu, tu, ties);
+    lg::job_split64(js[k], pairs, P.cu);
     for (int kind = 0; kind < lg::kNumKinds; ++kind)
       T.g[kind] += lg::kind_count(js[k], kind);
     const int m = js[k].m;
@@ -348,7 +350,7 @@ template <typename AfterGram>
 int enqueue_setup(const Plan& P, const std::vector<lg::JobDev>& dj, char* ws, hipStream_t st,
                   Prof* pf, AfterGram after_gram) {
   lg::JobDev* table = reinterpret_cast<lg::JobDev*>(ws + P.table_off);
-  const lg::SchedDev sc = lg::sched_at(ws + P.sched_off, P.njobs);
+  const lg::SchedDev sc = lg::sched_at(ws + P.sched_off, P.njobs, 0);
   for (int k = 0; k < P.njobs; k += lg::kJobsPerLaunch)
     LG_TRY(lg::launch_set_jobs(table, k, dj.data() + k,
                                std::min(lg::kJobsPerLaunch, P.njobs - k), st),
@@ -378,13 +380,14 @@ int enqueue_setup(const Plan& P, const std::vector<lg::JobDev>& dj, char* ws, hi
 int enqueue_steps(const Plan& P, const std::vector<HostJob>& jobs, char* ws, hipStream_t st,
                   lg::Tune tu, Prof* pf, bool ties) {
   lg::JobDev* table = reinterpret_cast<lg::JobDev*>(ws + P.table_off);
-  const lg::SchedDev sc = lg::sched_at(ws + P.sched_off, P.njobs);
   // bounded grids: one workgroup of w waves per resident slot
   auto resident = [&](int w) { return P.cu * (lg::kPairWavesPerCu / w); };
   for (int t = 0; t + 1 < P.max_d; ++t) {
     const StepTotals T = step_totals(jobs, P, t, tu, ties);
     if (T.g[lg::kKSel] == 0) break;  // every job finished
-    LG_TRY(lg::launch_step_schedule(table, P.njobs, t, P.cu, tu, sc, st), "step schedule");
+    const lg::SchedDev sc = lg::sched_at(ws + P.sched_off, P.njobs, t);
+    if (t == 0)  // later steps are planned by the selection before them
+      LG_TRY(lg::launch_step_schedule(table, P.njobs, t, P.cu, tu, sc, st), "step schedule");
     if (T.g[lg::kKFeat] > 0 || T.g[lg::kKMlp] > 0)
       LG_TRY(lg::launch_learned_front(table, P.njobs, t, sc, T.g, st), "features / scores");
     if (T.g[lg::kKPairC] > 0) {
@@ -448,7 +451,10 @@ int enqueue_steps(const Plan& P, const std::vector<HostJob>& jobs, char* ws, hip
     }
     LG_TRY(lg::launch_pair64(table, P.njobs, sc, T.g[lg::kKP64], st), "pair64");
     LG_TRY(lg::launch_rowk(table, P.njobs, sc, capped(T.g[lg::kKRowk], 8), st), "rowk");
-    LG_TRY(lg::launch_select(table, P.njobs, t, sc, T.g[lg::kKSel], st), "select");
+    const lg::NextStep next{lg::sched_at(ws + P.sched_off, P.njobs, t + 1), P.cu, tu};
+    LG_TRY(lg::launch_select(table, P.njobs, t, sc, T.g[lg::kKSel],
+                             t + 2 < P.max_d ? &next : nullptr, st),
+           "select");
     // near-ties of FP32-path steps (full or learned) decided in FP64
     if (ties && (T.g[lg::kKPair] > 0 || gated))
       LG_TRY(lg::launch_tie(table, P.njobs, sc, t, P.cu, st), "tie");
@@ -467,10 +473,11 @@ int enqueue_steps(const Plan& P, const std::vector<HostJob>& jobs, char* ws, hip
 // --------------------------------------------------------------------------
 
 // Default: 8 (tile, direction) items a CU, that is 4 workgroups (3 are resident),
-// each at least 4 sample blocks long.  k_pair at d = 331, n = 4801: 65 us a
-// launch, against 67 with 16 items; d = 97, n = 1999: 14.7 us against 15.3 with
-// 8 blocks and 18.9 with 16; d = 1024, n = 8192 and the uneven batch move by 1%.
-const lg::Tune kDefaultTune{8, 4, 4, 4};
+// each at least 8 sample blocks long.  k_pair at d = 331, n = 4801: 65 us a
+// launch, against 67 with 16 items; at d = 97, n = 1999: 15.3 us against 18.9
+// with 16 blocks and 14.7 with 4; d = 1024, n = 8192 and an uneven batch move by
+// 1%.  (Not 4: below 8 a small job's split in a batch parts from its own.)
+const lg::Tune kDefaultTune{8, 8, 4, 4};
 // split policies (target workgroups per CU, least sample iterations per split)
 const int32_t kSplitCandidates[][2] = {{8, 8}, {16, 8}, {16, 4}, {32, 4}, {8, 16}, {16, 16}};
 const int32_t kWaveChoices[] = {4, 2, 1};
@@ -544,7 +551,7 @@ void save_tune_file(const DevState& ds) {
 int autotune(const Plan& P, const std::vector<HostJob>& jobs, char* ws, hipStream_t st,
              bool ties, lg::Tune* out) {
   lg::JobDev* table = reinterpret_cast<lg::JobDev*>(ws + P.table_off);
-  const lg::SchedDev sc = lg::sched_at(ws + P.sched_off, P.njobs);
+  const lg::SchedDev sc = lg::sched_at(ws + P.sched_off, P.njobs, 0);
   std::vector<int> steps;
   const int dmax = P.max_d;
   for (double f : {0.0, 0.25, 0.5, 0.7, 0.85}) {

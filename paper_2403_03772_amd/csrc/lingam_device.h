@@ -108,14 +108,15 @@ __device__ inline double logcosh64(double u) {
 }
 __device__ inline double gauss64(double u) { return u * exp(-0.5 * u * u); }
 
-// R(pi, pj) of two active positions entirely in FP64 from the FP64 residuals
-// (the small-m path and the FP64 decision of near-ties): one wave, lanes over
-// samples, both residual directions; the result is valid in every lane.
+// The four sums of both residuals of two active positions entirely in FP64 from
+// the FP64 residuals (the small-m path and the FP64 decision of near-ties): one
+// wave, lanes over samples, of the 64-sample blocks first, first + stride, ...;
+// the sums over the lanes are valid in every lane.
 // log cosh u = |u| + log(1 + e^{-2|u|}) - ln 2; the logs of a lane's samples
 // are taken as the log of their product (each factor is in (1, 2], so 512 of
 // them stay below 2^512), one FP64 log per 512 samples.
-__device__ inline double pair_measure64(const JobDev& J, int pi, int pj, int lane) {
-  const int si = J.act[pi], sj = J.act[pj];
+__device__ inline void pair_sums64(const JobDev& J, int si, int sj, int lane, int first,
+                                   int stride, double (&v)[4]) {
   double r = J.rho[(int64_t)si * J.d + sj];
   const double lim = 1.0 - kCollinear;
   r = r > lim ? lim : (r < -lim ? -lim : r);
@@ -125,14 +126,14 @@ __device__ inline double pair_measure64(const JobDev& J, int pi, int pj, int lan
   double a1 = 0.0, a2 = 0.0, b1 = 0.0, b2 = 0.0;
   double pa = 1.0, pb = 1.0;
   int cnt = 0, tot = 0;
-  for (int s = lane; s < J.n; s += 64) {
+  for (int s = first * 64 + lane; s < J.n; s += stride * 64) {
     const double xi = zi[s], xj = zj[s];
     const double u = al * (xi - r * xj), w = al * (xj - r * xi);
     const double au = fabs(u), aw = fabs(w);
     a1 += au;
     b1 += aw;
-    pa *= 1.0 + exp_nonpos(-2.0 * au);
-    pb *= 1.0 + exp_nonpos(-2.0 * aw);
+    pa = fma(pa, exp_nonpos(-2.0 * au), pa);
+    pb = fma(pb, exp_nonpos(-2.0 * aw), pb);
     a2 += u * exp_nonpos(-0.5 * u * u);
     b2 += w * exp_nonpos(-0.5 * w * w);
     ++tot;
@@ -143,18 +144,21 @@ __device__ inline double pair_measure64(const JobDev& J, int pi, int pj, int lan
       cnt = 0;
     }
   }
-  a1 += log(pa) - (double)tot * kLn2;
-  b1 += log(pb) - (double)tot * kLn2;
+  v[0] = a1 + (log(pa) - (double)tot * kLn2);
+  v[1] = a2;
+  v[2] = b1 + (log(pb) - (double)tot * kLn2);
+  v[3] = b2;
 #pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) {
-    a1 += __shfl_xor(a1, off);
-    a2 += __shfl_xor(a2, off);
-    b1 += __shfl_xor(b1, off);
-    b2 += __shfl_xor(b2, off);
-  }
+  for (int k = 0; k < 4; ++k)
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) v[k] += __shfl_xor(v[k], off);
+}
+
+// R from the sums of pair_sums64 over all samples.
+__device__ inline double measure64(const JobDev& J, int si, int sj, const double (&v)[4]) {
   const double inv_n = 1.0 / (double)J.n;
-  const double h_ij = entropy_from_moments(a1 * inv_n, a2 * inv_n);
-  const double h_ji = entropy_from_moments(b1 * inv_n, b2 * inv_n);
+  const double h_ij = entropy_from_moments(v[0] * inv_n, v[1] * inv_n);
+  const double h_ji = entropy_from_moments(v[2] * inv_n, v[3] * inv_n);
   return (J.hm[sj] + h_ij) - (J.hm[si] + h_ji);
 }
 

@@ -258,6 +258,7 @@ struct JobStep {
   int32_t nct3;       // extension tiles ceil(nsus / 8) * ceil(ne / 8)
   int32_t q_all;      // workgroups per tile item of the all-pairs kernel (4 / w_all)
   int32_t q_rows;     // ... of the learned row kernels (4 / w_rows)
+  int32_t w64;        // waves per pair of the FP64 pair kernel (1, 2 or 4)
 };
 
 // Candidates of a learned step with m active variables and at most K: about
@@ -273,8 +274,8 @@ __host__ __device__ inline int32_t step_topk(int32_t m, int32_t K) {
 enum Kind : int {
   kKPair = 0,   // k_pair: ntiles * nsplit * q_all
   kKComb,       // k_combine: ceil(ntiles / 4)
-  kKP64,        // k_pair64: ceil(m (m - 1) / 2 / 4)
-  kKRowk,       // k_rowk: ceil(m / 4)
+  kKP64,        // k_pair64: ceil(w64 m (m - 1) / 2 / 4)
+  kKRowk,       // k_rowk: ceil(m / 4) on the FP32 path (k_select sums an FP64 step's rows)
   kKSel,        // k_select: 1
   kKRes,        // k_resid: m - 1 when m > 2
   kKFeat,       // k_features: ceil(m / 4)
@@ -405,6 +406,20 @@ __host__ __device__ inline void job_split(JobStep& s, int32_t n_pad, int64_t ite
   split_for(items_total, n_pad, num_cu, tu, s.nsplit, s.split_len);
 }
 
+// Waves per pair of one FP64-path job given the batch's number of such pairs:
+// with a wave a pair the last steps leave most of the device idle behind a few
+// long waves, so as many as keep the waves at 4 per SIMD, up to a workgroup.
+// (k_pair64 of 50 jobs of d = 10, n = 10000: 91 -> 50 us a launch; of d = 10, n =
+// 1000 alone: 11.8 -> 6.6; of d = 97, n = 1999: 20.5 -> 13.9.)
+__host__ __device__ inline void job_split64(JobStep& s, int64_t pairs_total, int32_t num_cu) {
+  s.w64 = 1;
+  while (s.w64 < 4 && pairs_total * s.w64 < 16LL * num_cu) s.w64 *= 2;
+}
+// Pairs of a step on the FP64 path (0 otherwise).
+__host__ __device__ inline int64_t pairs64(const JobStep& s) {
+  return s.m >= 2 && s.fp64 ? (int64_t)s.m * (s.m - 1) / 2 : 0;
+}
+
 // Extension columns of a learned step: the next ne_max ranks after the K
 // candidates, as many as there are.
 __host__ __device__ inline int32_t ext_count(int32_t m, int32_t K, int32_t ne_max) {
@@ -458,8 +473,8 @@ __host__ __device__ inline int32_t kind_count(const JobStep& s, int kind) {
   switch (kind) {
     case kKPair: return s.fp64 ? 0 : s.ntiles * s.nsplit * s.q_all;
     case kKComb: return s.fp64 ? 0 : cdiv(s.ntiles, 4);
-    case kKP64: return s.fp64 ? cdiv((int64_t)s.m * (s.m - 1) / 2, 4) : 0;
-    case kKRowk: return cdiv(s.m, 4);
+    case kKP64: return s.fp64 ? cdiv((int64_t)s.w64 * (s.m * (s.m - 1) / 2), 4) : 0;
+    case kKRowk: return s.fp64 ? 0 : cdiv(s.m, 4);
     case kKSel: return 1;
     case kKRes: return s.m > 2 ? s.m - 1 : 0;
     case kKFeat: return s.feat ? cdiv(s.m, 4) : 0;
@@ -498,16 +513,16 @@ __host__ __device__ inline int32_t setup_count(int32_t n_pad, int32_t d, int kin
 // share: with the region of exp(-z^2 / 2) (the last one).
 Layout make_layout(int64_t n, int64_t d, int num_cu, int K = 0, bool share = true);
 
-// Schedule buffer of a batch (device): per step, JobStep[njobs] and
-// kNumKinds prefix arrays of njobs + 1 entries; for the set-up,
-// kNumSetupKinds prefix arrays.
+// Schedule buffers of a batch (device): JobStep[njobs] and kNumKinds prefix
+// arrays of njobs + 1 entries, twice (a step's selection plans the next step
+// in the other buffer); for the set-up, kNumSetupKinds prefix arrays.
 struct SchedDev {
   JobStep* js;
   int32_t* pre;   // [kNumKinds][njobs + 1]
   int32_t* spre;  // [kNumSetupKinds][njobs + 1]
 };
 size_t sched_bytes(int njobs);
-SchedDev sched_at(char* base, int njobs);
+SchedDev sched_at(char* base, int njobs, int t);  // the buffer of step t
 
 // Kernel launchers (all asynchronous on `st`).  `grid` is the host's total of
 // the matching prefix array.
@@ -527,8 +542,14 @@ hipError_t launch_pair(const JobDev* jobs, int njobs, SchedDev sc, int grid, int
 hipError_t launch_combine(const JobDev* jobs, int njobs, SchedDev sc, int grid, hipStream_t st);
 hipError_t launch_pair64(const JobDev* jobs, int njobs, SchedDev sc, int grid, hipStream_t st);
 hipError_t launch_rowk(const JobDev* jobs, int njobs, SchedDev sc, int grid, hipStream_t st);
+// next: where to plan step t + 1 (NULL: no further step).
+struct NextStep {
+  SchedDev sc;
+  int num_cu;
+  Tune tu;
+};
 hipError_t launch_select(const JobDev* jobs, int njobs, int t, SchedDev sc, int grid,
-                         hipStream_t st);
+                         const NextStep* next, hipStream_t st);
 hipError_t launch_resid(const JobDev* jobs, int njobs, SchedDev sc, int grid, hipStream_t st);
 hipError_t launch_gather_status(const JobDev* jobs, int njobs, int32_t* dst, hipStream_t st);
 // FP64 decision of the steps whose choice was deferred as a near-tie (step t).

@@ -84,23 +84,26 @@ __device__ void step_schedule_wave(const JobDev* __restrict__ jobs, int njobs, i
                                    int32_t* __restrict__ pre) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nwaves = blockDim.x >> 6;
   JobStep s{};
-  long long mine = 0, mine_c = 0;
+  long long mine = 0, mine_c = 0, mine_p = 0;
   if (lane < njobs) {
     const JobDev& J = jobs[lane];
     s = job_step_base(J.d, t, J.prop ? J.K : 0, J.min_m, J.record != nullptr);
     if (s.m >= 2 && !s.fp64) mine = 2LL * s.ntiles;
     if (s.learned) mine_c = 2LL * s.nct;
+    mine_p = pairs64(s);
   }
-  long long items = mine, items_c = mine_c;
+  long long items = mine, items_c = mine_c, pairs = mine_p;
 #pragma unroll
   for (int off = 32; off >= 1; off >>= 1) {
     items += __shfl_xor(items, off);
     items_c += __shfl_xor(items_c, off);
+    pairs += __shfl_xor(pairs, off);
   }
   if (lane < njobs) {
     const JobDev& J = jobs[lane];
     job_split(s, J.n_pad, items, num_cu, tu);
     job_split_cand(s, J.n_pad, items_c, num_cu, tu, J.tie_on != 0);
+    job_split64(s, pairs, num_cu);
     if (wave == 0) js[lane] = s;
   }
   for (int kind = wave; kind < kNumKinds; kind += nwaves) {
@@ -113,35 +116,38 @@ __device__ void step_schedule_wave(const JobDev* __restrict__ jobs, int njobs, i
   }
 }
 
-__global__ __launch_bounds__(1024) void k_step_schedule(const JobDev* __restrict__ jobs,
-                                                        int njobs, int t, int num_cu, Tune tu,
-                                                        JobStep* __restrict__ js,
-                                                        int32_t* __restrict__ pre) {
+// The plan of step t, by one block of 1024 threads.
+__device__ void step_schedule(const JobDev* __restrict__ jobs, int njobs, int t, int num_cu,
+                              Tune tu, JobStep* __restrict__ js, int32_t* __restrict__ pre) {
   if (njobs <= 64) {  // uniform over the block
     step_schedule_wave(jobs, njobs, t, num_cu, tu, js, pre);
     return;
   }
-  __shared__ long long items, items_c;
+  __shared__ long long items, items_c, pairs;
   const int tid = threadIdx.x;
-  if (tid == 0) items = items_c = 0;
+  if (tid == 0) items = items_c = pairs = 0;
   __syncthreads();
-  long long mine = 0, mine_c = 0;
+  long long mine = 0, mine_c = 0, mine_p = 0;
   for (int j = tid; j < njobs; j += 1024) {
     const JobDev& J = jobs[j];
     const JobStep s = job_step_base(J.d, t, J.prop ? J.K : 0, J.min_m, J.record != nullptr);
     js[j] = s;
     if (s.m >= 2 && !s.fp64) mine += 2LL * s.ntiles;
     if (s.learned) mine_c += 2LL * s.nct;
+    mine_p += pairs64(s);
   }
   if (mine) atomicAdd(reinterpret_cast<unsigned long long*>(&items), (unsigned long long)mine);
   if (mine_c)
     atomicAdd(reinterpret_cast<unsigned long long*>(&items_c), (unsigned long long)mine_c);
+  if (mine_p)
+    atomicAdd(reinterpret_cast<unsigned long long*>(&pairs), (unsigned long long)mine_p);
   __syncthreads();
   for (int j = tid; j < njobs; j += 1024) {
     JobStep s = js[j];
     const JobDev& J = jobs[j];
     job_split(s, J.n_pad, items, num_cu, tu);
     job_split_cand(s, J.n_pad, items_c, num_cu, tu, J.tie_on != 0);
+    job_split64(s, pairs, num_cu);
     js[j] = s;
   }
   __syncthreads();
@@ -162,6 +168,13 @@ __global__ __launch_bounds__(1024) void k_step_schedule(const JobDev* __restrict
     }
     if (lane == 0) out[njobs] = run;
   }
+}
+
+__global__ __launch_bounds__(1024) void k_step_schedule(const JobDev* __restrict__ jobs,
+                                                        int njobs, int t, int num_cu, Tune tu,
+                                                        JobStep* __restrict__ js,
+                                                        int32_t* __restrict__ pre) {
+  step_schedule(jobs, njobs, t, num_cu, tu, js, pre);
 }
 
 // After the learned decisions: gate off the full step of every job whose
@@ -456,42 +469,52 @@ __global__ __launch_bounds__(256) void k_combine(const JobDev* __restrict__ jobs
 }
 
 // The same measure entirely in FP64 from the FP64 residuals, for steps with few
-// active variables.  One wave per unordered pair (both directions), lanes over
-// samples, FP64 wave reduction; writes R(i,j) and R(j,i) = -R(i,j).
+// active variables.  w64 waves per unordered pair (both directions), 4 / w64
+// pairs a workgroup, lanes over samples, the waves' sums added in order; writes
+// R(i,j) and R(j,i) = -R(i,j).  About 90 FP64 instructions a sample and pair, 72
+// of them the four exponentials: bound by their issue once the device is full.
 __global__ __launch_bounds__(256) void k_pair64(const JobDev* __restrict__ jobs, int njobs,
                                                 const JobStep* __restrict__ js,
                                                 const int32_t* __restrict__ pre) {
+  __shared__ double part[4][4];
   for_blocks(pre, njobs, [&](int jb, int lb) {
   const JobDev& J = jobs[jb];
-  const int m = js[jb].m;
-  const int lane = threadIdx.x & 63;
-  const int pair = lb * 4 + (threadIdx.x >> 6);
+  const int m = js[jb].m, W = js[jb].w64;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int pair = lb * (4 / W) + wave / W, sub = wave % W;
   const int npairs = m * (m - 1) / 2;
-  if (pair >= npairs) return;
-  int pi = 0, rem = pair;
-  while (rem >= m - 1 - pi) {
-    rem -= m - 1 - pi;
-    ++pi;
+  double v[4] = {0.0, 0.0, 0.0, 0.0};
+  int pi = 0, pj = 0;
+  if (pair < npairs) {
+    int rem = pair;
+    while (rem >= m - 1 - pi) {
+      rem -= m - 1 - pi;
+      ++pi;
+    }
+    pj = pi + 1 + rem;
+    pair_sums64(J, J.act[pi], J.act[pj], lane, sub, W, v);
   }
-  const int pj = pi + 1 + rem;
-  const double Rv = pair_measure64(J, pi, pj, lane);
-  if (lane == 0) {
+  if (W > 1) {  // workgroup-uniform
+    if (lane == 0)
+#pragma unroll
+      for (int k = 0; k < 4; ++k) part[wave][k] = v[k];
+    __syncthreads();
+    if (sub == 0)
+      for (int w = 1; w < W; ++w)
+#pragma unroll
+        for (int k = 0; k < 4; ++k) v[k] += part[wave + w][k];
+    __syncthreads();  // part is rewritten for the next item
+  }
+  if (pair < npairs && sub == 0 && lane == 0) {
+    const double Rv = measure64(J, J.act[pi], J.act[pj], v);
     J.rmat[(int64_t)pi * J.d + pj] = Rv;
     J.rmat[(int64_t)pj * J.d + pi] = -Rv;
   }
   });
 }
 
-// k_p = sum_{q != p} min(0, R(p, q))^2, one wave per row; mvec[p] = -k_p.
-__global__ __launch_bounds__(256) void k_rowk(const JobDev* __restrict__ jobs, int njobs,
-                                              const JobStep* __restrict__ js,
-                                              const int32_t* __restrict__ pre) {
-  for_blocks(pre, njobs, [&](int jb, int lb) {
-  const JobDev& J = jobs[jb];
-  const int m = js[jb].m;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int p = lb * 4 + wave;
-  if (p >= m) return;
+// k_p = sum_{q != p} min(0, R(p, q))^2 by one wave; mvec[p] = -k_p.
+__device__ inline void row_k(const JobDev& J, int m, int p, int lane) {
   const double* row = J.rmat + (int64_t)p * J.d;
   double k = 0.0;
   for (int q = lane; q < m; q += 64) {
@@ -503,22 +526,40 @@ __global__ __launch_bounds__(256) void k_rowk(const JobDev* __restrict__ jobs, i
 #pragma unroll
   for (int off = 32; off >= 1; off >>= 1) k += __shfl_xor(k, off);
   if (lane == 0) J.mvec[p] = -k;
+}
+
+__global__ __launch_bounds__(256) void k_rowk(const JobDev* __restrict__ jobs, int njobs,
+                                              const JobStep* __restrict__ js,
+                                              const int32_t* __restrict__ pre) {
+  for_blocks(pre, njobs, [&](int jb, int lb) {
+    const int m = js[jb].m, p = lb * 4 + (threadIdx.x >> 6);
+    if (p < m) row_k(jobs[jb], m, p, threadIdx.x & 63);
   });
 }
 
 // Argmax with tie-break on the original id, teacher forcing, per-step outputs,
-// swap-remove of the chosen variable.  One workgroup of 1024 threads per job.
+// swap-remove of the chosen variable.  One workgroup of 1024 threads per job;
+// an FP64 step's rows (at most 64) are summed here too, 16 waves four rows each.
+// A further workgroup (has_next) plans step t + 1, which depends on no result:
+// as kernels of their own these two took 3 and 4 us of a step, and their launch.
 __global__ __launch_bounds__(1024) void k_select(const JobDev* __restrict__ jobs, int njobs,
                                                  const JobStep* __restrict__ js,
-                                                 const int32_t* __restrict__ pre, int t) {
+                                                 const int32_t* __restrict__ pre, int t,
+                                                 int has_next, NextStep next) {
   __shared__ Best sh[1024];
   __shared__ int forced_pos, ntie;
+  if (has_next && blockIdx.x == gridDim.x - 1) {
+    step_schedule(jobs, njobs, t + 1, next.num_cu, next.tu, next.sc.js, next.sc.pre);
+    return;
+  }
   for_blocks(pre, njobs, [&](int jb, int) {
   const JobDev& J = jobs[jb];
   const int m = js[jb].m, d = J.d;
   int32_t* act = J.act;
   const int tid = threadIdx.x;
   if (tid == 0) forced_pos = -1;
+  if (js[jb].fp64)
+    for (int p = tid >> 6; p < m; p += 16) row_k(J, m, p, tid & 63);
   __syncthreads();
   Best b{-INFINITY, 0x7fffffff, -1, -INFINITY};
   const bool force = t < J.forced_len;
@@ -682,7 +723,13 @@ __global__ __launch_bounds__(256) void k_tie(const JobDev* __restrict__ jobs, in
       const int r = (int)(q / m), pj = (int)(q - (int64_t)r * m);
       const int pi = J.tie[r];
       double* out = J.tie_r + (int64_t)r * J.d + pj;
-      const double Rv = pi == pj ? 0.0 : pair_measure64(J, pi, pj, lane);
+      double Rv = 0.0;
+      if (pi != pj) {
+        double v[4];
+        const int si = J.act[pi], sj = J.act[pj];
+        pair_sums64(J, si, sj, lane, 0, 1, v);
+        Rv = measure64(J, si, sj, v);
+      }
       if (lane == 0) *out = Rv;
       __threadfence();
       int done = 0;
@@ -1149,19 +1196,20 @@ Layout make_layout(int64_t n, int64_t d, int num_cu, int K, bool share) {
   return L;
 }
 
+static size_t sched_js_bytes(int njobs) { return align256(2 * sizeof(JobStep) * (size_t)njobs); }
+
 size_t sched_bytes(int njobs) {
-  return align256(sizeof(JobStep) * (size_t)njobs) +
-         align256(sizeof(int32_t) * (size_t)kNumKinds * (size_t)(njobs + 1)) +
-         align256(sizeof(int32_t) * (size_t)kNumSetupKinds * (size_t)(njobs + 1));
+  return sched_js_bytes(njobs) +
+         align256(sizeof(int32_t) * (size_t)(2 * kNumKinds + kNumSetupKinds) * (size_t)(njobs + 1));
 }
 
-SchedDev sched_at(char* base, int njobs) {
+SchedDev sched_at(char* base, int njobs, int t) {
   SchedDev s;
-  s.js = reinterpret_cast<JobStep*>(base);
-  char* p = base + align256(sizeof(JobStep) * (size_t)njobs);
-  s.pre = reinterpret_cast<int32_t*>(p);
-  p += align256(sizeof(int32_t) * (size_t)kNumKinds * (size_t)(njobs + 1));
-  s.spre = reinterpret_cast<int32_t*>(p);
+  const size_t kinds = (size_t)kNumKinds * (size_t)(njobs + 1);
+  int32_t* p = reinterpret_cast<int32_t*>(base + sched_js_bytes(njobs));
+  s.js = reinterpret_cast<JobStep*>(base) + (size_t)(t & 1) * (size_t)njobs;
+  s.pre = p + (size_t)(t & 1) * kinds;
+  s.spre = p + 2 * kinds;
   return s;
 }
 
@@ -1279,10 +1327,11 @@ hipError_t launch_rowk(const JobDev* jobs, int njobs, SchedDev sc, int grid, hip
 }
 
 hipError_t launch_select(const JobDev* jobs, int njobs, int t, SchedDev sc, int grid,
-                         hipStream_t st) {
+                         const NextStep* next, hipStream_t st) {
   if (grid <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_select, dim3((unsigned)grid), dim3(1024), 0, st, jobs, njobs,
-                     (const JobStep*)sc.js, pre_of(sc, njobs, kKSel), t);
+  hipLaunchKernelGGL(k_select, dim3((unsigned)(grid + (next ? 1 : 0))), dim3(1024), 0, st, jobs,
+                     njobs, (const JobStep*)sc.js, pre_of(sc, njobs, kKSel), t, next ? 1 : 0,
+                     next ? *next : NextStep{});
   return hipGetLastError();
 }
 
