@@ -366,7 +366,9 @@ int enqueue_setup(const Plan& P, const std::vector<lg::JobDev>& dj, char* ws, hi
   const int cols = setup_total(P, lg::kSCols);
   LG_TRY(lg::launch_moments(table, P.njobs, sc, cols, st), "moments");
   if (pf && pf->tm.on) pf->g0 = pf->tm.take(st);
-  LG_TRY(lg::launch_gram(table, P.njobs, sc, setup_total(P, lg::kSGram), st), "gram");
+  LG_TRY(lg::launch_gram(table, P.njobs, sc, setup_total(P, lg::kSGram),
+                         setup_total(P, lg::kSGramSum), st),
+         "gram");
   if (pf && pf->tm.on) pf->g1 = pf->tm.take(st);
   if (pf)
     for (int k = 0; k < P.njobs; ++k)
@@ -1144,7 +1146,8 @@ int lingam_adjacency(const float* X, int64_t n_rows, int64_t ldx, const int32_t*
                 (long long)d, (long long)ldx, (long long)n_rows);
   if (n > kMaxN || d > kMaxD || n_rows > kMaxN)
     return fail(LINGAM_E_UNSUPPORTED, "size beyond supported range");
-  const lg::AdjLayout A = lg::make_adj_layout(n, d);
+  lg::AdjLayout A = lg::make_adj_layout(n, d);
+  if (ws_bytes < A.total) A = lg::make_adj_layout(n, d, false);
   if (!ws || ws_bytes < A.total)
     return fail(LINGAM_E_WORKSPACE, "workspace of %zu bytes needed (got %zu)", A.total,
                 ws ? ws_bytes : (size_t)0);

@@ -304,11 +304,30 @@ __host__ __device__ inline bool gated_kind(int kind) {
 enum SetupKind : int {
   kSIngest = 0,  // (n_pad / 64) * ceil((d + 1) / 64)
   kSCols,        // d (moments, standardize)
-  kSGram,        // nb (nb + 1) / 2, nb = ceil(d / 32)
+  kSGram,        // tiles * splits, tiles = nb (nb + 1) / 2, nb = ceil(d / 32)
+  kSGramSum,     // tiles when there are splits to add
   kNumSetupKinds
 };
 
 __host__ __device__ inline int32_t cdiv(int64_t a, int64_t b) { return (int32_t)((a + b - 1) / b); }
+
+// Sample splits of a Gram matrix of d rows over n samples in 32 x 32 tiles
+// (kTileElems doubles each): a tile's chunks are a serial chain (about 1 us per
+// 32 samples), so about 4096 workgroups, none shorter than 256 samples, and no
+// more partial tiles than `room` holds (1: none are needed).
+constexpr int kTileElems = 1024;
+__host__ __device__ inline int32_t gram_splits(int64_t n, int64_t d, int64_t room) {
+  const int64_t nb = (d + 31) / 32, tiles = nb * (nb + 1) / 2;
+  int64_t s = (n + 255) / 256;
+  if (s > 4096 / tiles) s = 4096 / tiles;
+  if (s > room / tiles) s = room / tiles;
+  return s > 1 ? (int32_t)s : 1;
+}
+// ... of a job's set-up: its partial tiles lie in the FP32 copy's rows, which
+// are written after the Gram matrix.
+__host__ __device__ inline int32_t setup_gram_splits(int32_t n_pad, int32_t d) {
+  return gram_splits(n_pad, d, (int64_t)d * n_pad / (2 * kTileElems));
+}
 
 // Tile order of the all-pairs kernel: the upper triangle of nb x nb blocks
 // (bi <= bj) is walked in super-blocks of kSuperTile x kSuperTile blocks --
@@ -501,9 +520,10 @@ __host__ __device__ inline int32_t setup_count(int32_t n_pad, int32_t d, int kin
   switch (kind) {
     case kSIngest: return (n_pad / 64) * cdiv(d + 1, 64);
     case kSCols: return d;
-    case kSGram: {
-      const int32_t nb = cdiv(d, 32);
-      return nb * (nb + 1) / 2;
+    case kSGram:
+    case kSGramSum: {
+      const int32_t nb = cdiv(d, 32), splits = setup_gram_splits(n_pad, d);
+      return nb * (nb + 1) / 2 * (kind == kSGram ? splits : splits > 1 ? 1 : 0);
     }
     default: return 0;
   }
@@ -530,7 +550,9 @@ hipError_t launch_setup_schedule(const JobDev* jobs, int njobs, SchedDev sc, hip
 hipError_t launch_init(const JobDev* jobs, int njobs, hipStream_t st);
 hipError_t launch_ingest(const JobDev* jobs, int njobs, SchedDev sc, int grid, hipStream_t st);
 hipError_t launch_moments(const JobDev* jobs, int njobs, SchedDev sc, int grid, hipStream_t st);
-hipError_t launch_gram(const JobDev* jobs, int njobs, SchedDev sc, int grid, hipStream_t st);
+// grid, grid_sum: totals of kSGram and kSGramSum.
+hipError_t launch_gram(const JobDev* jobs, int njobs, SchedDev sc, int grid, int grid_sum,
+                       hipStream_t st);
 hipError_t launch_standardize(const JobDev* jobs, int njobs, SchedDev sc, int grid,
                               hipStream_t st);
 hipError_t launch_step_schedule(const JobDev* jobs, int njobs, int t, int num_cu, Tune tu,
@@ -644,10 +666,13 @@ struct AdjLayout {
   size_t xd;     // double [(d + 1) * ldx] the data, variable-major
   size_t s;      // double [d * d] permuted covariance, then its Cholesky factor
   size_t y;      // double [d * d] columns of the inverse factor
+  size_t part;   // double [nsplit * tiles * kTileElems] partial covariance tiles
+  int32_t nsplit;  // sample splits of the covariance (1: no such region)
   size_t total;
 };
 
-AdjLayout make_adj_layout(int64_t n, int64_t d);
+// split: with the region of partial tiles (the last one), if there are any.
+AdjLayout make_adj_layout(int64_t n, int64_t d, bool split = true);
 // Zero the status; status kInvalid unless `order` is a permutation and every
 // rows[s] (s < n, if rows is given) lies in [0, n_rows).
 hipError_t launch_adj_check(const AdjLayout& A, char* ws, const int32_t* order,
@@ -670,29 +695,30 @@ hipError_t launch_boot_finalize(const int32_t* order_count, const int32_t* edge_
 
 // Dense FP64 pieces shared by the adjacency and VarLiNGAM.
 // In-place Cholesky of the leading p x p block of A (lower triangle holds L;
-// the upper triangle and columns >= p are left alone).  Status kDegenerate
-// for a pivot <= 1e-13 max |A_jj| or a non-finite one.
-hipError_t launch_cholesky(double* A, int64_t lda, int p, double* tol, Ctrl* ctrl,
-                           hipStream_t st);
-// X (ld ldx) = L^-1 for the lower-triangular p x p L (the upper triangle of
-// X's diagonal blocks is written as zero; blocks above them are not touched).
-hipError_t launch_tri_inverse(const double* L, int64_t ldl, int p, double* X, int64_t ldx,
-                              hipStream_t st);
+// the upper triangle and columns >= p are left alone), and X (p x p, ld ldx) =
+// L^-1 below and on the diagonal (its blocks above the diagonal are scratch).
+// Status kDegenerate for a pivot <= 1e-13 max |A_jj| or a non-finite one.
+hipError_t launch_cholesky_inverse(double* A, int64_t lda, int p, double* X, int64_t ldx,
+                                   double* tol, Ctrl* ctrl, hipStream_t st);
+// X alone, for a given unit lower-triangular L.
+hipError_t launch_unit_inverse(const double* L, int64_t ldl, int p, double* X, int64_t ldx,
+                               hipStream_t st);
 // C = op(A) B, A lower-triangular M x M (op: A, or A^T when trans), B M x N;
 // C must not alias B.
 hipError_t launch_trmm(int M, int N, const double* A, int64_t lda, bool trans, const double* B,
                        int64_t ldb, double* C, int64_t ldc, hipStream_t st);
 // B (p x p, ld p) = least-squares coefficients of every variable on its order
-// predecessors from the Cholesky factor L of the order-permuted covariance;
+// predecessors from the order-permuted covariance A (ld p; factored in place);
 // B[order[i]][order[k]] for k < i, zero elsewhere.  Y: p x p scratch (L^-1).
-hipError_t launch_tri_adjacency(const double* L, int64_t ldl, int p, const int32_t* order,
-                                double* B, double* Y, hipStream_t st);
+hipError_t launch_tri_adjacency(double* A, int p, const int32_t* order, double* B, double* Y,
+                                double* tol, Ctrl* ctrl, hipStream_t st);
 // S[a][b] = sig[o_a] sig[o_b] rho[o_a][o_b].
 hipError_t launch_perm_scale(const double* rho, int64_t ldr, const double* sig,
                              const int32_t* order, int d, double* S, hipStream_t st);
-// mu = row means of Xd[0..d-1][0..n-1]; S = centred Gram permuted into `order`.
+// mu = row means of Xd[0..d-1][0..n-1]; S = centred Gram permuted into `order`;
+// nsplit > 1: part holds that many partial tile sets.
 hipError_t launch_cov_perm(const double* Xd, int64_t ldx, int n, int d, const int32_t* order,
-                           double* mu, double* S, hipStream_t st);
+                           double* mu, double* S, int nsplit, double* part, hipStream_t st);
 // theta[t] = (I - B0) M[t], t < lags (d x d each, row-major).
 hipError_t launch_lagged_effects(const double* M, const double* B0, int d, int lags,
                                  double* theta, hipStream_t st);

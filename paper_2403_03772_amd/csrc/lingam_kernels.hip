@@ -320,68 +320,66 @@ __global__ __launch_bounds__(256) void k_moments(const JobDev* __restrict__ jobs
   }
 }
 
-typedef double double4_t __attribute__((ext_vector_type(4)));
-
 // Correlation matrix rho = C / (n sigma_i sigma_j), C = sum_s (x_i - mu_i)(x_j - mu_j),
-// on FP64 MFMA (v_mfma_f64_16x16x4f64).  One workgroup per 32 x 32 tile of the
-// upper triangle, four waves each owning a 16 x 16 block; samples staged
-// through LDS in chunks of 32, centred on the way in.
-__global__ __launch_bounds__(256) void k_gram(const JobDev* __restrict__ jobs, int njobs,
-                                              const int32_t* __restrict__ spre) {
-  constexpr int KC = 32;
-  __shared__ double As[KC][33];
-  __shared__ double Bs[KC][33];
-  int jb, tile;
-  if (!locate(spre + (int64_t)kSGram * (njobs + 1), njobs, blockIdx.x, jb, tile)) return;
-  const JobDev& J = jobs[jb];
-  const int d = J.d, n = J.n, n_pad = J.n_pad;
-  const int64_t ldz = J.ldz, ldr = d;
-  const int nb = cdiv(d, 32);
-  int bi, bj;
-  decode_tile(tile, nb, bi, bj);
-  const int I0 = bi * 32, J0 = bj * 32;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wi = wave >> 1, wj = wave & 1;
-  // loader mapping: 32 variables x 32 samples, 4 consecutive samples per thread
-  const int lv = tid >> 3, ls = (tid & 7) * 4;
-  const int va = I0 + lv, vb = J0 + lv;
-  const double* za = J.zd + (int64_t)(va < d ? va : d) * ldz;  // row d is all zeros
-  const double* zb = J.zd + (int64_t)(vb < d ? vb : d) * ldz;
-  const double mua = va < d ? J.mu[va] : 0.0, mub = vb < d ? J.mu[vb] : 0.0;
-  double4_t acc = {0.0, 0.0, 0.0, 0.0};
-  for (int s0 = 0; s0 < n_pad; s0 += KC) {
-    __syncthreads();
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const int s = s0 + ls + u;
-      const bool live = s < n;
-      As[ls + u][lv] = (live && va < d) ? za[s] - mua : 0.0;
-      Bs[ls + u][lv] = (live && vb < d) ? zb[s] - mub : 0.0;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int kk = 0; kk < KC / 4; ++kk) {
-      const double a = As[kk * 4 + (lane >> 4)][wi * 16 + (lane & 15)];
-      const double b = Bs[kk * 4 + (lane >> 4)][wj * 16 + (lane & 15)];
-      acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, acc, 0, 0, 0);
-    }
-  }
-  // output layout of the 16x16x4 f64 MFMA: register r of lane l holds
-  // D[4 r + l / 16][l % 16]
+// on FP64 MFMA.  One workgroup per 32 x 32 tile of the upper triangle and range
+// of samples, centred on the way into LDS.  With several ranges the tiles' sums
+// go to the FP32 copy's rows (not yet written) and k_gram_sum adds them.
+// d = 10, n = 1000: 43 -> 12 + 4 us; 50 jobs of d = 10, n = 10000: 398 -> 36 + 17.
+__device__ void gram_store(const JobDev& J, int bi, int bj, const double4_t& acc) {
+  const int d = J.d;
   bool degenerate = false;
 #pragma unroll
   for (int r = 0; r < 4; ++r) {
-    const int i = I0 + wi * 16 + 4 * r + (lane >> 4);
-    const int jj = J0 + wj * 16 + (lane & 15);
+    const int i = bi * 32 + tile_row(r), jj = bj * 32 + tile_col();
     if (i < d && jj < d && (bi != bj || i <= jj)) {
-      double v = acc[r] / ((double)n * J.sig[i] * J.sig[jj]);
+      double v = acc[r] / ((double)J.n * J.sig[i] * J.sig[jj]);
       if (i == jj) v = 1.0;
       else if (!(fabs(v) < 1.0 - kCollinear)) degenerate = true;
-      J.rho[(int64_t)i * ldr + jj] = v;
-      J.rho[(int64_t)jj * ldr + i] = v;
+      J.rho[(int64_t)i * d + jj] = v;
+      J.rho[(int64_t)jj * d + i] = v;
     }
   }
   if (degenerate) set_status(J.ctrl, kStDegenerate);
+}
+
+__global__ __launch_bounds__(256) void k_gram(const JobDev* __restrict__ jobs, int njobs,
+                                              const int32_t* __restrict__ spre) {
+  __shared__ Tile64 T;
+  int jb, item;
+  if (!locate(spre, njobs, blockIdx.x, jb, item)) return;
+  const JobDev& J = jobs[jb];
+  const int d = J.d, n = J.n;
+  const int nb = cdiv(d, 32), ntiles = nb * (nb + 1) / 2;
+  const int nsplit = setup_gram_splits(J.n_pad, d);
+  const int split = item / ntiles, tile = item - split * ntiles;
+  int bi, bj;
+  decode_tile(tile, nb, bi, bj);
+  const int lv = threadIdx.x >> 3, ls = (threadIdx.x & 7) * 4;
+  const int va = bi * 32 + lv, vb = bj * 32 + lv;
+  const double* za = J.zd + (int64_t)(va < d ? va : d) * J.ldz;  // row d is all zeros
+  const double* zb = J.zd + (int64_t)(vb < d ? vb : d) * J.ldz;
+  const double mua = va < d ? J.mu[va] : 0.0, mub = vb < d ? J.mu[vb] : 0.0;
+  const int chunks = J.n_pad / 32, per = cdiv(chunks, nsplit);
+  const double4_t acc = mfma_chunks<true>(
+      T, split * per, min(split * per + per, chunks), double4_t{0.0, 0.0, 0.0, 0.0},
+      [&](int c, double (&v)[4]) { centred4(za, c * 32 + ls, n, va < d, mua, v); },
+      [&](int c, double (&v)[4]) { centred4(zb, c * 32 + ls, n, vb < d, mub, v); });
+  if (nsplit == 1) gram_store(J, bi, bj, acc);
+  else
+    tile_put(reinterpret_cast<double*>(J.z) + ((int64_t)split * ntiles + tile) * kTileElems, acc);
+}
+
+__global__ __launch_bounds__(256) void k_gram_sum(const JobDev* __restrict__ jobs, int njobs,
+                                                  const int32_t* __restrict__ spre) {
+  int jb, tile;
+  if (!locate(spre, njobs, blockIdx.x, jb, tile)) return;
+  const JobDev& J = jobs[jb];
+  const int nb = cdiv(J.d, 32);
+  int bi, bj;
+  decode_tile(tile, nb, bi, bj);
+  gram_store(J, bi, bj,
+             tile_sum(reinterpret_cast<const double*>(J.z), setup_gram_splits(J.n_pad, J.d),
+                      nb * (nb + 1) / 2, tile));
 }
 
 // z = (x - mu) / sigma in place in FP64, its FP32 copy, and the marginal
@@ -878,44 +876,33 @@ __global__ void k_fill(double* p, int n, double v) {
 }
 
 // W = D^T D for the lagged design D (N rows, q = 1 + lags d + d columns), FP64
-// MFMA, upper 32 x 32 tiles mirrored.  Same tiling as k_gram, uncentred.
+// MFMA, upper 32 x 32 tiles mirrored.  Same tiling as k_gram, uncentred, whole
+// columns.
 __global__ __launch_bounds__(256) void k_gram_design(const double* __restrict__ Xd, int64_t ldx,
                                                      const double* __restrict__ ones, int d,
                                                      int lags, int N, int q, int nb,
                                                      double* __restrict__ W, int64_t ldw) {
-  constexpr int KC = 32;
-  __shared__ double As[KC][33];
-  __shared__ double Bs[KC][33];
+  __shared__ Tile64 T;
   int bi, bj;
   decode_tile(blockIdx.x, nb, bi, bj);
-  const int I0 = bi * 32, J0 = bj * 32;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wi = wave >> 1, wj = wave & 1;
-  const int lv = tid >> 3, ls = (tid & 7) * 4;
-  const int va = I0 + lv, vb = J0 + lv;
+  const int lv = threadIdx.x >> 3, ls = (threadIdx.x & 7) * 4;
+  const int va = bi * 32 + lv, vb = bj * 32 + lv;
   const double* za = design_col(va < q ? va : 0, Xd, ldx, d, lags, ones);
   const double* zb = design_col(vb < q ? vb : 0, Xd, ldx, d, lags, ones);
-  double4_t acc = {0.0, 0.0, 0.0, 0.0};
-  for (int s0 = 0; s0 < N; s0 += KC) {
-    __syncthreads();
+  auto load = [&](const double* z, bool on, int c, double (&v)[4]) {
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
-      const int s = s0 + ls + u;
-      As[ls + u][lv] = (s < N && va < q) ? za[s] : 0.0;
-      Bs[ls + u][lv] = (s < N && vb < q) ? zb[s] : 0.0;
+      const int s = c * 32 + ls + u;
+      v[u] = on && s < N ? z[s] : 0.0;
     }
-    __syncthreads();
-#pragma unroll
-    for (int kk = 0; kk < KC / 4; ++kk) {
-      const double a = As[kk * 4 + (lane >> 4)][wi * 16 + (lane & 15)];
-      const double b = Bs[kk * 4 + (lane >> 4)][wj * 16 + (lane & 15)];
-      acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, acc, 0, 0, 0);
-    }
-  }
+  };
+  const double4_t acc = mfma_chunks<true>(
+      T, 0, (N + 31) / 32, double4_t{0.0, 0.0, 0.0, 0.0},
+      [&](int c, double (&v)[4]) { load(za, va < q, c, v); },
+      [&](int c, double (&v)[4]) { load(zb, vb < q, c, v); });
 #pragma unroll
   for (int r = 0; r < 4; ++r) {
-    const int i = I0 + wi * 16 + 4 * r + (lane >> 4);
-    const int j = J0 + wj * 16 + (lane & 15);
+    const int i = bi * 32 + tile_row(r), j = bj * 32 + tile_col();
     if (i < q && j < q && (bi != bj || i <= j)) {
       W[(int64_t)i * ldw + j] = acc[r];
       W[(int64_t)j * ldw + i] = acc[r];
@@ -1252,9 +1239,14 @@ hipError_t launch_moments(const JobDev* jobs, int njobs, SchedDev sc, int grid, 
   return hipGetLastError();
 }
 
-hipError_t launch_gram(const JobDev* jobs, int njobs, SchedDev sc, int grid, hipStream_t st) {
+hipError_t launch_gram(const JobDev* jobs, int njobs, SchedDev sc, int grid, int grid_sum,
+                       hipStream_t st) {
   if (grid <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_gram, dim3((unsigned)grid), dim3(256), 0, st, jobs, njobs, sc.spre);
+  hipLaunchKernelGGL(k_gram, dim3((unsigned)grid), dim3(256), 0, st, jobs, njobs,
+                     spre_of(sc, njobs, kSGram));
+  if (grid_sum > 0)
+    hipLaunchKernelGGL(k_gram_sum, dim3((unsigned)grid_sum), dim3(256), 0, st, jobs, njobs,
+                       spre_of(sc, njobs, kSGramSum));
   return hipGetLastError();
 }
 
@@ -1428,11 +1420,10 @@ hipError_t launch_var_fit(const VarLayout& V, char* ws, char* job, float* G, con
   const int nb = (int)((V.q + 31) / 32);
   hipLaunchKernelGGL(k_gram_design, dim3((unsigned)(nb * (nb + 1) / 2)), dim3(256), 0, st, Xd,
                      V.ldx, ones, (int)V.d, V.lags, (int)V.N, (int)V.q, nb, W, V.q);
-  LG_HIP(launch_cholesky(W, V.q, (int)V.p, at<double>(ws, V.tol), ctrl, st));
   // coefficients (L L^T)^-1 C = X^T (X C), X = L^-1, C = W[0:p, p:q]
   double* Xi = at<double>(ws, V.linv);
   double* T = at<double>(ws, V.tmp);
-  LG_HIP(launch_tri_inverse(W, V.q, (int)V.p, Xi, V.p, st));
+  LG_HIP(launch_cholesky_inverse(W, V.q, (int)V.p, Xi, V.p, at<double>(ws, V.tol), ctrl, st));
   LG_HIP(launch_trmm((int)V.p, (int)V.d, Xi, V.p, false, W + V.p, V.q, T, V.d, st));
   LG_HIP(launch_trmm((int)V.p, (int)V.d, Xi, V.p, true, T, V.d, W + V.p, V.q, st));
   dim3 g2((unsigned)V.N, (unsigned)((V.d + 63) / 64));
@@ -1457,15 +1448,15 @@ hipError_t launch_b0(const VarLayout& V, char* ws, char* job, const int32_t* ord
   double* S = at<double>(ws, V.scr);
   LG_HIP(launch_perm_scale(at<double>(ws, V.rho0), V.d, at<double>(job, V.ord.sig), order,
                            (int)V.d, S, st));
-  LG_HIP(launch_cholesky(S, V.d, (int)V.d, at<double>(ws, V.tol), at<Ctrl>(job, V.ord.ctrl), st));
-  return launch_tri_adjacency(S, V.d, (int)V.d, order, B0, at<double>(ws, V.y), st);
+  return launch_tri_adjacency(S, (int)V.d, order, B0, at<double>(ws, V.y), at<double>(ws, V.tol),
+                              at<Ctrl>(job, V.ord.ctrl), st);
 }
 
 // ---------------------------------------------------------------------------
 // least-squares adjacency from a causal order
 // ---------------------------------------------------------------------------
 
-AdjLayout make_adj_layout(int64_t n, int64_t d) {
+AdjLayout make_adj_layout(int64_t n, int64_t d, bool split) {
   AdjLayout A{};
   A.n = n;
   A.d = d;
@@ -1483,6 +1474,10 @@ AdjLayout make_adj_layout(int64_t n, int64_t d) {
   A.xd = take(sizeof(double) * (size_t)(d + 1) * (size_t)A.ldx);
   A.s = take(sizeof(double) * (size_t)d * (size_t)d);
   A.y = take(sizeof(double) * (size_t)d * (size_t)d);
+  A.nsplit = split ? gram_splits(n, d, INT32_MAX) : 1;
+  const size_t nb = (size_t)(d + 31) / 32;
+  if (A.nsplit > 1)
+    A.part = take(sizeof(double) * kTileElems * (nb * (nb + 1) / 2) * (size_t)A.nsplit);
   A.total = off;
   return A;
 }
@@ -1508,9 +1503,10 @@ hipError_t launch_adjacency(const AdjLayout& A, char* ws, const float* X, int64_
   dim3 g1((unsigned)(A.ldx / 64), (unsigned)((A.d + 1 + 63) / 64));
   hipLaunchKernelGGL(k_transpose_f64, g1, dim3(256), 0, st, X, ldx, rows, (int)A.n, (int)A.d,
                      (int)A.ldx, Xd, A.ldx, ctrl);
-  LG_HIP(launch_cov_perm(Xd, A.ldx, (int)A.n, (int)A.d, order, at<double>(ws, A.mu), S, st));
-  LG_HIP(launch_cholesky(S, A.d, (int)A.d, at<double>(ws, A.tol), ctrl, st));
-  return launch_tri_adjacency(S, A.d, (int)A.d, order, B, at<double>(ws, A.y), st);
+  LG_HIP(launch_cov_perm(Xd, A.ldx, (int)A.n, (int)A.d, order, at<double>(ws, A.mu), S, A.nsplit,
+                         at<double>(ws, A.part), st));
+  return launch_tri_adjacency(S, (int)A.d, order, B, at<double>(ws, A.y), at<double>(ws, A.tol),
+                              ctrl, st);
 }
 
 hipError_t launch_boot_accumulate(const int32_t* order, const double* B, int d, double thr,

@@ -1,25 +1,16 @@
 // gfx950 dense FP64 linear algebra of the library.
 //
-//   blocked Cholesky     A = L L^T by 32-wide panels: the diagonal block is
-//                        factored in LDS by one workgroup, the panel below it
-//                        is solved row-parallel against that block (rows
-//                        staged in LDS), and the trailing lower triangle takes
-//                        the rank-32 update on FP64 MFMA (16 x 16 x 4), one
-//                        32 x 32 tile per workgroup.
-//   adjacency from L     least squares of every variable on the variables
-//                        that precede it in a causal order (the second phase
-//                        of DirectLiNGAM, Section 1; B0 of VarLiNGAM, Section
-//                        3.3).  With the covariance permuted into the order,
-//                        S = L L^T, the coefficients of variable o_i on
-//                        o_0 .. o_{i-1} solve S_i b = s_i with S_i = L_i L_i^T
-//                        (leading i x i blocks) and s_i = L_i l_i (l_i = row i
-//                        of L left of the diagonal), so b = L_i^-T l_i.
-//                        Stacked over i this is B = I - diag(L) L^-1.
-//   triangular inverse   X = L^-1 by 32 x 32 blocks: the diagonal blocks are
-//                        inverted in LDS (all at once), then block row I is
-//                        X_IJ = -X_II sum_{J <= K < I} L_IK X_KJ for all J < I
-//                        in one launch (both products on FP64 MFMA), so the
-//                        dependency chain is p / 32 launches long.
+//   blocked Cholesky     A = L L^T by 32-wide panels, a launch each: the
+//                        diagonal block is factored and inverted in one
+//                        wave's registers by the workgroup that updated it;
+//                        every workgroup multiplies the panel's rows that it
+//                        needs by that inverse and gives its 32 x 32 tile of
+//                        the trailing lower triangle the rank-32 update, on
+//                        FP64 MFMA (16 x 16 x 4).
+//   triangular inverse   X = L^-1: the 32 x 32 diagonal blocks, then pairs of
+//                        neighbours merged level by level (X21 = -X22 L21
+//                        X11, both products on FP64 MFMA), 2 log2(p / 32)
+//                        launches.
 //   triangular products  op(X) B for the normal equations of the VAR fit:
 //                        (L L^T)^-1 C = X^T (X C).
 //   covariance           centred Gram matrix of variable rows, permuted into
@@ -32,213 +23,296 @@
 namespace lg {
 namespace {
 
-typedef double double4_t __attribute__((ext_vector_type(4)));
-
 constexpr int kNb = 32;  // Cholesky panel width and update tile
 
-// tol = 1e-13 * max_j |A_jj|: pivots at or below it are rounding noise.
-__global__ __launch_bounds__(256) void k_chol_tol(const double* __restrict__ A, int64_t lda,
-                                                  int p, double* __restrict__ tol) {
+typedef double Block[kNb][kNb + 1];
+
+__device__ inline double lane_of(double v, int l) {
+  const int lo = __builtin_amdgcn_readlane(__double2loint(v), l);
+  const int hi = __builtin_amdgcn_readlane(__double2hiint(v), l);
+  return __hiloint2double(hi, lo);
+}
+
+// v[k] -= m col_k for k > j, col_k being lane k's value of col: all lanes are
+// read first, so that no product waits for its own, and fenced, or the compiler
+// would put every update of a column off to its turn, a chain as long as the
+// column's number.
+__device__ __forceinline__ void eliminate(double (&v)[32], double m, double col, int j) {
+  double s[32];
+#pragma unroll
+  for (int k = j + 1; k < 32; ++k) s[k] = lane_of(col, k);
+  __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+  for (int k = j + 1; k < 32; ++k) v[k] = fma(-m, s[k], v[k]);
+  __builtin_amdgcn_sched_barrier(0);
+}
+
+// Wave 0 of a workgroup factors the 32 x 32 block in T (lower triangle; rows past
+// kb hold the identity) in registers: lane i < 32 holds row i, and column j's
+// entries reach the others through readlane.  Lanes 32 + i start from column i
+// of the identity: what eliminates column j from the rows, v_k -= v_j L_kj with
+// v_j divided by the pivot's root, is the substitution's step for that column,
+// so they end with the inverse at no cost.  T holds L, D its inverse on return.
+// Bound by the chain of 32 pivots, each a reciprocal root (Newton's iteration
+// from v_rsq_f64) and its column's products: 9 us, where elimination in LDS with
+// a barrier a column took 17 and the inverse 18 more.  The same with the column
+// broadcast out of LDS; loops over the columns in place of code for each: 15 us.
+__device__ __forceinline__ void factor_block(Block& T, Block& D, int kb, double tl, Ctrl* ctrl) {
+  if (threadIdx.x >= 64) return;
+  const int i = threadIdx.x & 31;
+  const bool rows = threadIdx.x < 32;
+  double v[32];
+#pragma unroll
+  for (int j = 0; j < 32; ++j) v[j] = rows ? T[i][j] : (i == j ? 1.0 : 0.0);
+  bool bad = false;
+#pragma unroll
+  for (int j = 0; j < 32; ++j) {
+    // without a branch: the compiler would move the columns' updates past it
+    double piv = lane_of(v[j], j);
+    const bool poor = (j < kb) & (!(piv > tl) | !isfinite(piv));
+    bad |= poor;
+    piv = poor ? 1.0 : piv;
+    double y = __builtin_amdgcn_rsq(piv);
+    y = fma(0.5 * y, fma(-piv * y, y, 1.0), y);
+    y = fma(0.5 * y, fma(-piv * y, y, 1.0), y);
+    double root = piv * y;
+    root = fma(fma(-root, root, piv), 0.5 * y, root);
+    v[j] = rows && i == j ? root : v[j] * y;
+    eliminate(v, v[j], v[j], j);
+  }
+  if (bad && threadIdx.x == 0) set_status(ctrl, kStDegenerate);
+#pragma unroll
+  for (int j = 0; j < 32; ++j)
+    if (rows) T[i][j] = v[j];
+    else D[j][i] = v[j];
+}
+
+// Factored block and its inverse from LDS to A and X (in full: zeros above the
+// diagonal; past kb the block is cut).  Called by every thread of 256.
+__device__ __forceinline__ void store_block(Block& T, Block& D, int k0, int kb, double* A,
+                                            int64_t lda, double* X, int64_t ldx) {
+  for (int e = threadIdx.x; e < kNb * kNb; e += 256) {
+    const int i = e >> 5, j = e & 31;
+    if (i >= kb || j >= kb) continue;
+    if (j <= i) A[(int64_t)(k0 + i) * lda + k0 + j] = T[i][j];
+    X[(int64_t)(k0 + i) * ldx + k0 + j] = j <= i ? D[i][j] : 0.0;
+  }
+}
+
+// Where step k0 finds the columns of its panel, rows below the diagonal block,
+// before they are multiplied by its inverse: transposed (row c, column i for
+// A[i][k0 + c]), in block rows 0 and 1 of X by turns, right of the diagonal.
+__device__ inline double* raw_panel(double* X, int64_t ldx, int k0) {
+  return X + (int64_t)(k0 & kNb) * ldx;
+}
+
+// tol = 1e-13 * max_j |A_jj| (pivots at or below it are rounding noise) and the
+// first diagonal block (workgroup 0); the first panel's columns, 32 rows each
+// (the others).
+__global__ __launch_bounds__(256) void k_chol_first(double* __restrict__ A, int64_t lda, int p,
+                                                    double* __restrict__ X, int64_t ldx,
+                                                    double* __restrict__ tol, Ctrl* ctrl) {
+  __shared__ Block T, D;
   __shared__ double sh[256];
+  const int tid = threadIdx.x, kb = p < kNb ? p : kNb, I0 = blockIdx.x * kNb;
+  for (int e = tid; e < kNb * kNb; e += 256) {
+    const int i = e >> 5, j = e & 31;
+    const bool in = I0 + i < p && (I0 > 0 || j <= i);
+    T[i][j] = in ? A[(int64_t)(I0 + i) * lda + j] : (i == j ? 1.0 : 0.0);
+  }
+  if (I0 > 0) {
+    __syncthreads();
+    for (int e = tid; e < kNb * kNb; e += 256) {
+      const int j = e >> 5, i = e & 31;
+      if (I0 + i < p) raw_panel(X, ldx, 0)[(int64_t)j * ldx + I0 + i] = T[i][j];
+    }
+    return;
+  }
   double mx = 0.0;
-  for (int j = threadIdx.x; j < p; j += 256) mx = fmax(mx, fabs(A[(int64_t)j * lda + j]));
-  sh[threadIdx.x] = mx;
+  for (int j = tid; j < p; j += 256) mx = fmax(mx, fabs(A[(int64_t)j * lda + j]));
+  sh[tid] = mx;
   __syncthreads();
   for (int off = 128; off > 0; off >>= 1) {
-    if (threadIdx.x < off) sh[threadIdx.x] = fmax(sh[threadIdx.x], sh[threadIdx.x + off]);
+    if (tid < off) sh[tid] = fmax(sh[tid], sh[tid + off]);
     __syncthreads();
   }
-  if (threadIdx.x == 0) tol[0] = sh[0] * 1e-13;
+  const double tl = sh[0] * 1e-13;
+  if (tid == 0) tol[0] = tl;
+  factor_block(T, D, kb, tl, ctrl);
+  __syncthreads();
+  store_block(T, D, 0, kb, A, lda, X, ldx);
 }
 
-// Factor the kb x kb diagonal block at (k0, k0) (lower triangle) in LDS.
-__global__ __launch_bounds__(256) void k_chol_diag(double* __restrict__ A, int64_t lda, int k0,
-                                                   int kb, const double* __restrict__ tol,
+// Step k0 right of its diagonal block (full), r0 = k0 + 32, one 32 x 32 tile
+// (I >= J) of the trailing lower triangle per workgroup, on MFMA: the panel's
+// rows P_I = A_I L_kk^-T and P_J from the block's inverse (in X), then A_IJ -= P_I
+// P_J^T.  Every workgroup forms the rows it needs, which costs it 16 MFMAs a
+// wave and saves the launch that would form them first; they are read from
+// raw_panel, so those of the first tile column store P_I in place and their tile,
+// the next panel, to the next raw_panel; the first workgroup's is the next
+// diagonal block, which it factors and inverts.  A launch of 13.8 us a step at d = 1024, where a
+// panel solve (32), an update (6) and a factorization with a barrier a column
+// (22) were three.
+__global__ __launch_bounds__(256) void k_chol_step(double* __restrict__ A, int64_t lda, int p,
+                                                   int k0, int nt, double* __restrict__ X,
+                                                   int64_t ldx, const double* __restrict__ tol,
                                                    Ctrl* ctrl) {
-  __shared__ double T[kNb][kNb + 1];
-  const int tid = threadIdx.x;
-  for (int e = tid; e < kNb * kNb; e += 256) {
-    const int i = e / kNb, j = e - i * kNb;
-    T[i][j] = (i < kb && j <= i) ? A[(int64_t)(k0 + i) * lda + k0 + j] : 0.0;
-  }
-  __syncthreads();
-  const double tl = tol[0];
-  for (int j = 0; j < kb; ++j) {
-    if (tid == 0) {
-      double a = T[j][j];
-      if (!(a > tl) || !isfinite(a)) {
-        set_status(ctrl, kStDegenerate);
-        a = 1.0;
-      }
-      T[j][j] = sqrt(a);
-    }
-    __syncthreads();
-    if (tid > j && tid < kb) T[tid][j] /= T[j][j];
-    __syncthreads();
-    const int w = kb - j - 1;
-    for (int e = tid; e < w * w; e += 256) {
-      const int ii = e / w, kk = e - ii * w;
-      if (kk <= ii) T[j + 1 + ii][j + 1 + kk] -= T[j + 1 + ii][j] * T[j + 1 + kk][j];
-    }
-    __syncthreads();
-  }
-  for (int e = tid; e < kb * kb; e += 256) {
-    const int i = e / kb, j = e - i * kb;
-    if (j <= i) A[(int64_t)(k0 + i) * lda + k0 + j] = T[i][j];
-  }
-}
-
-// Rows i >= r0 = k0 + kb of the panel: A[i, k0:k0+kb] <- A[i, k0:k0+kb] L_kk^-T
-// (forward substitution along the row; one thread per row, the rows staged
-// in LDS, 64 rows per workgroup).
-constexpr int kPanelRows = 64;
-
-__global__ __launch_bounds__(kPanelRows) void k_chol_panel(double* __restrict__ A, int64_t lda,
-                                                           int p, int k0, int kb) {
-  __shared__ double Lk[kNb][kNb + 1];
-  __shared__ double X[kPanelRows][kNb + 1];
-  const int tid = threadIdx.x;
-  for (int e = tid; e < kNb * kNb; e += kPanelRows) {
-    const int i = e / kNb, j = e - i * kNb;
-    Lk[i][j] = (i < kb && j <= i) ? A[(int64_t)(k0 + i) * lda + k0 + j] : 0.0;
-  }
-  const int rbase = k0 + kb + blockIdx.x * kPanelRows;
-  // coalesced staging: consecutive threads take consecutive columns of a row
-  for (int e = tid; e < kPanelRows * kNb; e += kPanelRows) {
-    const int r = e / kNb, c = e - r * kNb;
-    X[r][c] = (rbase + r < p && c < kb) ? A[(int64_t)(rbase + r) * lda + k0 + c] : 0.0;
-  }
-  __syncthreads();
-  for (int c = 0; c < kb; ++c) {
-    double s = X[tid][c];
-    for (int t = 0; t < c; ++t) s -= X[tid][t] * Lk[c][t];
-    X[tid][c] = s / Lk[c][c];
-  }
-  __syncthreads();
-  for (int e = tid; e < kPanelRows * kNb; e += kPanelRows) {
-    const int r = e / kNb, c = e - r * kNb;
-    if (rbase + r < p && c < kb) A[(int64_t)(rbase + r) * lda + k0 + c] = X[r][c];
-  }
-}
-
-// Trailing update of the lower triangle right of the panel:
-// A[i][j] -= sum_c A[i][k0 + c] A[j][k0 + c] for r0 <= j <= i < p, r0 = k0 + kb.
-// One 32 x 32 tile (I >= J) per workgroup, four waves of 16 x 16 on MFMA.
-__global__ __launch_bounds__(256) void k_chol_update(double* __restrict__ A, int64_t lda, int p,
-                                                     int k0, int kb, int nt) {
-  __shared__ double As[kNb][kNb + 1];
-  __shared__ double Bs[kNb][kNb + 1];
+  __shared__ __align__(16) double PI[32][32], PJ[32][32], Li[32][32];
+  __shared__ Block F, D;
   int bj, bi;
   decode_tile(blockIdx.x, nt, bj, bi);  // bj <= bi: tile (I, J) = (bi, bj) is lower
-  const int r0 = k0 + kb;
+  const int lv = threadIdx.x >> 3, ls = (threadIdx.x & 7) * 4;
+  const int r0 = k0 + kNb;
   const int I0 = r0 + bi * kNb, J0 = r0 + bj * kNb;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wi = wave >> 1, wj = wave & 1;
-  const int lv = tid >> 3, ls = (tid & 7) * 4;
+  const double* raw = raw_panel(X, ldx, k0) + (int64_t)lv * ldx;
 #pragma unroll
   for (int u = 0; u < 4; ++u) {
     const int c = ls + u;
-    As[c][lv] = (c < kb && I0 + lv < p) ? A[(int64_t)(I0 + lv) * lda + k0 + c] : 0.0;
-    Bs[c][lv] = (c < kb && J0 + lv < p) ? A[(int64_t)(J0 + lv) * lda + k0 + c] : 0.0;
+    PI[lv][c ^ swz(lv)] = I0 + c < p ? raw[I0 + c] : 0.0;
+    PJ[lv][c ^ swz(lv)] = J0 + c < p ? raw[J0 + c] : 0.0;
+    Li[c][lv ^ swz(c)] = X[(int64_t)(k0 + lv) * ldx + k0 + c];
   }
-  __syncthreads();
-  double4_t acc = {0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-  for (int kk = 0; kk < kNb / 4; ++kk) {
-    const double a = As[kk * 4 + (lane >> 4)][wi * 16 + (lane & 15)];
-    const double b = Bs[kk * 4 + (lane >> 4)][wj * 16 + (lane & 15)];
-    acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, acc, 0, 0, 0);
-  }
+  double4_t t;  // the tile (the diagonal block's past p: identity)
 #pragma unroll
   for (int r = 0; r < 4; ++r) {
-    const int i = I0 + wi * 16 + 4 * r + (lane >> 4);
-    const int j = J0 + wj * 16 + (lane & 15);
-    if (i < p && j <= i) A[(int64_t)i * lda + j] -= acc[r];
+    const int i = I0 + tile_row(r), j = J0 + tile_col();
+    t[r] = i < p && j <= i ? A[(int64_t)i * lda + j] : (i == j ? 1.0 : 0.0);
   }
+  __syncthreads();
+  const double4_t zero = {0.0, 0.0, 0.0, 0.0};
+  const double4_t pi = mfma_block(PI, Li, zero);
+  const double4_t pj = bi == bj ? pi : mfma_block(PJ, Li, zero);
+  __syncthreads();
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    const int i = tile_row(r), c = tile_col();
+    PI[c][i ^ swz(c)] = pi[r];
+    PJ[c][i ^ swz(c)] = pj[r];
+    if (bj == 0 && I0 + i < p) A[(int64_t)(I0 + i) * lda + k0 + c] = pi[r];
+  }
+  __syncthreads();
+  t -= mfma_block(PI, PJ, zero);
+  if (bj > 0) {
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int i = I0 + tile_row(r), j = J0 + tile_col();
+      if (i < p && j <= i) A[(int64_t)i * lda + j] = t[r];
+    }
+    return;
+  }
+#pragma unroll
+  for (int r = 0; r < 4; ++r) F[tile_row(r)][tile_col()] = t[r];
+  __syncthreads();
+  if (bi > 0) {
+    double* next = raw_panel(X, ldx, r0);
+    for (int e = threadIdx.x; e < kNb * kNb; e += 256) {
+      const int j = e >> 5, i = e & 31;
+      if (I0 + i < p) next[(int64_t)j * ldx + I0 + i] = F[i][j];
+    }
+    return;
+  }
+  const int kb = min(kNb, p - r0);
+  factor_block(F, D, kb, tol[0], ctrl);
+  __syncthreads();
+  store_block(F, D, r0, kb, A, lda, X, ldx);
 }
 
-// Diagonal 32 x 32 blocks of X = L^-1: X_II = L_II^-1, written in full (zeros
-// above the diagonal; past p the block is cut).  One workgroup per block;
-// thread j < 32 runs the forward substitution of column j in LDS.
+// Diagonal blocks of X = L^-1 for a unit lower-triangular L, one wave each: lane
+// i holds row i of the block and column i of the inverse (the substitution of
+// factor_block).
 __global__ __launch_bounds__(64) void k_trinv_diag(const double* __restrict__ L, int64_t ldl,
                                                    int p, double* __restrict__ X, int64_t ldx) {
-  __shared__ double Ls[kNb][kNb + 1];
-  __shared__ double Ds[kNb][kNb + 1];
+  __shared__ Block T;
   const int I0 = blockIdx.x * kNb, kb = min(kNb, p - I0);
-  const int tid = threadIdx.x;
+  const int tid = threadIdx.x, i = tid & 31;
   for (int e = tid; e < kNb * kNb; e += 64) {
-    const int i = e / kNb, j = e - i * kNb;
-    Ls[i][j] = (i < kb && j <= i) ? L[(int64_t)(I0 + i) * ldl + I0 + j] : 0.0;
+    const int r = e >> 5, j = e & 31;
+    T[r][j] = (r < kb && j < r) ? L[(int64_t)(I0 + r) * ldl + I0 + j] : 0.0;
   }
   __syncthreads();
-  if (tid < kb) {
-    const int j = tid;
-    for (int i = 0; i < kNb; ++i) Ds[i][j] = 0.0;
-    Ds[j][j] = 1.0 / Ls[j][j];
-    for (int i = j + 1; i < kb; ++i) {
-      double s = 0.0;
-      for (int t = j; t < i; ++t) s += Ls[i][t] * Ds[t][j];
-      Ds[i][j] = -s / Ls[i][i];
-    }
+  double a[32], x[32];
+#pragma unroll
+  for (int j = 0; j < 32; ++j) {
+    a[j] = T[i][j];
+    x[j] = i == j ? 1.0 : 0.0;
   }
+#pragma unroll
+  for (int j = 0; j < 32; ++j) eliminate(x, x[j], a[j], j);
   __syncthreads();
-  for (int e = tid; e < kb * kb; e += 64) {
-    const int i = e / kb, j = e - i * kb;
-    X[(int64_t)(I0 + i) * ldx + I0 + j] = Ds[i][j];
+#pragma unroll
+  for (int r = 0; r < 32; ++r) T[r][i] = x[r];  // both halves of the wave alike
+  __syncthreads();
+  for (int e = tid; e < kNb * kNb; e += 64) {
+    const int r = e >> 5, j = e & 31;
+    if (r < kb && j < kb) X[(int64_t)(I0 + r) * ldx + I0 + j] = T[r][j];
   }
 }
 
-// Block row I of X = L^-1 left of the diagonal: X_IJ = -X_II sum_{J <= K < I}
-// L_IK X_KJ for every J < I (one workgroup each), both products on FP64 MFMA.
-// Blocks K < I and J < I are full (only the last block row can be cut by p).
-__global__ __launch_bounds__(256) void k_trinv_row(const double* __restrict__ L, int64_t ldl,
-                                                   int p, int I, double* __restrict__ X,
-                                                   int64_t ldx) {
-  __shared__ double As[kNb][kNb + 1];
-  __shared__ double Bs[kNb][kNb + 1];
-  const int J = blockIdx.x;
-  const int I0 = I * kNb, J0 = J * kNb;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wi = wave >> 1, wj = wave & 1;
-  const int lv = tid >> 3, ls = (tid & 7) * 4;
-  const bool row_ok = I0 + lv < p;
-  double4_t acc = {0.0, 0.0, 0.0, 0.0};
-  for (int K = J; K < I; ++K) {
-    const int K0 = K * kNb;
-    __syncthreads();
+// One level of X = L^-1: with the diagonal blocks of b rows inverted, those of
+// 2 b: [L11 0; L21 L22]^-1 = [X11 0; X21 X22], X21 = -X22 (L21 X11).  A launch
+// forms every pair's product L21 X11 (kept transposed in the block of X above
+// the diagonal), the next one X21.  log2(p / 32) levels; block row by block
+// row it was a chain of p / 32 launches, each as long as its row: d = 1024, 31
+// launches of 15.7 us to 10 of 8.  Tiles of all pairs: (b / 32)^2 a pair, the
+// last pair's second half cut at p.
+__global__ __launch_bounds__(256) void k_trinv_prod(const double* __restrict__ L, int64_t ldl,
+                                                    int p, int b, double* __restrict__ X,
+                                                    int64_t ldx) {
+  __shared__ Tile64 T;
+  const int nt = b / kNb, pair = blockIdx.x / (nt * nt), e = blockIdx.x - pair * nt * nt;
+  const int I = e / nt, J = e - I * nt;
+  const int o1 = pair * 2 * b, o2 = o1 + b;  // first rows of the two halves
+  if (o2 + I * kNb >= p) return;
+  const int lv = threadIdx.x >> 3, ls = (threadIdx.x & 7) * 4;
+  const int row = o2 + I * kNb + lv;
+  const double4_t acc = mfma_chunks<false>(
+      T, J, nt, double4_t{0.0, 0.0, 0.0, 0.0},
+      [&](int c, double (&v)[4]) {
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      As[ls + u][lv] = row_ok ? L[(int64_t)(I0 + lv) * ldl + K0 + ls + u] : 0.0;  // L_IK[lv][k]
-      Bs[lv][ls + u] = X[(int64_t)(K0 + lv) * ldx + J0 + ls + u];                // X_KJ[k][j]
-    }
-    __syncthreads();
+        for (int u = 0; u < 4; ++u)
+          v[u] = row < p ? L[(int64_t)row * ldl + o1 + c * kNb + ls + u] : 0.0;
+      },
+      [&](int c, double (&v)[4]) {
 #pragma unroll
-    for (int kk = 0; kk < kNb / 4; ++kk) {
-      const double a = As[kk * 4 + (lane >> 4)][wi * 16 + (lane & 15)];
-      const double b = Bs[kk * 4 + (lane >> 4)][wj * 16 + (lane & 15)];
-      acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, acc, 0, 0, 0);
-    }
-  }
-  __syncthreads();
-  // T = acc becomes the right operand; X_II the left one
-#pragma unroll
-  for (int r = 0; r < 4; ++r) Bs[wi * 16 + 4 * r + (lane >> 4)][wj * 16 + (lane & 15)] = acc[r];
-#pragma unroll
-  for (int u = 0; u < 4; ++u)
-    As[ls + u][lv] = (row_ok && I0 + ls + u < p) ? X[(int64_t)(I0 + lv) * ldx + I0 + ls + u] : 0.0;
-  __syncthreads();
-  double4_t out = {0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-  for (int kk = 0; kk < kNb / 4; ++kk) {
-    const double a = As[kk * 4 + (lane >> 4)][wi * 16 + (lane & 15)];
-    const double b = Bs[kk * 4 + (lane >> 4)][wj * 16 + (lane & 15)];
-    out = __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, out, 0, 0, 0);
-  }
+        for (int u = 0; u < 4; ++u)
+          v[u] = X[(int64_t)(o1 + c * kNb + lv) * ldx + o1 + J * kNb + ls + u];
+      });
 #pragma unroll
   for (int r = 0; r < 4; ++r) {
-    const int i = I0 + wi * 16 + 4 * r + (lane >> 4);
-    const int j = J0 + wj * 16 + (lane & 15);
-    if (i < p) X[(int64_t)i * ldx + j] = -out[r];
+    const int i = o2 + I * kNb + tile_row(r);
+    if (i < p) X[(int64_t)(o1 + J * kNb + tile_col()) * ldx + i] = acc[r];
+  }
+}
+
+__global__ __launch_bounds__(256) void k_trinv_merge(int p, int b, double* __restrict__ X,
+                                                     int64_t ldx) {
+  __shared__ Tile64 T;
+  const int nt = b / kNb, pair = blockIdx.x / (nt * nt), e = blockIdx.x - pair * nt * nt;
+  const int I = e / nt, J = e - I * nt;
+  const int o1 = pair * 2 * b, o2 = o1 + b;
+  if (o2 + I * kNb >= p) return;
+  const int lv = threadIdx.x >> 3, ls = (threadIdx.x & 7) * 4;
+  const int row = o2 + I * kNb + lv;
+  const double4_t acc = mfma_chunks<true>(
+      T, 0, I + 1, double4_t{0.0, 0.0, 0.0, 0.0},
+      [&](int c, double (&v)[4]) {  // X22 (the diagonal block's upper half is zero)
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          const int k = o2 + c * kNb + ls + u;
+          v[u] = row < p && k < p ? X[(int64_t)row * ldx + k] : 0.0;
+        }
+      },
+      [&](int c, double (&v)[4]) {  // the product, transposed above the diagonal
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          const int k = o2 + c * kNb + ls + u;
+          v[u] = k < p ? X[(int64_t)(o1 + J * kNb + lv) * ldx + k] : 0.0;
+        }
+      });
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    const int i = o2 + I * kNb + tile_row(r);
+    if (i < p) X[(int64_t)i * ldx + o1 + J * kNb + tile_col()] = -acc[r];
   }
 }
 
@@ -262,41 +336,30 @@ __global__ void k_adj_scatter(const double* __restrict__ L, int64_t ldl,
 __global__ __launch_bounds__(256) void k_trmm(int M, int N, const double* __restrict__ A,
                                               int64_t lda, int trans, const double* __restrict__ B,
                                               int64_t ldb, double* __restrict__ C, int64_t ldc) {
-  __shared__ double As[kNb][kNb + 1];
-  __shared__ double Bs[kNb][kNb + 1];
+  __shared__ Tile64 T;
   const int I0 = blockIdx.y * kNb, J0 = blockIdx.x * kNb;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wi = wave >> 1, wj = wave & 1;
-  const int lv = tid >> 3, ls = (tid & 7) * 4;
-  const int kbeg = trans ? I0 : 0;
-  const int kend = trans ? M : min(M, I0 + kNb);
-  double4_t acc = {0.0, 0.0, 0.0, 0.0};
-  for (int k0 = kbeg; k0 < kend; k0 += kNb) {
-    __syncthreads();
+  const int lv = threadIdx.x >> 3, ls = (threadIdx.x & 7) * 4;
+  const int cbeg = trans ? blockIdx.y : 0;
+  const int cend = trans ? (M + kNb - 1) / kNb : blockIdx.y + 1;
+  const double4_t acc = mfma_chunks<false>(
+      T, cbeg, cend, double4_t{0.0, 0.0, 0.0, 0.0},
+      [&](int c, double (&v)[4]) {  // op(A)[I0 + lv][k]
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      if (!trans) {  // op(A)[i][k] = A[i][k]: lv = i, ls + u = k
-        const int i = I0 + lv, k = k0 + ls + u;
-        As[ls + u][lv] = (i < M && k < M) ? A[(int64_t)i * lda + k] : 0.0;
-      } else {       // op(A)[i][k] = A[k][i]: lv = k, ls + u = i
-        const int k = k0 + lv, i = I0 + ls + u;
-        As[lv][ls + u] = (i < M && k < M) ? A[(int64_t)k * lda + i] : 0.0;
-      }
-      const int k = k0 + lv, j = J0 + ls + u;
-      Bs[lv][ls + u] = (k < M && j < N) ? B[(int64_t)k * ldb + j] : 0.0;
-    }
-    __syncthreads();
+        for (int u = 0; u < 4; ++u) {
+          const int i = I0 + lv, k = c * kNb + ls + u;
+          v[u] = i < M && k < M ? (trans ? A[(int64_t)k * lda + i] : A[(int64_t)i * lda + k]) : 0.0;
+        }
+      },
+      [&](int c, double (&v)[4]) {
 #pragma unroll
-    for (int kk = 0; kk < kNb / 4; ++kk) {
-      const double a = As[kk * 4 + (lane >> 4)][wi * 16 + (lane & 15)];
-      const double b = Bs[kk * 4 + (lane >> 4)][wj * 16 + (lane & 15)];
-      acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, acc, 0, 0, 0);
-    }
-  }
+        for (int u = 0; u < 4; ++u) {
+          const int k = c * kNb + lv, j = J0 + ls + u;
+          v[u] = k < M && j < N ? B[(int64_t)k * ldb + j] : 0.0;
+        }
+      });
 #pragma unroll
   for (int r = 0; r < 4; ++r) {
-    const int i = I0 + wi * 16 + 4 * r + (lane >> 4);
-    const int j = J0 + wj * 16 + (lane & 15);
+    const int i = I0 + tile_row(r), j = J0 + tile_col();
     if (i < M && j < N) C[(int64_t)i * ldc + j] = acc[r];
   }
 }
@@ -327,52 +390,48 @@ __global__ __launch_bounds__(256) void k_row_mean(const double* __restrict__ Xd,
 }
 
 // S[a][b] = sum_s (x_{o_a}(s) - mu_{o_a}) (x_{o_b}(s) - mu_{o_b}) on FP64 MFMA,
-// upper 32 x 32 tiles computed and mirrored.
-__global__ __launch_bounds__(256) void k_cov_perm(const double* __restrict__ Xd, int64_t ldx,
-                                                  int n, int d,
-                                                  const int32_t* __restrict__ order,
-                                                  const double* __restrict__ mu, int nb,
-                                                  double* __restrict__ S) {
-  constexpr int KC = 32;
-  __shared__ double As[KC][33];
-  __shared__ double Bs[KC][33];
-  int bi, bj;
-  decode_tile(blockIdx.x, nb, bi, bj);
-  const int I0 = bi * 32, J0 = bj * 32;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wi = wave >> 1, wj = wave & 1;
-  const int lv = tid >> 3, ls = (tid & 7) * 4;
-  const int va = I0 + lv < d ? order[I0 + lv] : -1;
-  const int vb = J0 + lv < d ? order[J0 + lv] : -1;
-  const double* za = Xd + (int64_t)(va < 0 ? 0 : va) * ldx;
-  const double* zb = Xd + (int64_t)(vb < 0 ? 0 : vb) * ldx;
-  const double ma = va < 0 ? 0.0 : mu[va], mb = vb < 0 ? 0.0 : mu[vb];
-  double4_t acc = {0.0, 0.0, 0.0, 0.0};
-  for (int s0 = 0; s0 < n; s0 += KC) {
-    __syncthreads();
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const int s = s0 + ls + u;
-      As[ls + u][lv] = (s < n && va >= 0) ? za[s] - ma : 0.0;
-      Bs[ls + u][lv] = (s < n && vb >= 0) ? zb[s] - mb : 0.0;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int kk = 0; kk < KC / 4; ++kk) {
-      const double a = As[kk * 4 + (lane >> 4)][wi * 16 + (lane & 15)];
-      const double b = Bs[kk * 4 + (lane >> 4)][wj * 16 + (lane & 15)];
-      acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, acc, 0, 0, 0);
-    }
-  }
+// upper 32 x 32 tiles computed and mirrored; a workgroup per tile and range of
+// samples (blockIdx.y), whose tiles k_cov_sum adds when there are several.
+__device__ void cov_store(double* S, int d, int bi, int bj, const double4_t& acc) {
 #pragma unroll
   for (int r = 0; r < 4; ++r) {
-    const int i = I0 + wi * 16 + 4 * r + (lane >> 4);
-    const int j = J0 + wj * 16 + (lane & 15);
+    const int i = bi * 32 + tile_row(r), j = bj * 32 + tile_col();
     if (i < d && j < d && (bi != bj || i <= j)) {
       S[(int64_t)i * d + j] = acc[r];
       S[(int64_t)j * d + i] = acc[r];
     }
   }
+}
+
+__global__ __launch_bounds__(256) void k_cov_perm(const double* __restrict__ Xd, int64_t ldx,
+                                                  int n, int d,
+                                                  const int32_t* __restrict__ order,
+                                                  const double* __restrict__ mu, int nb,
+                                                  double* __restrict__ S,
+                                                  double* __restrict__ part) {
+  __shared__ Tile64 T;
+  int bi, bj;
+  decode_tile(blockIdx.x, nb, bi, bj);
+  const int lv = threadIdx.x >> 3, ls = (threadIdx.x & 7) * 4;
+  const int va = bi * 32 + lv < d ? order[bi * 32 + lv] : -1;
+  const int vb = bj * 32 + lv < d ? order[bj * 32 + lv] : -1;
+  const double* za = Xd + (int64_t)(va < 0 ? 0 : va) * ldx;
+  const double* zb = Xd + (int64_t)(vb < 0 ? 0 : vb) * ldx;
+  const double ma = va < 0 ? 0.0 : mu[va], mb = vb < 0 ? 0.0 : mu[vb];
+  const int chunks = (n + 31) / 32, per = (chunks + gridDim.y - 1) / gridDim.y;
+  const double4_t acc = mfma_chunks<true>(
+      T, blockIdx.y * per, min((int)(blockIdx.y + 1) * per, chunks), double4_t{0.0, 0.0, 0.0, 0.0},
+      [&](int c, double (&v)[4]) { centred4(za, c * 32 + ls, n, va >= 0, ma, v); },
+      [&](int c, double (&v)[4]) { centred4(zb, c * 32 + ls, n, vb >= 0, mb, v); });
+  if (gridDim.y == 1) cov_store(S, d, bi, bj, acc);
+  else tile_put(part + ((int64_t)blockIdx.y * gridDim.x + blockIdx.x) * kTileElems, acc);
+}
+
+__global__ __launch_bounds__(256) void k_cov_sum(const double* __restrict__ part, int nsplit,
+                                                 int d, int nb, double* __restrict__ S) {
+  int bi, bj;
+  decode_tile(blockIdx.x, nb, bi, bj);
+  cov_store(S, d, bi, bj, tile_sum(part, nsplit, gridDim.x, blockIdx.x));
 }
 
 // theta[t][i][j] = M[t][i][j] - sum_k B0[i][k] M[t][k][j] (16 x 16 tiles, LDS).
@@ -812,37 +871,42 @@ unsigned grid_for(int64_t n) {
 
 }  // namespace
 
-hipError_t launch_cholesky(double* A, int64_t lda, int p, double* tol, Ctrl* ctrl,
-                           hipStream_t st) {
-  hipLaunchKernelGGL(k_chol_tol, dim3(1), dim3(256), 0, st, A, lda, p, tol);
-  for (int k0 = 0; k0 < p; k0 += kNb) {
-    const int kb = p - k0 < kNb ? p - k0 : kNb;
-    hipLaunchKernelGGL(k_chol_diag, dim3(1), dim3(256), 0, st, A, lda, k0, kb, tol, ctrl);
-    const int rest = p - k0 - kb;
-    if (rest <= 0) break;
-    hipLaunchKernelGGL(k_chol_panel, dim3((unsigned)((rest + kPanelRows - 1) / kPanelRows)),
-                       dim3(kPanelRows), 0, st, A, lda, p, k0, kb);
-    const int nt = (rest + kNb - 1) / kNb;
-    hipLaunchKernelGGL(k_chol_update, dim3((unsigned)(nt * (nt + 1) / 2)), dim3(256), 0, st, A,
-                       lda, p, k0, kb, nt);
+// X's blocks below the diagonal from its diagonal blocks, level by level.
+static hipError_t tri_levels(const double* L, int64_t ldl, int p, double* X, int64_t ldx,
+                             hipStream_t st) {
+  for (int b = kNb; b < p; b *= 2) {
+    const int nt = b / kNb, pairs = (p - b + 2 * b - 1) / (2 * b);
+    const dim3 g((unsigned)(pairs * nt * nt));
+    hipLaunchKernelGGL(k_trinv_prod, g, dim3(256), 0, st, L, ldl, p, b, X, ldx);
+    hipLaunchKernelGGL(k_trinv_merge, g, dim3(256), 0, st, p, b, X, ldx);
   }
   return hipGetLastError();
 }
 
-hipError_t launch_tri_inverse(const double* L, int64_t ldl, int p, double* X, int64_t ldx,
-                              hipStream_t st) {
-  const int nb = (p + kNb - 1) / kNb;
-  hipLaunchKernelGGL(k_trinv_diag, dim3((unsigned)nb), dim3(64), 0, st, L, ldl, p, X, ldx);
-  for (int I = 1; I < nb; ++I)
-    hipLaunchKernelGGL(k_trinv_row, dim3((unsigned)I), dim3(256), 0, st, L, ldl, p, I, X, ldx);
-  return hipGetLastError();
+hipError_t launch_cholesky_inverse(double* A, int64_t lda, int p, double* X, int64_t ldx,
+                                   double* tol, Ctrl* ctrl, hipStream_t st) {
+  hipLaunchKernelGGL(k_chol_first, dim3((unsigned)((p + kNb - 1) / kNb)), dim3(256), 0, st, A,
+                     lda, p, X, ldx, tol, ctrl);
+  for (int k0 = 0; k0 + kNb < p; k0 += kNb) {
+    const int nt = (p - k0 - 1) / kNb;  // blocks of rows below the diagonal block
+    hipLaunchKernelGGL(k_chol_step, dim3((unsigned)(nt * (nt + 1) / 2)), dim3(256), 0, st, A, lda,
+                       p, k0, nt, X, ldx, (const double*)tol, ctrl);
+  }
+  return tri_levels(A, lda, p, X, ldx, st);
 }
 
-hipError_t launch_tri_adjacency(const double* L, int64_t ldl, int p, const int32_t* order,
-                                double* B, double* Y, hipStream_t st) {
-  LG_HIP(launch_tri_inverse(L, ldl, p, Y, p, st));
-  hipLaunchKernelGGL(k_adj_scatter, dim3(grid_for((int64_t)p * p)), dim3(256), 0, st, L, ldl, Y,
-                     (int64_t)p, p, order, B);
+hipError_t launch_unit_inverse(const double* L, int64_t ldl, int p, double* X, int64_t ldx,
+                              hipStream_t st) {
+  hipLaunchKernelGGL(k_trinv_diag, dim3((unsigned)((p + kNb - 1) / kNb)), dim3(64), 0, st, L, ldl,
+                     p, X, ldx);
+  return tri_levels(L, ldl, p, X, ldx, st);
+}
+
+hipError_t launch_tri_adjacency(double* A, int p, const int32_t* order, double* B, double* Y,
+                                double* tol, Ctrl* ctrl, hipStream_t st) {
+  LG_HIP(launch_cholesky_inverse(A, p, p, Y, p, tol, ctrl, st));
+  hipLaunchKernelGGL(k_adj_scatter, dim3(grid_for((int64_t)p * p)), dim3(256), 0, st,
+                     (const double*)A, (int64_t)p, Y, (int64_t)p, p, order, B);
   return hipGetLastError();
 }
 
@@ -861,11 +925,15 @@ hipError_t launch_perm_scale(const double* rho, int64_t ldr, const double* sig,
 }
 
 hipError_t launch_cov_perm(const double* Xd, int64_t ldx, int n, int d, const int32_t* order,
-                           double* mu, double* S, hipStream_t st) {
+                           double* mu, double* S, int nsplit, double* part, hipStream_t st) {
   hipLaunchKernelGGL(k_row_mean, dim3((unsigned)d), dim3(256), 0, st, Xd, ldx, n, mu);
   const int nb = (d + 31) / 32;
-  hipLaunchKernelGGL(k_cov_perm, dim3((unsigned)(nb * (nb + 1) / 2)), dim3(256), 0, st, Xd, ldx,
-                     n, d, order, mu, nb, S);
+  const unsigned tiles = (unsigned)(nb * (nb + 1) / 2);
+  hipLaunchKernelGGL(k_cov_perm, dim3(tiles, (unsigned)nsplit), dim3(256), 0, st, Xd, ldx, n, d,
+                     order, mu, nb, S, part);
+  if (nsplit > 1)
+    hipLaunchKernelGGL(k_cov_sum, dim3(tiles), dim3(256), 0, st, (const double*)part, nsplit, d,
+                       nb, S);
   return hipGetLastError();
 }
 
@@ -918,12 +986,14 @@ hipError_t launch_adjacency_pruned(const PruneLayout& A, char* ws, const float* 
   dim3 g1((unsigned)(A.ldx / 64), (unsigned)((A.d + 63) / 64));
   hipLaunchKernelGGL(k_gather_f64, g1, dim3(256), 0, st, X, ldx, rows, n, d, (int)A.ldx, Xd,
                      A.ldx, ctrl);
-  LG_HIP(launch_cov_perm(Xd, A.ldx, n, d, order, at<double>(ws, A.mu), Sm, st));
+  // partial tiles lie in the regions from the correlation matrix on (7 d^2
+  // doubles), which are written later
+  LG_HIP(launch_cov_perm(Xd, A.ldx, n, d, order, at<double>(ws, A.mu), Sm,
+                         gram_splits(n, d, 7 * (int64_t)d * d / kTileElems), Rm, st));
   const int64_t dd = (int64_t)d * d;
   hipLaunchKernelGGL(k_corr, dim3(grid_for(dd)), dim3(256), 0, st, (const double*)Sm, d, n,
                      at<double>(ws, A.sd), Rm, Lm, ctrl);
-  LG_HIP(launch_cholesky(Lm, d, d, at<double>(ws, A.tol), ctrl, st));
-  LG_HIP(launch_tri_inverse(Lm, d, d, Ym, d, st));
+  LG_HIP(launch_cholesky_inverse(Lm, d, d, Ym, d, at<double>(ws, A.tol), ctrl, st));
   hipLaunchKernelGGL(k_zero_f64, dim3(grid_for(dd)), dim3(256), 0, st, B, dd);
   if (d < 2) return hipGetLastError();
   const int cap = max_active < kLassoMaxActive ? max_active : kLassoMaxActive;
@@ -957,7 +1027,7 @@ hipError_t launch_total_effects(const EffectsLayout& A, char* ws, const double* 
   double* Am = at<double>(ws, A.a);
   double* Xm = at<double>(ws, A.x);
   hipLaunchKernelGGL(k_unit_lower, dim3(grid_for(dd)), dim3(256), 0, st, B, order, d, Am);
-  LG_HIP(launch_tri_inverse(Am, d, d, Xm, d, st));
+  LG_HIP(launch_unit_inverse(Am, d, d, Xm, d, st));
   hipLaunchKernelGGL(k_scatter_lower, dim3(grid_for(dd)), dim3(256), 0, st, (const double*)Xm,
                      order, d, T);
   return hipGetLastError();
