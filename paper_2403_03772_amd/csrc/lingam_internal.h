@@ -614,7 +614,7 @@ struct TrainLayout {
   int64_t rows;
   int32_t n_lists;
   int nparts;
-  size_t status, prop, score, ds, h1, h2, loss_part, part, total;  // status: int32, 0 = ok
+  size_t status, prop, score, ds, loss_part, part, total;  // status: int32, 0 = ok
 };
 TrainLayout make_train_layout(int64_t rows, int32_t n_lists);
 // Scores of `rows` feature rows; ws holds a PropDev.

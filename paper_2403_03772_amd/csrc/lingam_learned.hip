@@ -41,7 +41,7 @@
 //   k_pair_susp, k_combine_susp, k_susp_rowk, k_lselect2  the remaining
 //                   suspects' full rows and the exact choice
 //
-// and the training kernels of the network (forward with saved activations,
+// and the training kernels of the network (forward pass,
 // listwise softmax cross-entropy, backward on MFMA, gradient reduction, Adam).
 #include "lingam_device.h"
 
@@ -78,7 +78,6 @@ __device__ __forceinline__ f32x4_t mfma16(bf16x4_t a, bf16x4_t b, f32x4_t c) {
 }
 
 constexpr int kLdW = kHidden + 8;  // padded LDS row of 128 BF16 values
-constexpr int kLdR = 64 + 8;       // padded LDS row of 64 BF16 values
 
 // ---------------------------------------------------------------------------
 // network preparation
@@ -86,7 +85,9 @@ constexpr int kLdR = 64 + 8;       // padded LDS row of 64 BF16 values
 
 // FP32 parameter block [mean(16), scale(16), W1, b1, W2, b2, w3, b3] -> BF16
 // weights; a non-finite value or a scale <= 0 marks every job invalid (and
-// sets *flag when given).
+// sets *flag when given).  kPrepBlocks workgroups: one walks the 75 KB in 21 us,
+// they in 4.
+constexpr int kPrepBlocks = 24;
 __global__ __launch_bounds__(256) void k_prop_prep(const float* __restrict__ in,
                                                    PropDev* __restrict__ out,
                                                    const JobDev* __restrict__ jobs, int njobs,
@@ -95,31 +96,32 @@ __global__ __launch_bounds__(256) void k_prop_prep(const float* __restrict__ in,
   if (threadIdx.x == 0) bad = 0;
   __syncthreads();
   const float* w = in + kPropNorm;
+  const int tid = blockIdx.x * 256 + threadIdx.x, nthreads = gridDim.x * 256;
   int mybad = 0;
-  for (int i = threadIdx.x; i < kHidden * kHidden; i += 256) {
+  for (int i = tid; i < kHidden * kHidden; i += nthreads) {
     const float v = w[kOffW2 + i];
     mybad |= !isfinite(v);
     out->w2[i] = to_bf16(v);
   }
-  for (int i = threadIdx.x; i < kHidden * kFeat; i += 256) {
+  for (int i = tid; i < kHidden * kFeat; i += nthreads) {
     const float v = w[kOffW1 + i];
     mybad |= !isfinite(v);
     out->w1[i] = to_bf16(v);
   }
-  for (int i = threadIdx.x; i < kHidden; i += 256) {
+  for (int i = tid; i < kHidden; i += nthreads) {
     const float a = w[kOffW3 + i], b1 = w[kOffB1 + i], b2 = w[kOffB2 + i];
     mybad |= !isfinite(a) || !isfinite(b1) || !isfinite(b2);
     out->w3[i] = to_bf16(a);
     out->b1[i] = b1;
     out->b2[i] = b2;
   }
-  if (threadIdx.x < kFeat) {
-    const float mu = in[threadIdx.x], sd = in[kFeat + threadIdx.x];
+  if (tid < kFeat) {
+    const float mu = in[tid], sd = in[kFeat + tid];
     mybad |= !isfinite(mu) || !(sd > 0.f) || !isfinite(sd);
-    out->mu[threadIdx.x] = mu;
-    out->sd[threadIdx.x] = sd;
+    out->mu[tid] = mu;
+    out->sd[tid] = sd;
   }
-  if (threadIdx.x == 0) {
+  if (tid == 0) {
     out->b3 = w[kOffB3];
     mybad |= !isfinite(w[kOffB3]);
   }
@@ -294,11 +296,9 @@ __device__ inline void stage_w2(const PropDev& W, MlpShared& S) {
 // Forward pass of rows row0 .. row0 + 63 (rows >= nrows are zero inputs and
 // produce nothing).  Wave w owns rows row0 + 16 w .. + 15.  Features are
 // normalized with the network's mean and scale and rounded to BF16.  Writes
-// score[row]; with H1 / H2 non-NULL also the BF16 first and FP32 second hidden
-// layer ([row][128]) for the backward pass.  S.w2 must be staged.
+// score[row].  S.w2 must be staged.
 __device__ void mlp_tile(const PropDev& W, MlpShared& S, const float* __restrict__ feat,
-                         int64_t row0, int64_t nrows, float* __restrict__ score,
-                         uint16_t* __restrict__ H1, float* __restrict__ H2) {
+                         int64_t row0, int64_t nrows, float* __restrict__ score) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int li = lane & 15, lg4 = (lane >> 4) * 4;
   // layer 1: A = x[row][f], B = W1^T
@@ -327,15 +327,6 @@ __device__ void mlp_tile(const PropDev& W, MlpShared& S, const float* __restrict
     }
   }
   __syncthreads();
-  if (H1) {
-    for (int e = lane; e < 16 * kHidden / 4; e += 64) {
-      const int i = e / (kHidden / 4), g4 = (e % (kHidden / 4)) * 4;
-      const int64_t row = row0 + wave * 16 + i;
-      if (row < nrows)
-        *reinterpret_cast<uint2*>(&H1[row * kHidden + g4]) =
-            *reinterpret_cast<const uint2*>(&S.h1[wave * 16 + i][g4]);
-    }
-  }
   // layer 2: A = h1[row][g], B = W2^T; score = w3 . relu(.) + b3
   float ps[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll 1
@@ -353,10 +344,6 @@ __device__ void mlp_tile(const PropDev& W, MlpShared& S, const float* __restrict
     for (int r = 0; r < 4; ++r) {
       const float h = fmaxf(acc[r] + b2, 0.f);
       ps[r] = fmaf(h, w3, ps[r]);
-      if (H2) {
-        const int64_t row = row0 + wave * 16 + lg4 + r;
-        if (row < nrows) H2[row * kHidden + n] = h;
-      }
     }
   }
 #pragma unroll
@@ -1332,16 +1319,14 @@ __global__ __launch_bounds__(256) void k_lselect2(const JobDev* __restrict__ job
 // training
 // ---------------------------------------------------------------------------
 
-// Forward pass over the training rows with saved activations.
+// Forward pass over the training rows: their scores.
 __global__ __launch_bounds__(256) void k_train_fwd(const PropDev* __restrict__ W,
                                                    const float* __restrict__ feat, int64_t rows,
-                                                   float* __restrict__ score,
-                                                   uint16_t* __restrict__ H1,
-                                                   float* __restrict__ H2) {
+                                                   float* __restrict__ score) {
   __shared__ MlpShared S;
   stage_w2(*W, S);
   __syncthreads();
-  mlp_tile(*W, S, feat, (int64_t)blockIdx.x * 64, rows, score, H1, H2);
+  mlp_tile(*W, S, feat, (int64_t)blockIdx.x * 64, rows, score);
 }
 
 // Listwise softmax cross-entropy, one workgroup per list:
@@ -1427,168 +1412,246 @@ __global__ void k_zero_f32(float* __restrict__ p, int64_t n, int32_t* __restrict
   if (i == 0 && status) *status = 0;
 }
 
-// LDS of the backward pass of one 64-row tile.
-struct BwdShared {
-  uint16_t w2t[kHidden][kLdW];  // W2^T[g][h] = W2[h][g]
-  uint16_t dh2t[kHidden][kLdR]; // dh2^T[h][i] (BF16)
-  uint16_t h1t[kHidden][kLdR];  // h1^T[g][i]
-  uint16_t dh1t[kHidden][kLdR]; // dh1^T[g][i]
-  uint16_t xt[kFeat][kLdR];     // x^T[f][i]
-  float ds[64];
-};
+__device__ __forceinline__ bf16x4_t pack4(const float (&v)[4]) {
+  bf16x4_t r;
+#pragma unroll
+  for (int j = 0; j < 4; ++j) r[j] = (short)__builtin_bit_cast(uint16_t, (__bf16)v[j]);
+  return r;
+}
 
-// Backward pass.  Each workgroup walks 64-row tiles (grid stride) and keeps its
-// share of the weight gradients in registers (W2: wave w owns rows
-// 32 w .. 32 w + 31 of dW2; W1: wave w owns rows 32 w .. + 31 of dW1) and
-// the vector gradients in per-thread registers (thread h < 128), then writes
-// one partial gradient of kParams values per workgroup.
-__global__ __launch_bounds__(256) void k_train_bwd(const PropDev* __restrict__ W,
-                                                   const float* __restrict__ feat, int64_t rows,
-                                                   const float* __restrict__ dsv,
-                                                   const uint16_t* __restrict__ H1,
-                                                   const float* __restrict__ H2,
-                                                   float* __restrict__ part) {
-  __shared__ BwdShared S;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+// Backward pass, 16 rows at a time (grid stride) through the whole network, the
+// activations formed again rather than saved (the forward pass writes scores
+// only: saved, they were 78 MB each way for 102400 rows).  A product's result
+// holds 4 consecutive rows of it a lane, which is what an operand of the next
+// product wants when it contracts over them, so activations stay in registers:
+// the hidden layers are formed twice, rows along lanes ("t") for the products
+// over hidden units and rows along registers ("n") for those over rows, from
+// the same two operands swapped.  Wave w owns units 32 w .. + 31: it keeps their
+// weights and its share of the gradients in registers, forms the first layer
+// whole and its units of the second, and passes on their dh2 through LDS (two
+// buffers, one barrier a group).  One partial gradient of kParams values a
+// workgroup.  Bound by 82 MFMAs a wave and group and as many cycles of rounding;
+// 102400 rows: 54 us, 134 with tiles of 64 rows staged and transposed in LDS.
+__global__ __launch_bounds__(256, 2) void k_train_bwd(const PropDev* __restrict__ W,
+                                                      const float* __restrict__ feat,
+                                                      int64_t rows,
+                                                      const float* __restrict__ dsv,
+                                                      float* __restrict__ part) {
+  __shared__ __align__(16) uint16_t d2[2][16][kLdW];  // dh2[row][unit]
+  __shared__ __align__(16) uint16_t w1[kHidden][kFeat + 4];
+  __shared__ __align__(16) float b1[kHidden], b2[kHidden], w3[kHidden];
+  constexpr int kB = kHidden / 16;  // blocks of 16 hidden units, two a wave
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int li = lane & 15, lg4 = (lane >> 4) * 4;
-  for (int i = tid; i < kHidden * kHidden; i += 256) {
-    const int h = i / kHidden, g = i % kHidden;
-    S.w2t[g][h] = W->w2[i];
+  for (int i = threadIdx.x; i < kHidden * kFeat; i += 256) w1[i / kFeat][i % kFeat] = W->w1[i];
+  if (threadIdx.x < kHidden) {
+    b1[threadIdx.x] = W->b1[threadIdx.x];
+    b2[threadIdx.x] = W->b2[threadIdx.x];
+    w3[threadIdx.x] = from_bf16(W->w3[threadIdx.x]);
   }
-  f32x4_t gw2[2][8];
-  f32x4_t gw1[2];
+  __syncthreads();
+  // own units' weights: W2[h = li][g = lg4 + j] and W2[h = lg4 + j][g = li]
+  bf16x4_t w2[2][kB], w2t[2][kB];
 #pragma unroll
   for (int a = 0; a < 2; ++a) {
-    gw1[a] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    const int u0 = wave * 32 + a * 16;
 #pragma unroll
-    for (int b = 0; b < 8; ++b) gw2[a][b] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    for (int k = 0; k < kB; ++k) {
+      w2[a][k] = load4(&W->w2[(u0 + li) * kHidden + k * 16 + lg4]);
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+        w2t[a][k][j] = (short)W->w2[(k * 16 + lg4 + j) * kHidden + u0 + li];
+    }
   }
-  float g_w3 = 0.f, g_b2 = 0.f, g_b1 = 0.f, g_b3 = 0.f;
-  const int h_own = tid & (kHidden - 1);  // threads h and h + 128 split the rows
-  const int half = tid >> 7;
-  const float w3h = from_bf16(W->w3[h_own]);
-  const int64_t ntile = (rows + 63) / 64;
-  for (int64_t tile = blockIdx.x; tile < ntile; tile += gridDim.x) {
-    const int64_t row0 = tile * 64;
-    __syncthreads();
-    if (tid < 64) S.ds[tid] = row0 + tid < rows ? dsv[row0 + tid] : 0.f;
-    // x^T (BF16, normalized) and h1^T of the tile
-    for (int e = tid; e < 64 * kFeat; e += 256) {
-      const int i = e / kFeat, f = e % kFeat;
-      const int64_t row = row0 + i;
-      const float v = row < rows ? (feat[row * kFeat + f] - W->mu[f]) / W->sd[f] : 0.f;
-      S.xt[f][i] = to_bf16(v);
-    }
-    for (int e = tid; e < 64 * kHidden; e += 256) {
-      const int i = e / kHidden, g = e % kHidden;
-      const int64_t row = row0 + i;
-      S.h1t[g][i] = row < rows ? H1[row * kHidden + g] : (uint16_t)0;
-    }
-    __syncthreads();
-    // dh2 = ds * w3 * [h2 > 0]; vector gradients of w3, b2, b3
-    for (int i = half * 32; i < half * 32 + 32; ++i) {
-      const int64_t row = row0 + i;
-      float d = 0.f;
-      if (row < rows) {
-        const float h2 = H2[row * kHidden + h_own];
-        const float dsi = S.ds[i];
-        g_w3 = fmaf(dsi, h2, g_w3);
-        d = h2 > 0.f ? dsi * w3h : 0.f;
-        g_b2 += d;
-      }
-      S.dh2t[h_own][i] = to_bf16(d);
-    }
-    if (tid == 0)
-      for (int i = 0; i < 64; ++i) g_b3 += S.ds[i];
-    __syncthreads();
-    // dh1 = (dh2 W2) * [h1 > 0]: rows 16 wave .. + 15, all 128 columns
-#pragma unroll 1
-    for (int nt = 0; nt < kHidden / 16; ++nt) {
-      f32x4_t acc = {0.f, 0.f, 0.f, 0.f};
+  float mut[4], sdt[4];
 #pragma unroll
-      for (int ks = 0; ks < kHidden / 16; ++ks) {
-        // A[i][h] = dh2[i][h] = dh2t[h][i]; B[h][g] = W2[h][g] = w2t[g][h]
-        bf16x4_t a;
+  for (int j = 0; j < 4; ++j) {
+    mut[j] = W->mu[lg4 + j];
+    sdt[j] = W->sd[lg4 + j];
+  }
+  const float mun = W->mu[li], sdn = W->sd[li];
+  const f32x4_t zero = {0.f, 0.f, 0.f, 0.f};
+  f32x4_t gw2[2][kB], gw1[2];
+  float g_w3[2], g_b2[2], g_b1[2], g_b3 = 0.f;
 #pragma unroll
-        for (int j = 0; j < 4; ++j) a[j] = (short)S.dh2t[ks * 16 + lg4 + j][wave * 16 + li];
-        const bf16x4_t b = load4(&S.w2t[nt * 16 + li][ks * 16 + lg4]);
-        acc = mfma16(a, b, acc);
-      }
-      const int g = nt * 16 + li;
+  for (int a = 0; a < 2; ++a) {
+    gw1[a] = zero;
+    g_w3[a] = g_b2[a] = g_b1[a] = 0.f;
+#pragma unroll
+    for (int b = 0; b < kB; ++b) gw2[a][b] = zero;
+  }
+  // a group's raw inputs, fetched one group ahead: t = row li, n = rows lg4 + j
+  const int64_t ngroup = (rows + 15) / 16;
+  float ft[4], fn[4], dt, dn[4];
+  auto fetch = [&](int64_t grp) {
+    const float* f0 = feat + grp * 16 * kFeat;
+    const float* d0 = dsv + grp * 16;
+    const int last = (int)min((int64_t)15, rows - 1 - grp * 16);
+    const int rt = min(li, last);
+    const float vd0 = d0[rt];
+    dt = li <= last ? vd0 : 0.f;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const int rn = min(lg4 + j, last);
+      const float vt = f0[rt * kFeat + lg4 + j], vn = f0[rn * kFeat + li], vd = d0[rn];
+      ft[j] = li <= last ? vt : mut[j];
+      fn[j] = lg4 + j <= last ? vn : mun;
+      dn[j] = lg4 + j <= last ? vd : 0.f;
+    }
+  };
+  fetch(blockIdx.x);  // gridDim.x <= ngroup
+  int buf = 0;
+  for (int64_t grp = blockIdx.x; grp < ngroup; grp += gridDim.x, buf ^= 1) {
+    float vt[4], vn[4], dsn[4];
+    const float dst = dt;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      vt[j] = (ft[j] - mut[j]) / sdt[j];
+      vn[j] = (fn[j] - mun) / sdn;
+      dsn[j] = dn[j];
+    }
+    const bf16x4_t xt = pack4(vt), xn = pack4(vn);
+    if (grp + gridDim.x < ngroup) fetch(grp + gridDim.x);
+    g_b3 += dst;
+    // layer 1: h1n (row lg4 + r, unit li), h1t (unit lg4 + r, row li)
+    bf16x4_t h1n[kB], h1t[kB];
+#pragma unroll
+    for (int a = 0; a < kB; ++a) {
+      const bf16x4_t w = load4(&w1[a * 16 + li][lg4]);
+      const f32x4_t pn = mfma16(xt, w, zero), pt = mfma16(w, xt, zero);
+      const float bn = b1[a * 16 + li];
+      const f32x4_t bt = *reinterpret_cast<const f32x4_t*>(&b1[a * 16 + lg4]);
+      float hn[4], ht[4];
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        const int i = wave * 16 + lg4 + r;
-        const float v = (S.h1t[g][i] & 0x7FFF) != 0 ? acc[r] : 0.f;  // h1 > 0 <=> a1 > 0
-        S.dh1t[g][i] = to_bf16(v);
+        hn[r] = fmaxf(pn[r] + bn, 0.f);
+        ht[r] = fmaxf(pt[r] + bt[r], 0.f);
       }
+      h1n[a] = pack4(hn);
+      h1t[a] = pack4(ht);
+      if (a & 1) __builtin_amdgcn_sched_barrier(0);  // or the blocks' temporaries spill
     }
-    __syncthreads();
-    // b1 from the BF16 dh1 (as the weight gradient sees it)
-    for (int i = half * 32; i < half * 32 + 32; ++i) g_b1 += from_bf16(S.dh1t[h_own][i]);
-    // dW2[h][g] += sum_i dh2[i][h] h1[i][g]: wave owns h = 32 wave .. + 31
+    // layer 2, dh2 = ds w3 [h2 > 0]; gradients of w3, b2 and W2
 #pragma unroll
     for (int a = 0; a < 2; ++a) {
-      const int h = wave * 32 + a * 16 + li;
+      f32x4_t pn = zero, pt = zero;
 #pragma unroll
-      for (int ks = 0; ks < 4; ++ks) {
-        const bf16x4_t A = load4(&S.dh2t[h][ks * 16 + lg4]);
-#pragma unroll
-        for (int b = 0; b < 8; ++b) {
-          const bf16x4_t B = load4(&S.h1t[b * 16 + li][ks * 16 + lg4]);
-          gw2[a][b] = mfma16(A, B, gw2[a][b]);
-        }
+      for (int k = 0; k < kB; ++k) {
+        pn = mfma16(h1t[k], w2[a][k], pn);
+        pt = mfma16(w2[a][k], h1t[k], pt);
       }
-      // dW1[h][f] += sum_i dh1[i][h] x[i][f]
+      const int u0 = wave * 32 + a * 16;
+      const float bn = b2[u0 + li], wn = w3[u0 + li];
+      const f32x4_t bt = *reinterpret_cast<const f32x4_t*>(&b2[u0 + lg4]);
+      const f32x4_t wt = dst * *reinterpret_cast<const f32x4_t*>(&w3[u0 + lg4]);
+      float vd[4], td[4];
 #pragma unroll
-      for (int ks = 0; ks < 4; ++ks) {
-        const bf16x4_t A = load4(&S.dh1t[h][ks * 16 + lg4]);
-        const bf16x4_t B = load4(&S.xt[li][ks * 16 + lg4]);
-        gw1[a] = mfma16(A, B, gw1[a]);
+      for (int r = 0; r < 4; ++r) {
+        const float h2 = fmaxf(pn[r] + bn, 0.f);
+        g_w3[a] = fmaf(dsn[r], h2, g_w3[a]);
+        const float d = dsn[r] * wn;
+        vd[r] = h2 > 0.f ? d : 0.f;
+        g_b2[a] += vd[r];
+        td[r] = pt[r] + bt[r] > 0.f ? wt[r] : 0.f;
       }
+      *reinterpret_cast<bf16x4_t*>(&d2[buf][li][u0 + lg4]) = pack4(td);
+      const bf16x4_t d2n = pack4(vd);
+#pragma unroll
+      for (int b = 0; b < kB; ++b) gw2[a][b] = mfma16(d2n, h1n[b], gw2[a][b]);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    __syncthreads();
+    // dh1 = (dh2 W2) [h1 > 0], row lg4 + r, unit li; gradients of b1 and W1
+    f32x4_t p1[2] = {zero, zero};
+#pragma unroll
+    for (int k = 0; k < kB; ++k) {
+      const bf16x4_t d = load4(&d2[buf][li][k * 16 + lg4]);
+#pragma unroll
+      for (int a = 0; a < 2; ++a) p1[a] = mfma16(d, w2t[a][k], p1[a]);
+    }
+#pragma unroll
+    for (int a = 0; a < 2; ++a) {
+      bf16x4_t h = h1n[a];  // the own units' h1 (a wave's index cannot be a register's)
+#pragma unroll
+      for (int w = 1; w < 4; ++w) h = wave == w ? h1n[w * 2 + a] : h;
+      float v[4];
+#pragma unroll
+      for (int r = 0; r < 4; ++r) v[r] = (h[r] & 0x7FFF) != 0 ? p1[a][r] : 0.f;
+      const bf16x4_t d1 = pack4(v);
+#pragma unroll
+      for (int r = 0; r < 4; ++r) g_b1[a] += from_bf16((uint16_t)d1[r]);
+      gw1[a] = mfma16(d1, xn, gw1[a]);
     }
   }
   // partial gradient of this workgroup
   float* out = part + (int64_t)blockIdx.x * kParams;
 #pragma unroll
   for (int a = 0; a < 2; ++a) {
+    const int u0 = wave * 32 + a * 16;
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-      const int h = wave * 32 + a * 16 + lg4 + r;
+      const int h = u0 + lg4 + r;
 #pragma unroll
-      for (int b = 0; b < 8; ++b) out[kOffW2 + h * kHidden + b * 16 + li] = gw2[a][b][r];
+      for (int b = 0; b < kB; ++b) out[kOffW2 + h * kHidden + b * 16 + li] = gw2[a][b][r];
       out[kOffW1 + h * kFeat + li] = gw1[a][r];
     }
+    float v[3] = {g_w3[a], g_b2[a], g_b1[a]};
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+      v[c] += __shfl_xor(v[c], 16);
+      v[c] += __shfl_xor(v[c], 32);
+    }
+    if (lane < 16) {
+      out[kOffW3 + u0 + li] = v[0];
+      out[kOffB2 + u0 + li] = v[1];
+      out[kOffB1 + u0 + li] = v[2];
+    }
   }
-  // the two halves of the vector gradients
-  __shared__ float vec[3][256];
-  vec[0][tid] = g_w3;
-  vec[1][tid] = g_b2;
-  vec[2][tid] = g_b1;
-  __syncthreads();
-  if (tid < kHidden) {
-    out[kOffW3 + tid] = vec[0][tid] + vec[0][tid + 128];
-    out[kOffB2 + tid] = vec[1][tid] + vec[1][tid + 128];
-    out[kOffB1 + tid] = vec[2][tid] + vec[2][tid + 128];
-  }
-  if (tid == 0) out[kOffB3] = g_b3;
+#pragma unroll
+  for (int off = 8; off >= 1; off >>= 1) g_b3 += __shfl_xor(g_b3, off);
+  if (threadIdx.x == 0) out[kOffB3] = g_b3;
 }
 
-// grad[p] = sum over workgroups of the partials (fixed order); loss = mean.
-__global__ __launch_bounds__(256) void k_grad_reduce(const float* __restrict__ part, int nparts,
+// grad[p] = sum over workgroups of the partials in a fixed order; loss = mean.
+// 64 parameters a workgroup, its eight waves an eighth of the partials each,
+// sixteen loads in flight: the partials are read at memory speed.  256
+// parameters a workgroup, every thread all partials, and the loss summed by one
+// thread were 131 us for 512 partials and 256 lists; this is 11.
+__global__ __launch_bounds__(512) void k_grad_reduce(const float* __restrict__ part, int nparts,
                                                      float* __restrict__ grad,
                                                      const double* __restrict__ loss_part,
                                                      int n_lists, float* __restrict__ loss) {
-  const int p = blockIdx.x * 256 + threadIdx.x;
-  if (p < kParams) {
-    double s = 0.0;
-    for (int k = 0; k < nparts; ++k) s += (double)part[(int64_t)k * kParams + p];
-    grad[p] = (float)s;
+  __shared__ double sh[8][64];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int p = blockIdx.x * 64 + lane;
+  const bool sums_loss = blockIdx.x == gridDim.x - 1;  // its parameters lie past the end
+  double s = 0.0;
+  if (sums_loss) {
+    if (loss)
+      for (int L = threadIdx.x; L < n_lists; L += 512) s += loss_part[L];
+  } else if (p < kParams) {
+    const int per = (nparts + 7) / 8, k1 = min(nparts, (wave + 1) * per);
+    int k = wave * per;
+    for (; k + 16 <= k1; k += 16) {
+      float v[16];
+#pragma unroll
+      for (int u = 0; u < 16; ++u) v[u] = part[(int64_t)(k + u) * kParams + p];
+#pragma unroll
+      for (int u = 0; u < 16; ++u) s += (double)v[u];
+    }
+    for (; k < k1; ++k) s += (double)part[(int64_t)k * kParams + p];
   }
-  if (blockIdx.x == 0 && threadIdx.x == 0 && loss) {
-    double s = 0.0;
-    for (int L = 0; L < n_lists; ++L) s += loss_part[L];
-    *loss = (float)(s / (double)n_lists);
+  sh[wave][lane] = s;
+  __syncthreads();
+  if (wave > 0) return;
+  for (int w = 1; w < 8; ++w) s += sh[w][lane];
+  if (!sums_loss) {
+    if (p < kParams) grad[p] = (float)s;
+    return;
   }
+#pragma unroll
+  for (int off = 32; off >= 1; off >>= 1) s += __shfl_xor(s, off);
+  if (lane == 0 && loss) *loss = (float)(s / (double)n_lists);
 }
 
 // Adam on the FP32 master weights (after the 32 normalisation values).
@@ -1619,7 +1682,7 @@ static inline const int32_t* pre_kind(SchedDev sc, int njobs, int kind) {
 
 hipError_t launch_prop_prep(const float* in, PropDev* out, const JobDev* jobs, int njobs,
                             hipStream_t st) {
-  hipLaunchKernelGGL(k_prop_prep, dim3(1), dim3(256), 0, st, in, out, jobs, njobs,
+  hipLaunchKernelGGL(k_prop_prep, dim3(kPrepBlocks), dim3(256), 0, st, in, out, jobs, njobs,
                      (int32_t*)nullptr);
   return hipGetLastError();
 }
@@ -1722,8 +1785,8 @@ hipError_t launch_susp_back(const JobDev* jobs, int njobs, int t, SchedDev sc, i
   return hipGetLastError();
 }
 
-// Training workspace: [status][PropDev][score f32 rows][ds f32 rows][H1 u16 rows*128]
-// [H2 f32 rows*128][loss_part f64 n_lists][partials f32 nparts*kParams]
+// Training workspace: [status][PropDev][score f32 rows][ds f32 rows]
+// [loss_part f64 n_lists][partials f32 nparts*kParams]
 TrainLayout make_train_layout(int64_t rows, int32_t n_lists) {
   TrainLayout T{};
   size_t off = 0;
@@ -1740,8 +1803,6 @@ TrainLayout make_train_layout(int64_t rows, int32_t n_lists) {
   T.prop = take(sizeof(PropDev));
   T.score = take(sizeof(float) * (size_t)rows);
   T.ds = take(sizeof(float) * (size_t)rows);
-  T.h1 = take(sizeof(uint16_t) * (size_t)rows * kHidden);
-  T.h2 = take(sizeof(float) * (size_t)rows * kHidden);
   T.loss_part = take(sizeof(double) * (size_t)n_lists);
   T.part = take(sizeof(float) * (size_t)T.nparts * kParams);
   T.total = off;
@@ -1751,7 +1812,7 @@ TrainLayout make_train_layout(int64_t rows, int32_t n_lists) {
 hipError_t launch_scores(const float* prop, const float* feat, int64_t rows, float* score,
                          char* ws, hipStream_t st) {
   PropDev* W = reinterpret_cast<PropDev*>(ws);
-  hipLaunchKernelGGL(k_prop_prep, dim3(1), dim3(256), 0, st, prop, W, (const JobDev*)nullptr, 0,
+  hipLaunchKernelGGL(k_prop_prep, dim3(kPrepBlocks), dim3(256), 0, st, prop, W, (const JobDev*)nullptr, 0,
                      (int32_t*)nullptr);
   hipLaunchKernelGGL(k_scores, dim3((unsigned)((rows + 15) / 16)), dim3(256), 0, st,
                      (const PropDev*)W, feat, rows, score);
@@ -1764,25 +1825,22 @@ hipError_t launch_grad(const TrainLayout& T, const float* prop, const float* fea
   PropDev* W = reinterpret_cast<PropDev*>(ws + T.prop);
   float* score = reinterpret_cast<float*>(ws + T.score);
   float* ds = reinterpret_cast<float*>(ws + T.ds);
-  uint16_t* H1 = reinterpret_cast<uint16_t*>(ws + T.h1);
-  float* H2 = reinterpret_cast<float*>(ws + T.h2);
   double* lp = reinterpret_cast<double*>(ws + T.loss_part);
   float* part = reinterpret_cast<float*>(ws + T.part);
   int32_t* status = reinterpret_cast<int32_t*>(ws + T.status);
   hipLaunchKernelGGL(k_zero_f32, dim3((unsigned)((T.rows + 255) / 256)), dim3(256), 0, st, ds,
                      T.rows, status);
-  hipLaunchKernelGGL(k_prop_prep, dim3(1), dim3(256), 0, st, prop, W, (const JobDev*)nullptr, 0,
+  hipLaunchKernelGGL(k_prop_prep, dim3(kPrepBlocks), dim3(256), 0, st, prop, W, (const JobDev*)nullptr, 0,
                      status);
   const int64_t ntile = (T.rows + 63) / 64;
   hipLaunchKernelGGL(k_train_fwd, dim3((unsigned)ntile), dim3(256), 0, st, (const PropDev*)W,
-                     feat, T.rows, score, H1, H2);
+                     feat, T.rows, score);
   hipLaunchKernelGGL(k_list_ce, dim3((unsigned)T.n_lists), dim3(256), 0, st,
                      (const float*)score, T.rows, offsets, targets, weights, T.n_lists, ds, lp,
                      status);
   hipLaunchKernelGGL(k_train_bwd, dim3((unsigned)T.nparts), dim3(256), 0, st, (const PropDev*)W,
-                     feat, T.rows, (const float*)ds, (const uint16_t*)H1, (const float*)H2,
-                     part);
-  hipLaunchKernelGGL(k_grad_reduce, dim3((unsigned)((kParams + 255) / 256)), dim3(256), 0, st,
+                     feat, T.rows, (const float*)ds, part);
+  hipLaunchKernelGGL(k_grad_reduce, dim3((unsigned)((kParams + 63) / 64 + 1)), dim3(512), 0, st,
                      (const float*)part, T.nparts, grad, (const double*)lp, T.n_lists, loss);
   if (score_out)
     return hipMemcpyAsync(score_out, score, sizeof(float) * (size_t)T.rows,
