@@ -511,51 +511,105 @@ __global__ void k_zero_f64(double* __restrict__ p, int64_t n) {
     p[i] = 0.0;
 }
 
+// Path state of a target of at most this many predictors in LDS.
+constexpr int kLarsLds = 1024;
+
 struct LarsShared {
-  double M[kLassoMaxActive][kLassoMaxActive + 1];  // inverse of G on the active set
-  double g[kLassoMaxActive], v[kLassoMaxActive], wv[kLassoMaxActive];
+  // inverse of G on the active set; the refit's matrix with its right side below
+  double M[kLassoMaxActive + 1][kLassoMaxActive + 1];
+  double g[kLassoMaxActive], v[kLassoMaxActive], wv[kLassoMaxActive], cf[kLassoMaxActive];
   double sgn[kLassoMaxActive];
+  int64_t row[kLassoMaxActive];  // idx d: rows of R
   int idx[kLassoMaxActive];
   int best_idx[kLassoMaxActive];
-  double rv[256];
-  int ri[256];
-  double sv;
-  int si;
+  // the four waves' parts of a reduction, a slot a use, so that one barrier
+  // orders it: the next write of a slot lies past other barriers
+  double rv[8][4];
+  int ri[8][4];
 };
 
-// Block arg-min of (value, index), ties to the smaller index; index -1 = none.
-__device__ inline void block_argmin(double v, int i, LarsShared& S, double& ov, int& oi) {
-  const int tid = threadIdx.x;
-  S.rv[tid] = v;
-  S.ri[tid] = i;
-  __syncthreads();
-  for (int off = 128; off > 0; off >>= 1) {
-    if (tid < off) {
-      const double a = S.rv[tid], b = S.rv[tid + off];
-      const int ia = S.ri[tid], ib = S.ri[tid + off];
-      if (ib >= 0 && (ia < 0 || b < a || (b == a && ib < ia))) {
-        S.rv[tid] = b;
-        S.ri[tid] = ib;
-      }
-    }
-    __syncthreads();
-  }
-  ov = S.rv[0];
-  oi = S.ri[0];
-  __syncthreads();
+// Reductions within a wave: the lanes of a row of 16 exchange by DPP (a few cycles
+// a step, where a shuffle goes through LDS: eight reductions of six shuffles were
+// half of a join), the four rows' results by readlane.
+template <int kCtrl>
+__device__ __forceinline__ int dpp(int v) {
+  return __builtin_amdgcn_update_dpp(0, v, kCtrl, 0xF, 0xF, true);
+}
+template <int kCtrl>
+__device__ __forceinline__ double dpp(double v) {
+  return __hiloint2double(dpp<kCtrl>(__double2hiint(v)), dpp<kCtrl>(__double2loint(v)));
+}
+constexpr int kXor1 = 0xB1, kXor2 = 0x4E, kHalfMirror = 0x141, kMirror = 0x140;
+template <class Op>
+__device__ __forceinline__ double wave_reduce(double v, Op op) {
+  v = op(v, dpp<kXor1>(v));
+  v = op(v, dpp<kXor2>(v));
+  v = op(v, dpp<kHalfMirror>(v));
+  v = op(v, dpp<kMirror>(v));
+  return op(op(lane_of(v, 0), lane_of(v, 16)), op(lane_of(v, 32), lane_of(v, 48)));
 }
 
-__device__ inline double block_sum(double v, LarsShared& S) {
-  const int tid = threadIdx.x;
-  S.rv[tid] = v;
-  __syncthreads();
-  for (int off = 128; off > 0; off >>= 1) {
-    if (tid < off) S.rv[tid] += S.rv[tid + off];
-    __syncthreads();
+// (v, i) against (b, ib): the smaller value, ties to the smaller index; index -1 =
+// none.
+__device__ __forceinline__ void take_less(double& v, int& i, double b, int ib) {
+  const bool less = ib >= 0 && (i < 0 || b < v || (b == v && ib < i));
+  v = less ? b : v;
+  i = less ? ib : i;
+}
+
+// The wave's part of a reduction, left for the workgroup in a slot.
+__device__ inline void put_argmin(double v, int i, LarsShared& S, int slot) {
+  take_less(v, i, dpp<kXor1>(v), dpp<kXor1>(i));
+  take_less(v, i, dpp<kXor2>(v), dpp<kXor2>(i));
+  take_less(v, i, dpp<kHalfMirror>(v), dpp<kHalfMirror>(i));
+  take_less(v, i, dpp<kMirror>(v), dpp<kMirror>(i));
+  double bv = lane_of(v, 0);
+  int bi = __builtin_amdgcn_readlane(i, 0);
+#pragma unroll
+  for (int l = 16; l < 64; l += 16)
+    take_less(bv, bi, lane_of(v, l), __builtin_amdgcn_readlane(i, l));
+  if ((threadIdx.x & 63) == 0) {
+    S.rv[slot][threadIdx.x >> 6] = bv;
+    S.ri[slot][threadIdx.x >> 6] = bi;
   }
-  const double r = S.rv[0];
-  __syncthreads();
-  return r;
+}
+__device__ inline void get_argmin(const LarsShared& S, int slot, double& v, int& i) {
+  v = S.rv[slot][0];
+  i = S.ri[slot][0];
+#pragma unroll
+  for (int w = 1; w < 4; ++w) take_less(v, i, S.rv[slot][w], S.ri[slot][w]);
+}
+__device__ inline void put_sum(double v, LarsShared& S, int slot) {
+  v = wave_reduce(v, [](double a, double b) { return a + b; });
+  if ((threadIdx.x & 63) == 0) S.rv[slot][threadIdx.x >> 6] = v;
+}
+__device__ inline double get_sum(const LarsShared& S, int slot) {
+  return (S.rv[slot][0] + S.rv[slot][1]) + (S.rv[slot][2] + S.rv[slot][3]);
+}
+__device__ inline void put_max(double v, LarsShared& S, int slot) {
+  v = wave_reduce(v, [](double a, double b) { return fmax(a, b); });
+  if ((threadIdx.x & 63) == 0) S.rv[slot][threadIdx.x >> 6] = v;
+}
+__device__ inline double get_max(const LarsShared& S, int slot) {
+  return fmax(fmax(S.rv[slot][0], S.rv[slot][1]), fmax(S.rv[slot][2], S.rv[slot][3]));
+}
+
+// sum_{q = c, c + 4, ..} row[q] x[q], q < n <= all, c = tid % 4 (all: the bound of
+// the other rows); four products' loads at a time, up to 64 read.
+__device__ __forceinline__ double row_dot(const double* row, const double* x, int n, int all) {
+  double acc = 0.0;
+  for (int q0 = threadIdx.x & 3; q0 < all; q0 += 16) {
+    double a[4], b[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      a[u] = row[q0 + 4 * u];
+      b[u] = x[q0 + 4 * u];
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+      if (q0 + 4 * u < n) acc = fma(a[u], b[u], acc);
+  }
+  return acc;
 }
 
 // One workgroup per target position t >= 1 (predictors: positions 0 .. t-1).
@@ -566,9 +620,17 @@ __device__ inline double block_sum(double v, LarsShared& S) {
 // at most max_active active; the breakpoint of least BIC
 // n log(2 pi s2) + RSS / s2 + log(n) df, s2 = n L_tt^2 / (n - t - 1); the
 // kept predictors refitted by least squares (standardized, then rescaled).
-// The path state (correlations, coefficients, directions, flags) lives in
-// st[t][4][d]; the inverse of G on the active set in LDS, updated by the
-// Schur complement on a join and the rank-1 downdate on a leave.
+// The inverse of G on the active set lies in LDS, updated by the Schur complement
+// on a join and the rank-1 downdate on a leave; so does the path state
+// (correlations, coefficients, directions, flags, weights) up to kLarsLds
+// predictors, past them in st[t][4][d].  Up to 256, thread k holds predictor k's
+// entries of the active rows of R in registers.  A path is a serial chain of up
+// to max_active joins and, at d = 200, the only one of its CU, so latency is the
+// bound: reductions within waves, one barrier each; products with M by four
+// threads a row, in the pass that updates it; six barriers a join.  d = 200, n =
+// 5000: 1287 us with trees of barriers, serial sums and the state in memory, 688
+// without, 644 with the rows in registers and M passed over once, 575 with DPP.
+template <bool kLds, bool kRegs>
 __global__ __launch_bounds__(256) void k_lars(const double* __restrict__ R,
                                               const double* __restrict__ L,
                                               const double* __restrict__ Y,
@@ -577,32 +639,44 @@ __global__ __launch_bounds__(256) void k_lars(const double* __restrict__ R,
                                               int cap, double* __restrict__ st,
                                               double* __restrict__ B, Ctrl* ctrl) {
   __shared__ LarsShared S;
+  __shared__ double state[kLds ? 6 * kLarsLds : 1];
   const int t = blockIdx.x + 1;
   const int p = t;
   const int tid = threadIdx.x;
   const double nn = (double)n;
-  double* corr = st + (int64_t)t * 4 * d;
-  double* beta = corr + d;
-  double* av = beta + d;
-  double* flag = av + d;
+  double* corr = kLds ? state : st + (int64_t)t * 4 * d;
+  double* beta = corr + (kLds ? kLarsLds : d);
+  double* av = beta + (kLds ? kLarsLds : d);
+  double* flag = av + (kLds ? kLarsLds : d);
+  double* weight = state + (kLds ? 4 * kLarsLds : 0);
+  double* with_t = state + (kLds ? 5 * kLarsLds : 0);  // n w_k R_kt
   const double Ltt = L[(int64_t)t * d + t];
   const double* Yt = Y + (int64_t)t * d;
   const double* Rt = R + (int64_t)t * d;  // row t = column t (symmetric)
-  auto wgt = [&](int k) { return fabs(Ltt * Yt[k]); };
-  auto cval = [&](int k) { return nn * wgt(k) * Rt[k]; };
-  double cmax = 0.0;
+  auto wgt = [&](int k) { return kLds ? weight[k] : fabs(Ltt * Yt[k]); };
+  auto cval = [&](int k) { return kLds ? with_t[k] : nn * wgt(k) * Rt[k]; };
+  double x[kRegs ? kLassoMaxActive : 1] = {};  // R[idx_r][tid]
+  // inactive predictor of largest |corr| (ties to the smaller position)
+  double jv = INFINITY;
+  int j = -1;
   for (int k = tid; k < p; k += 256) {
-    const double c = cval(k);
+    const double w = fabs(Ltt * Yt[k]), c = nn * w * Rt[k];
+    if (kLds) {
+      weight[k] = w;
+      with_t[k] = c;
+    }
     corr[k] = c;
     beta[k] = 0.0;
     flag[k] = 0.0;
-    cmax = fmax(cmax, fabs(c));
+    if (-fabs(c) < jv) {
+      jv = -fabs(c);
+      j = k;
+    }
   }
-  // max |c| through the arg-min of its negation
-  double mv;
-  int mi;
-  block_argmin(-cmax, tid, S, mv, mi);
-  const double tiny = 1e-14 * fmax(1.0, -mv);
+  put_argmin(jv, j, S, 0);
+  __syncthreads();
+  get_argmin(S, 0, jv, j);
+  const double tiny = 1e-14 * fmax(1.0, -jv);
   const double s2 = nn * Ltt * Ltt / (double)(n - p - 1);
   const double logterm = nn * log(2.0 * 3.14159265358979323846 * s2);
   const double lnn = log(nn);
@@ -612,91 +686,108 @@ __global__ __launch_bounds__(256) void k_lars(const double* __restrict__ R,
   bool joined = true;
   const int cap_a = cap < p ? cap : p;
   const int max_iter = 8 * kLassoMaxActive + 16;  // bound on the loop (never reached in practice)
+  const int r4 = tid >> 2, c4 = tid & 3;  // row of M and first column of this thread
   for (int iter = 0; iter < max_iter; ++iter) {
+    double cr = 0.0;  // correlation of active predictor tid
+    double ms = 0.0;  // M sgn, row r4
     if (joined) {
       if (na == p) break;
-      // inactive predictor of largest |corr| (ties to the smaller position)
-      double bv = INFINITY;
-      int bi = -1;
-      for (int k = tid; k < p; k += 256)
-        if (flag[k] == 0.0) {
-          const double v = -fabs(corr[k]);
-          if (v < bv) {
-            bv = v;
-            bi = k;
-          }
-        }
-      double jv;
-      int j;
-      block_argmin(bv, bi, S, jv, j);
       if (j < 0 || -jv <= tiny) break;
       // Schur complement: append j to the inverse of G on the active set
       const double wj = wgt(j);
       const double* Rj = R + (int64_t)j * d;
-      if (tid < na) S.g[tid] = nn * wgt(S.idx[tid]) * wj * Rj[S.idx[tid]];
-      __syncthreads();
-      if (tid < na) {
-        double acc = 0.0;
-        for (int q = 0; q < na; ++q) acc += S.M[tid][q] * S.g[q];
-        S.v[tid] = acc;
+      const double Rjj = Rj[j];
+      double xj = 0.0;
+      if (kRegs && tid < p) xj = Rj[tid];
+      if (tid <= na) {
+        const int k = tid < na ? S.idx[tid] : j;
+        if (tid < na) S.g[tid] = nn * wgt(k) * wj * Rj[k];
+        cr = corr[k];
+        S.sgn[tid] = cr >= 0.0 ? 1.0 : -1.0;
       }
       __syncthreads();
+      double mg = row_dot(S.M[r4], S.g, r4 < na ? na : 0, na);
+      mg += dpp<kXor1>(mg);
+      mg += dpp<kXor2>(mg);
+      const bool own = r4 < na && c4 == 0;
+      if (own) S.v[r4] = mg;
+      put_sum(own ? S.g[r4] * mg : 0.0, S, 1);
+      put_max(fabs(cr), S, 3);
       if (tid == 0) {
-        double gv = 0.0;
-        for (int q = 0; q < na; ++q) gv += S.g[q] * S.v[q];
-        S.sv = nn * wj * wj * Rj[j] - gv;
-      }
-      __syncthreads();
-      const double sch = S.sv;
-      if (!(sch > 1e-12 * nn * wj * wj)) break;  // the new predictor is (nearly) collinear
-      for (int e = tid; e < na * na; e += 256) {
-        const int r = e / na, q = e - r * na;
-        S.M[r][q] += S.v[r] * S.v[q] / sch;
-      }
-      if (tid < na) {
-        S.M[tid][na] = -S.v[tid] / sch;
-        S.M[na][tid] = -S.v[tid] / sch;
-      }
-      if (tid == 0) {
-        S.M[na][na] = 1.0 / sch;
         S.idx[na] = j;
+        S.row[na] = (int64_t)j * d;
         flag[j] = 1.0;
       }
       __syncthreads();
+      const double sch = nn * wj * wj * Rjj - get_sum(S, 1);
+      if (!(sch > 1e-12 * nn * wj * wj)) break;  // the new predictor is (nearly) collinear
+      // M and, in the same pass, its product with the signs
+      const double rs = 1.0 / sch, vr = r4 < na ? mg * rs : -rs;
+      for (int q0 = c4; q0 <= na; q0 += 16) {
+        double m[4], v[4], sg[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          m[u] = S.M[r4][q0 + 4 * u];
+          v[u] = S.v[q0 + 4 * u];
+          sg[u] = S.sgn[q0 + 4 * u];
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          const int q = q0 + 4 * u;  // row and column na: -v / sch, 1 / sch
+          const double e = fma(q < na ? v[u] : -1.0, vr, r4 < na && q < na ? m[u] : 0.0);
+          if (r4 <= na && q <= na) {
+            S.M[r4][q] = e;
+            ms = fma(e, sg[u], ms);
+          }
+        }
+      }
+      if (kRegs) {
+#pragma unroll
+        for (int r = 0; r < kLassoMaxActive; ++r) x[r] = r == na ? xj : x[r];
+      }
       ++na;
+    } else {
+      if (tid < na) {
+        cr = corr[S.idx[tid]];
+        S.sgn[tid] = cr >= 0.0 ? 1.0 : -1.0;
+      }
+      put_max(fabs(cr), S, 3);
+      __syncthreads();
+      ms = row_dot(S.M[r4], S.sgn, r4 < na ? na : 0, na);
     }
     // equiangular direction on the active set
-    if (tid < na) S.sgn[tid] = corr[S.idx[tid]] >= 0.0 ? 1.0 : -1.0;
+    ms += dpp<kXor1>(ms);
+    ms += dpp<kXor2>(ms);
+    const bool own = r4 < na && c4 == 0;
+    put_sum(own ? S.sgn[r4] * ms : 0.0, S, 2);
     __syncthreads();
-    if (tid < na) {
-      double acc = 0.0;
-      for (int q = 0; q < na; ++q) acc += S.M[tid][q] * S.sgn[q];
-      S.v[tid] = acc;
+    const double AA = 1.0 / sqrt(get_sum(S, 2));
+    const double C = get_max(S, 3);
+    if (c4 == 0) {
+      S.wv[r4] = r4 < na ? AA * ms : 0.0;
+      S.cf[r4] = r4 < na ? nn * wgt(S.idx[r4]) * (AA * ms) : 0.0;
     }
-    __syncthreads();
-    if (tid == 0) {
-      double sx = 0.0, cm = 0.0;
-      for (int q = 0; q < na; ++q) {
-        sx += S.sgn[q] * S.v[q];
-        cm = fmax(cm, fabs(corr[S.idx[q]]));
-      }
-      S.sv = sx;
-      S.rv[0] = cm;
-    }
-    __syncthreads();
-    const double AA = 1.0 / sqrt(S.sv);
-    const double C = S.rv[0];
-    __syncthreads();
-    if (tid < na) S.wv[tid] = AA * S.v[tid];
     __syncthreads();
     // a_k = sum_r G(k, idx_r) wv_r, and the first join along the direction
     double gj = INFINITY;
     int kj = -1;
     for (int k = tid; k < p; k += 256) {
       double acc = 0.0;
-      for (int r = 0; r < na; ++r) {
-        const int ir = S.idx[r];
-        acc += nn * wgt(ir) * R[(int64_t)ir * d + k] * S.wv[r];
+      if (kRegs) {
+#pragma unroll
+        for (int r0 = 0; r0 < kLassoMaxActive; r0 += 16)
+          if (r0 < na)
+#pragma unroll
+            for (int u = 0; u < 16; ++u) acc = fma(S.cf[r0 + u], x[r0 + u], acc);  // cf 0 past na
+      } else {
+        for (int r0 = 0; r0 < na; r0 += 16) {  // rows past the last: read again, times 0
+          double y[16];
+#pragma unroll
+          for (int u = 0; u < 16; ++u) y[u] = R[S.row[min(r0 + u, na - 1)] + k];
+#pragma unroll
+          for (int u = 0; u < 16; ++u)
+            if (r0 + u < na) acc = fma(S.cf[r0 + u], y[u], acc);
+        }
       }
       acc *= wgt(k);
       av[k] = acc;
@@ -719,15 +810,6 @@ __global__ __launch_bounds__(256) void k_lars(const double* __restrict__ R,
         }
       }
     }
-    double gjoin;
-    int jn;
-    block_argmin(gj, kj, S, gjoin, jn);
-    double gam = C / AA;
-    int event = 0;  // 0 end, 1 join, 2 leave
-    if (jn >= 0 && gjoin < gam) {
-      gam = gjoin;
-      event = 1;
-    }
     // first active coefficient to reach zero
     double gl = INFINITY;
     int rl = -1;
@@ -738,17 +820,46 @@ __global__ __launch_bounds__(256) void k_lars(const double* __restrict__ R,
         rl = tid;
       }
     }
-    double gleave;
-    int lr;
-    block_argmin(gl, rl, S, gleave, lr);
+    put_argmin(gj, kj, S, 4);
+    put_argmin(gl, rl, S, 5);
+    __syncthreads();
+    double gjoin, gleave;
+    int jn, lr;
+    get_argmin(S, 4, gjoin, jn);
+    get_argmin(S, 5, gleave, lr);
+    double gam = C / AA;
+    int event = 0;  // 0 end, 1 join, 2 leave
+    if (jn >= 0 && gjoin < gam) {
+      gam = gjoin;
+      event = 1;
+    }
     if (lr >= 0 && gleave < gam) {
       gam = gleave;
       event = 2;
     }
-    // step
-    if (tid < na) beta[S.idx[tid]] += gam * S.wv[tid];
-    for (int k = tid; k < p; k += 256) corr[k] -= gam * av[k];
+    // step; the criterion at the new breakpoint: RSS = n - beta'c - beta'corr
+    double part = 0.0;
+    if (tid < na) {
+      const int k = S.idx[tid];
+      const double bk = beta[k] + gam * S.wv[tid];
+      beta[k] = bk;
+      if (event != 2 || tid != lr) part = bk * (cval(k) + (cr - gam * av[k]));
+    }
+    jv = INFINITY;
+    j = -1;
+    for (int k = tid; k < p; k += 256) {
+      const double c = corr[k] - gam * av[k];
+      corr[k] = c;
+      if (flag[k] == 0.0 && -fabs(c) < jv) {
+        jv = -fabs(c);
+        j = k;
+      }
+    }
+    put_argmin(jv, j, S, 6);  // who joins next
+    put_sum(part, S, 7);
     __syncthreads();
+    get_argmin(S, 6, jv, j);
+    const double bsum = get_sum(S, 7);
     if (event == 2) {
       const int who = S.idx[lr];
       // rank-1 downdate of the inverse without row / column lr, then compaction
@@ -768,7 +879,14 @@ __global__ __launch_bounds__(256) void k_lars(const double* __restrict__ R,
         const int r2 = e / nb, q2 = e - r2 * nb;
         S.M[r2][q2] = keep[cnt];
       }
-      if (tid < nb) S.idx[tid] = idx_keep;
+      if (tid < nb) {
+        S.idx[tid] = idx_keep;
+        S.row[tid] = (int64_t)idx_keep * d;
+      }
+      if (kRegs) {
+#pragma unroll
+        for (int r = 0; r + 1 < kLassoMaxActive; ++r) x[r] = r >= lr ? x[r + 1] : x[r];
+      }
       if (tid == 0) {
         beta[who] = 0.0;
         flag[who] = 0.0;
@@ -776,24 +894,17 @@ __global__ __launch_bounds__(256) void k_lars(const double* __restrict__ R,
       __syncthreads();
       na = nb;
     }
-    // criterion at the new breakpoint: RSS = n - beta'c - beta'corr
-    double part = 0.0;
-    if (tid < na) {
-      const int k = S.idx[tid];
-      part = beta[k] * (cval(k) + corr[k]);
-    }
-    const double bsum = block_sum(part, S);
     const double crit = logterm + (nn - bsum) / s2 + lnn * (double)na;
     if (crit < best) {
       best = crit;
       best_na = na;
       if (tid < na) S.best_idx[tid] = S.idx[tid];
     }
-    __syncthreads();
     if (event == 0) break;
     if (event == 1 && na >= cap_a) break;
     joined = event == 1;
   }
+  __syncthreads();
   // refit the kept predictors by least squares on the standardized data
   const int ns = best_na;
   if (ns == 0) return;
@@ -801,43 +912,36 @@ __global__ __launch_bounds__(256) void k_lars(const double* __restrict__ R,
     const int r = e / ns, q = e - r * ns;
     S.M[r][q] = R[(int64_t)S.best_idx[r] * d + S.best_idx[q]];
   }
-  if (tid < ns) S.g[tid] = Rt[S.best_idx[tid]];
+  if (tid < ns) S.M[ns][tid] = Rt[S.best_idx[tid]];  // row ns ends as L^-1 of it
   __syncthreads();
   for (int j = 0; j < ns; ++j) {  // Cholesky in LDS, lower triangle
-    if (tid == 0) {
-      double a = S.M[j][j];
-      if (!(a > 1e-13)) {
-        set_status(ctrl, kStDegenerate);
-        a = 1.0;
-      }
-      S.M[j][j] = sqrt(a);
+    double a = S.M[j][j];
+    if (!(a > 1e-13)) {
+      if (tid == 0) set_status(ctrl, kStDegenerate);
+      a = 1.0;
     }
+    const double root = sqrt(a);
+    if (tid > j && tid <= ns) S.M[tid][j] /= root;
     __syncthreads();
-    if (tid > j && tid < ns) S.M[tid][j] /= S.M[j][j];
-    __syncthreads();
-    const int w = ns - j - 1;
+    if (tid == j) S.M[j][j] = root;
+    const int w = ns - j;  // rows j + 1 .. ns, columns up to ns - 1
     for (int e = tid; e < w * w; e += 256) {
       const int ii = e / w, kk = e - ii * w;
-      if (kk <= ii) S.M[j + 1 + ii][j + 1 + kk] -= S.M[j + 1 + ii][j] * S.M[j + 1 + kk][j];
+      if (kk <= ii && kk < w - 1)
+        S.M[j + 1 + ii][j + 1 + kk] -= S.M[j + 1 + ii][j] * S.M[j + 1 + kk][j];
     }
     __syncthreads();
   }
-  if (tid == 0) {
-    for (int i = 0; i < ns; ++i) {  // forward, then backward substitution
-      double acc = S.g[i];
-      for (int q = 0; q < i; ++q) acc -= S.M[i][q] * S.g[q];
-      S.g[i] = acc / S.M[i][i];
-    }
-    for (int i = ns - 1; i >= 0; --i) {
-      double acc = S.g[i];
-      for (int q = i + 1; q < ns; ++q) acc -= S.M[q][i] * S.g[q];
-      S.g[i] = acc / S.M[i][i];
-    }
+  if (tid >= 64) return;
+  double z = tid < ns ? S.M[ns][tid] : 0.0;  // backward substitution, lane i unknown i
+  for (int i = ns - 1; i >= 0; --i) {
+    const double x = __shfl(z, i) / S.M[i][i];
+    if (tid == i) z = x;
+    else if (tid < i) z -= S.M[i][tid] * x;
   }
-  __syncthreads();
   if (tid < ns) {
     const int k = S.best_idx[tid];
-    B[(int64_t)order[t] * d + order[k]] = S.g[tid] * sd[t] / sd[k];
+    B[(int64_t)order[t] * d + order[k]] = z * sd[t] / sd[k];
   }
 }
 
@@ -997,9 +1101,14 @@ hipError_t launch_adjacency_pruned(const PruneLayout& A, char* ws, const float* 
   hipLaunchKernelGGL(k_zero_f64, dim3(grid_for(dd)), dim3(256), 0, st, B, dd);
   if (d < 2) return hipGetLastError();
   const int cap = max_active < kLassoMaxActive ? max_active : kLassoMaxActive;
-  hipLaunchKernelGGL(k_lars, dim3((unsigned)(d - 1)), dim3(256), 0, st, (const double*)Rm,
-                     (const double*)Lm, (const double*)Ym, (const double*)at<double>(ws, A.sd),
-                     order, d, n, cap, at<double>(ws, A.st), B, ctrl);
+  // registers hold a predictor's row entries a thread; LDS the path state (d = 1024:
+  // 48 KB beside M's 34, two workgroups a CU as in memory's case by registers)
+  const auto lars = d - 1 <= 256        ? k_lars<true, true>
+                    : d - 1 <= kLarsLds ? k_lars<true, false>
+                                        : k_lars<false, false>;
+  hipLaunchKernelGGL(lars, dim3((unsigned)(d - 1)), dim3(256), 0, st, (const double*)Rm, (const double*)Lm, (const double*)Ym,
+                     (const double*)at<double>(ws, A.sd), order, d, n, cap,
+                     at<double>(ws, A.st), B, ctrl);
   return hipGetLastError();
 }
 
