@@ -392,6 +392,21 @@ int lingam_bootstrap_accumulate(const int32_t* order, const double* B, int64_t d
                                 double* coef_sum, void* stream);
 
 /*
+ * lingam_adjacency of `count` resamples of one size along their orders, all at
+ * once, and lingam_bootstrap_accumulate of each in turn.
+ *   rows    device int32[count * n]: the resamples' row indices into X.
+ *   orders  device int32[count * d]: their causal orders.
+ * The other arguments as in those calls.  Synchronizes.  The first resample
+ * that lingam_adjacency would refuse gives its code, and nothing is counted.
+ * count <= 65535.
+ */
+size_t lingam_bootstrap_regress_workspace_size(int64_t n, int64_t d, int32_t count);
+int lingam_bootstrap_regress(const float* X, int64_t n_rows, int64_t ldx, const int32_t* rows,
+                             int64_t n, int64_t d, const int32_t* orders, int32_t count,
+                             double threshold, int32_t* order_count, int32_t* edge_count,
+                             double* coef_sum, void* ws, size_t ws_bytes, void* stream);
+
+/*
  * Bootstrap probabilities from the counts of lingam_bootstrap_accumulate
  * after n_resamples resamples: order_prob[i d + j] = P(x_j precedes x_i),
  * edge_prob[i d + j] = P(|B[i d + j]| > threshold), coef_mean = coef_sum /

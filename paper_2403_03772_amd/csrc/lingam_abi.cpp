@@ -1131,6 +1131,19 @@ int varlingam_fit(const float* X, int64_t T, int64_t d, int64_t ldx, int32_t lag
       });
 }
 
+static int adjacency_status(int32_t s) {
+  if (s == LINGAM_E_INVALID)
+    return fail(LINGAM_E_INVALID,
+                "order is not a permutation of 0 .. d-1, or a row index is outside [0, n_rows)");
+  if (s != 0)
+    return fail(LINGAM_E_DEGENERATE,
+                "non-finite data or a covariance that is not positive definite");
+  return LINGAM_OK;
+}
+
+// Resamples of one lingam_bootstrap_regress: the grid's third dimension.
+constexpr int32_t kMaxRegress = 65535;
+
 size_t lingam_adjacency_workspace_size(int64_t n, int64_t d) {
   if (n < 2 || d < 1 || n > kMaxN || d > kMaxD) return 0;
   return lg::make_adj_layout(n, d).total;
@@ -1154,22 +1167,56 @@ int lingam_adjacency(const float* X, int64_t n_rows, int64_t ldx, const int32_t*
   hipStream_t st = (hipStream_t)stream;
   char* w = (char*)ws;
   int32_t s = 0;
-  // the order and the row map index device arrays: check them before
-  // anything reads through them
-  LG_TRY(lg::launch_adj_check(A, w, order, rows, n_rows, st), "adjacency check");
+  // the order and the row map index device arrays: they are checked before
+  // anything reads through them, on the device
+  LG_TRY(lg::launch_adj_check(A, w, order, rows, n_rows, 1, st), "adjacency check");
+  LG_TRY(lg::launch_adjacency(A, w, X, ldx, rows, order, B, 1, st), "adjacency launch");
   LG_TRY(hipMemcpyAsync(&s, w + A.ctrl, sizeof(int32_t), hipMemcpyDeviceToHost, st),
          "hipMemcpyAsync(status)");
   LG_TRY(hipStreamSynchronize(st), "hipStreamSynchronize");
-  if (s != 0)
+  return adjacency_status(s);
+}
+
+size_t lingam_bootstrap_regress_workspace_size(int64_t n, int64_t d, int32_t count) {
+  if (n < 2 || d < 1 || n > kMaxN || d > kMaxD || count < 1 || count > kMaxRegress) return 0;
+  return (lg::make_adj_layout(n, d).total + sizeof(double) * (size_t)(d * d)) * (size_t)count +
+         256;
+}
+
+int lingam_bootstrap_regress(const float* X, int64_t n_rows, int64_t ldx, const int32_t* rows,
+                             int64_t n, int64_t d, const int32_t* orders, int32_t count,
+                             double threshold, int32_t* order_count, int32_t* edge_count,
+                             double* coef_sum, void* ws, size_t ws_bytes, void* stream) {
+  g_err[0] = 0;
+  if (!X || !rows || !orders || !order_count || !edge_count)
     return fail(LINGAM_E_INVALID,
-                "order is not a permutation of 0 .. d-1, or a row index is outside [0, n_rows)");
-  LG_TRY(lg::launch_adjacency(A, w, X, ldx, rows, order, B, st), "adjacency launch");
-  LG_TRY(hipMemcpyAsync(&s, w + A.ctrl, sizeof(int32_t), hipMemcpyDeviceToHost, st),
+                "X, rows, orders, order_count and edge_count must be non-NULL");
+  if (n < 2 || d < 1 || ldx < d || n_rows < 1 || count < 1)
+    return fail(LINGAM_E_INVALID, "bad sizes n=%lld d=%lld ldx=%lld n_rows=%lld count=%d",
+                (long long)n, (long long)d, (long long)ldx, (long long)n_rows, count);
+  if (n > kMaxN || d > kMaxD || n_rows > kMaxN || count > kMaxRegress)
+    return fail(LINGAM_E_UNSUPPORTED, "size beyond supported range");
+  if (!(threshold >= 0.0)) return fail(LINGAM_E_INVALID, "threshold must be >= 0");
+  const size_t need = lingam_bootstrap_regress_workspace_size(n, d, count);
+  if (!ws || ws_bytes < need)
+    return fail(LINGAM_E_WORKSPACE, "workspace of %zu bytes needed (got %zu)", need,
+                ws ? ws_bytes : (size_t)0);
+  const lg::AdjLayout A = lg::make_adj_layout(n, d);
+  hipStream_t st = (hipStream_t)stream;
+  int32_t* first = (int32_t*)ws;
+  char* w = (char*)ws + 256;
+  double* B = (double*)(w + A.total * (size_t)count);
+  int32_t s[2] = {-1, 0};
+  LG_TRY(lg::launch_adj_check(A, w, orders, rows, n_rows, count, st), "adjacency check");
+  LG_TRY(lg::launch_adjacency(A, w, X, ldx, rows, orders, B, count, st), "adjacency launch");
+  LG_TRY(lg::launch_first_status(A, w, count, first, st), "adjacency status");
+  LG_TRY(hipMemcpyAsync(s, first, sizeof(s), hipMemcpyDeviceToHost, st),
          "hipMemcpyAsync(status)");
   LG_TRY(hipStreamSynchronize(st), "hipStreamSynchronize");
-  if (s != 0)
-    return fail(LINGAM_E_DEGENERATE,
-                "non-finite data or a covariance that is not positive definite");
+  if (s[0] >= 0) return adjacency_status(s[1]);
+  LG_TRY(lg::launch_boot_accumulate(orders, B, (int)d, count, threshold, order_count, edge_count,
+                                    coef_sum, st),
+         "bootstrap accumulate");
   return LINGAM_OK;
 }
 
@@ -1206,18 +1253,15 @@ int lingam_adjacency_pruned(const float* X, int64_t n_rows, int64_t ldx, const i
   V.ctrl = A.ctrl;
   V.mark = A.mark;
   int32_t s = 0;
-  LG_TRY(lg::launch_adj_check(V, w, order, rows, n_rows, st), "pruned adjacency check");
-  LG_TRY(hipMemcpyAsync(&s, w + A.ctrl, sizeof(int32_t), hipMemcpyDeviceToHost, st),
-         "hipMemcpyAsync(status)");
-  LG_TRY(hipStreamSynchronize(st), "hipStreamSynchronize");
-  if (s != 0)
-    return fail(LINGAM_E_INVALID,
-                "order is not a permutation of 0 .. d-1, or a row index is outside [0, n_rows)");
+  LG_TRY(lg::launch_adj_check(V, w, order, rows, n_rows, 1, st), "pruned adjacency check");
   LG_TRY(lg::launch_adjacency_pruned(A, w, X, ldx, rows, order, max_active, B, st),
          "pruned adjacency launch");
   LG_TRY(hipMemcpyAsync(&s, w + A.ctrl, sizeof(int32_t), hipMemcpyDeviceToHost, st),
          "hipMemcpyAsync(status)");
   LG_TRY(hipStreamSynchronize(st), "hipStreamSynchronize");
+  if (s == LINGAM_E_INVALID)
+    return fail(LINGAM_E_INVALID,
+                "order is not a permutation of 0 .. d-1, or a row index is outside [0, n_rows)");
   if (s != 0)
     return fail(LINGAM_E_DEGENERATE,
                 "non-finite data or a correlation matrix that is not positive definite");
@@ -1248,7 +1292,7 @@ int lingam_total_effects(const double* B, int64_t d, const int32_t* order, doubl
   V.ctrl = A.ctrl;
   V.mark = A.mark;
   int32_t s = 0;
-  LG_TRY(lg::launch_adj_check(V, w, order, nullptr, 0, st), "total effects check");
+  LG_TRY(lg::launch_adj_check(V, w, order, nullptr, 0, 1, st), "total effects check");
   LG_TRY(hipMemcpyAsync(&s, w + A.ctrl, sizeof(int32_t), hipMemcpyDeviceToHost, st),
          "hipMemcpyAsync(status)");
   LG_TRY(hipStreamSynchronize(st), "hipStreamSynchronize");
@@ -1266,7 +1310,7 @@ int lingam_bootstrap_accumulate(const int32_t* order, const double* B, int64_t d
   if (d < 1) return fail(LINGAM_E_INVALID, "need d >= 1 (got %lld)", (long long)d);
   if (d > kMaxD) return fail(LINGAM_E_UNSUPPORTED, "d <= %lld supported", (long long)kMaxD);
   if (!(threshold >= 0.0)) return fail(LINGAM_E_INVALID, "threshold must be >= 0");
-  LG_TRY(lg::launch_boot_accumulate(order, B, (int)d, threshold, order_count, edge_count,
+  LG_TRY(lg::launch_boot_accumulate(order, B, (int)d, 1, threshold, order_count, edge_count,
                                     coef_sum, (hipStream_t)stream),
          "bootstrap accumulate");
   return LINGAM_OK;

@@ -35,6 +35,16 @@ __host__ __device__ inline T* at(char* ws, size_t off) {
 
 __device__ inline void set_status(Ctrl* c, int32_t s) { atomicCAS(&c->status, 0, s); }
 
+// The order or row map of a call was refused by its check (nothing may be read or
+// written through it); ctrl NULL: not checked.
+__device__ inline bool refused(const Ctrl* ctrl) { return ctrl && ctrl->status == kStInvalid; }
+
+// Job blockIdx.z's copy of a region, the jobs' workspaces `bytes` apart.
+template <class T>
+__device__ inline T* job_at(T* p, size_t bytes) {
+  return (T*)((char*)p + blockIdx.z * bytes);
+}
+
 __device__ inline double entropy_from_moments(double e_lc, double e_g) {
   const double a = e_lc - kGamma;
   return kHnu - kK1 * a * a - kK2 * e_g * e_g;

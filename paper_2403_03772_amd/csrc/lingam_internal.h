@@ -673,33 +673,40 @@ struct AdjLayout {
 
 // split: with the region of partial tiles (the last one), if there are any.
 AdjLayout make_adj_layout(int64_t n, int64_t d, bool split = true);
+// `count` jobs at once: their workspaces A.total, row maps n, orders d and results
+// d * d entries apart.
 // Zero the status; status kInvalid unless `order` is a permutation and every
 // rows[s] (s < n, if rows is given) lies in [0, n_rows).
 hipError_t launch_adj_check(const AdjLayout& A, char* ws, const int32_t* order,
-                            const int32_t* rows, int64_t n_rows, hipStream_t st);
-// B (d x d, row-major) after a passed check; sample s is row s of X, or row
-// rows[s]; status kDegenerate on non-finite data or a covariance that is not
-// positive definite.
+                            const int32_t* rows, int64_t n_rows, int count, hipStream_t st);
+// B (d x d, row-major) after the check (nothing if it failed); sample s is row s
+// of X, or row rows[s]; status kDegenerate on non-finite data or a covariance
+// that is not positive definite.
 hipError_t launch_adjacency(const AdjLayout& A, char* ws, const float* X, int64_t ldx,
-                            const int32_t* rows, const int32_t* order, double* B,
+                            const int32_t* rows, const int32_t* order, double* B, int count,
                             hipStream_t st);
-// One resample's bootstrap counts (see lingam_bootstrap_accumulate).
-hipError_t launch_boot_accumulate(const int32_t* order, const double* B, int d, double thr,
-                                  int32_t* order_count, int32_t* edge_count, double* coef_sum,
-                                  hipStream_t st);
+// out[0] = the first job whose status is not 0, or -1; out[1] = that status.
+hipError_t launch_first_status(const AdjLayout& A, const char* ws, int count, int32_t* out,
+                               hipStream_t st);
+// Bootstrap counts of `count` resamples (see lingam_bootstrap_accumulate).
+hipError_t launch_boot_accumulate(const int32_t* order, const double* B, int d, int count,
+                                  double thr, int32_t* order_count, int32_t* edge_count,
+                                  double* coef_sum, hipStream_t st);
 // The counts divided by the number of resamples (see lingam_bootstrap_finalize).
 hipError_t launch_boot_finalize(const int32_t* order_count, const int32_t* edge_count,
                                 const double* coef_sum, int d, int32_t n_resamples,
                                 double* order_prob, double* edge_prob, double* coef_mean,
                                 hipStream_t st);
 
-// Dense FP64 pieces shared by the adjacency and VarLiNGAM.
+// Dense FP64 pieces shared by the adjacency and VarLiNGAM; of `count` jobs, every
+// workspace region (A, X, tol, ctrl, S, mu, part, Y) wz bytes apart.
 // In-place Cholesky of the leading p x p block of A (lower triangle holds L;
 // the upper triangle and columns >= p are left alone), and X (p x p, ld ldx) =
 // L^-1 below and on the diagonal (its blocks above the diagonal are scratch).
 // Status kDegenerate for a pivot <= 1e-13 max |A_jj| or a non-finite one.
 hipError_t launch_cholesky_inverse(double* A, int64_t lda, int p, double* X, int64_t ldx,
-                                   double* tol, Ctrl* ctrl, hipStream_t st);
+                                   double* tol, Ctrl* ctrl, int count, size_t wz,
+                                   hipStream_t st);
 // X alone, for a given unit lower-triangular L.
 hipError_t launch_unit_inverse(const double* L, int64_t ldl, int p, double* X, int64_t ldx,
                                hipStream_t st);
@@ -709,16 +716,19 @@ hipError_t launch_trmm(int M, int N, const double* A, int64_t lda, bool trans, c
                        int64_t ldb, double* C, int64_t ldc, hipStream_t st);
 // B (p x p, ld p) = least-squares coefficients of every variable on its order
 // predecessors from the order-permuted covariance A (ld p; factored in place);
-// B[order[i]][order[k]] for k < i, zero elsewhere.  Y: p x p scratch (L^-1).
+// B[order[i]][order[k]] for k < i, zero elsewhere (untouched if the order was
+// refused).  Y: p x p scratch (L^-1).
 hipError_t launch_tri_adjacency(double* A, int p, const int32_t* order, double* B, double* Y,
-                                double* tol, Ctrl* ctrl, hipStream_t st);
+                                double* tol, Ctrl* ctrl, int count, size_t wz, hipStream_t st);
 // S[a][b] = sig[o_a] sig[o_b] rho[o_a][o_b].
 hipError_t launch_perm_scale(const double* rho, int64_t ldr, const double* sig,
                              const int32_t* order, int d, double* S, hipStream_t st);
 // mu = row means of Xd[0..d-1][0..n-1]; S = centred Gram permuted into `order`;
-// nsplit > 1: part holds that many partial tile sets.
+// nsplit > 1: part holds that many partial tile sets.  Nothing if ctrl says that
+// the order was refused.
 hipError_t launch_cov_perm(const double* Xd, int64_t ldx, int n, int d, const int32_t* order,
-                           double* mu, double* S, int nsplit, double* part, hipStream_t st);
+                           double* mu, double* S, int nsplit, double* part, const Ctrl* ctrl,
+                           int count, size_t wz, hipStream_t st);
 // theta[t] = (I - B0) M[t], t < lags (d x d each, row-major).
 hipError_t launch_lagged_effects(const double* M, const double* B0, int d, int lags,
                                  double* theta, hipStream_t st);

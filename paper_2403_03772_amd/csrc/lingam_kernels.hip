@@ -825,13 +825,20 @@ __global__ void k_gather_status(const JobDev* __restrict__ jobs, int njobs, int3
 // X row-major [n x ldx] -> Zd[v][s] (FP64) for the VAR series: zero padding
 // for s >= n and row d.
 // Sample s of the output is row s of X, or row rows[s] when a row map is given
-// (indices are checked before the launch).
+// (nothing if its check refused them).  Job blockIdx.z: the workspaces wz bytes,
+// the row maps n entries apart.
 __global__ __launch_bounds__(256) void k_transpose_f64(const float* __restrict__ X, int64_t ldx,
                                                        const int32_t* __restrict__ rows,
                                                        int n, int d, int n_pad,
                                                        double* __restrict__ Zd, int64_t ldz,
-                                                       Ctrl* ctrl) {
+                                                       Ctrl* ctrl, size_t wz) {
   __shared__ float tile[64][65];
+  Zd = job_at(Zd, wz);
+  ctrl = job_at(ctrl, wz);
+  if (rows) {
+    if (refused(ctrl)) return;
+    rows += (int64_t)blockIdx.z * n;
+  }
   const int s0 = blockIdx.x * 64, v0 = blockIdx.y * 64;
   const int tx = threadIdx.x & 63, ty = threadIdx.x >> 6;
   bool bad = false;
@@ -1025,12 +1032,22 @@ __global__ __launch_bounds__(256) void k_rr_apply(float* __restrict__ X, int64_t
 
 __global__ void k_zero_i32(int32_t* p) { p[0] = 0; }
 
-// Status kInvalid unless order is a permutation of 0 .. d-1 (mark starts at 0)
-// and every row index rows[0 .. n-1] (if given) lies in [0, n_rows).
+// Clears the status; kInvalid unless order is a permutation of 0 .. d-1 (mark is
+// scratch) and every row index rows[0 .. n-1] (if given) lies in [0, n_rows).  One
+// workgroup a job; the kernels that read through either look at the status, so
+// the host need not wait for it before it launches them.
 __global__ __launch_bounds__(1024) void k_check_perm(const int32_t* __restrict__ order, int d,
                                                      const int32_t* __restrict__ rows, int64_t n,
                                                      int64_t n_rows, int32_t* __restrict__ mark,
-                                                     Ctrl* ctrl) {
+                                                     Ctrl* ctrl, size_t wz) {
+  order += (int64_t)blockIdx.z * d;
+  if (rows) rows += (int64_t)blockIdx.z * n;
+  mark = job_at(mark, wz);
+  ctrl = job_at(ctrl, wz);
+  for (int i = threadIdx.x; i < d; i += 1024) mark[i] = 0;
+  if (threadIdx.x == 0) ctrl->status = 0;
+  __threadfence();
+  __syncthreads();
   for (int i = threadIdx.x; i < d; i += 1024) {
     const int v = order[i];
     if (v < 0 || v >= d || atomicAdd(&mark[v], 1) != 0) set_status(ctrl, kStInvalid);
@@ -1040,10 +1057,26 @@ __global__ __launch_bounds__(1024) void k_check_perm(const int32_t* __restrict__
       if (rows[s] < 0 || rows[s] >= n_rows) set_status(ctrl, kStInvalid);
 }
 
-// Bootstrap counts of one resample: order_count[i][j] += 1 when x_j precedes
-// x_i; edge_count[i][j] += 1 when |B[i][j]| > thr; coef_sum += B (if given).
+// out[0] = the first job of `count` whose status is not 0, or -1; out[1] = it.
+__global__ void k_first_status(const Ctrl* __restrict__ ctrl, size_t wz, int count,
+                               int32_t* __restrict__ out) {
+  int32_t job = -1, status = 0;
+  for (int z = 0; z < count && job < 0; ++z) {
+    const Ctrl* c = (const Ctrl*)((const char*)ctrl + z * wz);
+    if (c->status != 0) {
+      job = z;
+      status = c->status;
+    }
+  }
+  out[0] = job;
+  out[1] = status;
+}
+
+// Bootstrap counts of `count` resamples: order_count[i][j] += 1 when x_j precedes
+// x_i; edge_count[i][j] += 1 when |B[i][j]| > thr; coef_sum += B (if given), in
+// the resamples' order.
 __global__ void k_boot_accumulate(const int32_t* __restrict__ order,
-                                  const double* __restrict__ B, int d, double thr,
+                                  const double* __restrict__ B, int d, int count, double thr,
                                   int32_t* __restrict__ order_count,
                                   int32_t* __restrict__ edge_count,
                                   double* __restrict__ coef_sum) {
@@ -1051,14 +1084,20 @@ __global__ void k_boot_accumulate(const int32_t* __restrict__ order,
   for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < total;
        e += (int64_t)gridDim.x * blockDim.x) {
     const int a = (int)(e / d), b = (int)(e - (int64_t)a * d);  // positions a > b
-    if (a > b) {
-      const int oa = order[a], ob = order[b];
-      if ((unsigned)oa < (unsigned)d && (unsigned)ob < (unsigned)d)  // never write outside
-        order_count[(int64_t)oa * d + ob] += 1;
+    int edges = 0;
+    double sum = coef_sum ? coef_sum[e] : 0.0;
+    for (int z = 0; z < count; ++z) {
+      if (a > b) {
+        const int oa = order[(int64_t)z * d + a], ob = order[(int64_t)z * d + b];
+        if ((unsigned)oa < (unsigned)d && (unsigned)ob < (unsigned)d)  // never write outside
+          atomicAdd(&order_count[(int64_t)oa * d + ob], 1);
+      }
+      const double w = B[z * total + e];
+      edges += fabs(w) > thr ? 1 : 0;
+      sum += w;
     }
-    const double w = B[e];
-    if (fabs(w) > thr) edge_count[e] += 1;
-    if (coef_sum) coef_sum[e] += w;
+    edge_count[e] += edges;
+    if (coef_sum) coef_sum[e] = sum;
   }
 }
 
@@ -1075,12 +1114,6 @@ __global__ void k_boot_finalize(const int32_t* __restrict__ order_count,
     edge_prob[e] = (double)edge_count[e] * inv;
     if (coef_sum) coef_mean[e] = coef_sum[e] * inv;
   }
-}
-
-__global__ void k_fill_i32(int32_t* __restrict__ p, int64_t n, int32_t v) {
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
-       i += (int64_t)gridDim.x * blockDim.x)
-    p[i] = v;
 }
 
 }  // namespace
@@ -1414,7 +1447,7 @@ hipError_t launch_var_fit(const VarLayout& V, char* ws, char* job, float* G, con
   dim3 g1((unsigned)(V.ldx / 64), (unsigned)((V.d + 1 + 63) / 64));
   hipLaunchKernelGGL(k_transpose_f64, g1, dim3(256), 0, st, X, ldx_in, (const int32_t*)nullptr,
                      (int)V.T, (int)V.d,
-                     (int)V.ldx, Xd, V.ldx, ctrl);
+                     (int)V.ldx, Xd, V.ldx, ctrl, (size_t)0);
   hipLaunchKernelGGL(k_fill, dim3((unsigned)((V.N + 255) / 256)), dim3(256), 0, st, ones,
                      (int)V.N, 1.0);
   const int nb = (int)((V.q + 31) / 32);
@@ -1423,7 +1456,7 @@ hipError_t launch_var_fit(const VarLayout& V, char* ws, char* job, float* G, con
   // coefficients (L L^T)^-1 C = X^T (X C), X = L^-1, C = W[0:p, p:q]
   double* Xi = at<double>(ws, V.linv);
   double* T = at<double>(ws, V.tmp);
-  LG_HIP(launch_cholesky_inverse(W, V.q, (int)V.p, Xi, V.p, at<double>(ws, V.tol), ctrl, st));
+  LG_HIP(launch_cholesky_inverse(W, V.q, (int)V.p, Xi, V.p, at<double>(ws, V.tol), ctrl, 1, 0, st));
   LG_HIP(launch_trmm((int)V.p, (int)V.d, Xi, V.p, false, W + V.p, V.q, T, V.d, st));
   LG_HIP(launch_trmm((int)V.p, (int)V.d, Xi, V.p, true, T, V.d, W + V.p, V.q, st));
   dim3 g2((unsigned)V.N, (unsigned)((V.d + 63) / 64));
@@ -1449,7 +1482,7 @@ hipError_t launch_b0(const VarLayout& V, char* ws, char* job, const int32_t* ord
   LG_HIP(launch_perm_scale(at<double>(ws, V.rho0), V.d, at<double>(job, V.ord.sig), order,
                            (int)V.d, S, st));
   return launch_tri_adjacency(S, (int)V.d, order, B0, at<double>(ws, V.y), at<double>(ws, V.tol),
-                              at<Ctrl>(job, V.ord.ctrl), st);
+                              at<Ctrl>(job, V.ord.ctrl), 1, 0, st);
 }
 
 // ---------------------------------------------------------------------------
@@ -1483,38 +1516,41 @@ AdjLayout make_adj_layout(int64_t n, int64_t d, bool split) {
 }
 
 hipError_t launch_adj_check(const AdjLayout& A, char* ws, const int32_t* order,
-                            const int32_t* rows, int64_t n_rows, hipStream_t st) {
-  Ctrl* ctrl = at<Ctrl>(ws, A.ctrl);
-  hipLaunchKernelGGL(k_zero_i32, dim3(1), dim3(1), 0, st, &ctrl->status);
-  const int64_t g = (A.d + 255) / 256;
-  hipLaunchKernelGGL(k_fill_i32, dim3((unsigned)(g < 1024 ? g : 1024)), dim3(256), 0, st,
-                     at<int32_t>(ws, A.mark), A.d, 0);
-  hipLaunchKernelGGL(k_check_perm, dim3(1), dim3(1024), 0, st, order, (int)A.d, rows, A.n,
-                     n_rows, at<int32_t>(ws, A.mark), ctrl);
+                            const int32_t* rows, int64_t n_rows, int count, hipStream_t st) {
+  hipLaunchKernelGGL(k_check_perm, dim3(1, 1, (unsigned)count), dim3(1024), 0, st, order,
+                     (int)A.d, rows, A.n, n_rows, at<int32_t>(ws, A.mark), at<Ctrl>(ws, A.ctrl),
+                     A.total);
   return hipGetLastError();
 }
 
 hipError_t launch_adjacency(const AdjLayout& A, char* ws, const float* X, int64_t ldx,
-                            const int32_t* rows, const int32_t* order, double* B,
+                            const int32_t* rows, const int32_t* order, double* B, int count,
                             hipStream_t st) {
   Ctrl* ctrl = at<Ctrl>(ws, A.ctrl);
   double* Xd = at<double>(ws, A.xd);
   double* S = at<double>(ws, A.s);
-  dim3 g1((unsigned)(A.ldx / 64), (unsigned)((A.d + 1 + 63) / 64));
+  dim3 g1((unsigned)(A.ldx / 64), (unsigned)((A.d + 1 + 63) / 64), (unsigned)count);
   hipLaunchKernelGGL(k_transpose_f64, g1, dim3(256), 0, st, X, ldx, rows, (int)A.n, (int)A.d,
-                     (int)A.ldx, Xd, A.ldx, ctrl);
+                     (int)A.ldx, Xd, A.ldx, ctrl, A.total);
   LG_HIP(launch_cov_perm(Xd, A.ldx, (int)A.n, (int)A.d, order, at<double>(ws, A.mu), S, A.nsplit,
-                         at<double>(ws, A.part), st));
+                         at<double>(ws, A.part), ctrl, count, A.total, st));
   return launch_tri_adjacency(S, (int)A.d, order, B, at<double>(ws, A.y), at<double>(ws, A.tol),
-                              ctrl, st);
+                              ctrl, count, A.total, st);
 }
 
-hipError_t launch_boot_accumulate(const int32_t* order, const double* B, int d, double thr,
-                                  int32_t* order_count, int32_t* edge_count, double* coef_sum,
-                                  hipStream_t st) {
+hipError_t launch_first_status(const AdjLayout& A, const char* ws, int count, int32_t* out,
+                               hipStream_t st) {
+  hipLaunchKernelGGL(k_first_status, dim3(1), dim3(1), 0, st,
+                     reinterpret_cast<const Ctrl*>(ws + A.ctrl), A.total, count, out);
+  return hipGetLastError();
+}
+
+hipError_t launch_boot_accumulate(const int32_t* order, const double* B, int d, int count,
+                                  double thr, int32_t* order_count, int32_t* edge_count,
+                                  double* coef_sum, hipStream_t st) {
   const int64_t g = ((int64_t)d * d + 255) / 256;
   hipLaunchKernelGGL(k_boot_accumulate, dim3((unsigned)(g < 4096 ? g : 4096)), dim3(256), 0, st,
-                     order, B, d, thr, order_count, edge_count, coef_sum);
+                     order, B, d, count, thr, order_count, edge_count, coef_sum);
   return hipGetLastError();
 }
 

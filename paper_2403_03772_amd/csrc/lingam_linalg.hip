@@ -111,9 +111,14 @@ __device__ inline double* raw_panel(double* X, int64_t ldx, int k0) {
 // (the others).
 __global__ __launch_bounds__(256) void k_chol_first(double* __restrict__ A, int64_t lda, int p,
                                                     double* __restrict__ X, int64_t ldx,
-                                                    double* __restrict__ tol, Ctrl* ctrl) {
+                                                    double* __restrict__ tol, Ctrl* ctrl,
+                                                    size_t wz) {
   __shared__ Block T, D;
   __shared__ double sh[256];
+  A = job_at(A, wz);
+  X = job_at(X, wz);
+  tol = job_at(tol, wz);
+  ctrl = job_at(ctrl, wz);
   const int tid = threadIdx.x, kb = p < kNb ? p : kNb, I0 = blockIdx.x * kNb;
   for (int e = tid; e < kNb * kNb; e += 256) {
     const int i = e >> 5, j = e & 31;
@@ -156,9 +161,13 @@ __global__ __launch_bounds__(256) void k_chol_first(double* __restrict__ A, int6
 __global__ __launch_bounds__(256) void k_chol_step(double* __restrict__ A, int64_t lda, int p,
                                                    int k0, int nt, double* __restrict__ X,
                                                    int64_t ldx, const double* __restrict__ tol,
-                                                   Ctrl* ctrl) {
+                                                   Ctrl* ctrl, size_t wz) {
   __shared__ __align__(16) double PI[32][32], PJ[32][32], Li[32][32];
   __shared__ Block F, D;
+  A = job_at(A, wz);
+  X = job_at(X, wz);
+  tol = job_at(tol, wz);
+  ctrl = job_at(ctrl, wz);
   int bj, bi;
   decode_tile(blockIdx.x, nt, bj, bi);  // bj <= bi: tile (I, J) = (bi, bj) is lower
   const int lv = threadIdx.x >> 3, ls = (threadIdx.x & 7) * 4;
@@ -257,8 +266,10 @@ __global__ __launch_bounds__(64) void k_trinv_diag(const double* __restrict__ L,
 // last pair's second half cut at p.
 __global__ __launch_bounds__(256) void k_trinv_prod(const double* __restrict__ L, int64_t ldl,
                                                     int p, int b, double* __restrict__ X,
-                                                    int64_t ldx) {
+                                                    int64_t ldx, size_t wz) {
   __shared__ Tile64 T;
+  L = job_at(L, wz);
+  X = job_at(X, wz);
   const int nt = b / kNb, pair = blockIdx.x / (nt * nt), e = blockIdx.x - pair * nt * nt;
   const int I = e / nt, J = e - I * nt;
   const int o1 = pair * 2 * b, o2 = o1 + b;  // first rows of the two halves
@@ -285,8 +296,9 @@ __global__ __launch_bounds__(256) void k_trinv_prod(const double* __restrict__ L
 }
 
 __global__ __launch_bounds__(256) void k_trinv_merge(int p, int b, double* __restrict__ X,
-                                                     int64_t ldx) {
+                                                     int64_t ldx, size_t wz) {
   __shared__ Tile64 T;
+  X = job_at(X, wz);
   const int nt = b / kNb, pair = blockIdx.x / (nt * nt), e = blockIdx.x - pair * nt * nt;
   const int I = e / nt, J = e - I * nt;
   const int o1 = pair * 2 * b, o2 = o1 + b;
@@ -320,8 +332,14 @@ __global__ __launch_bounds__(256) void k_trinv_merge(int p, int b, double* __res
 // written once: order is a permutation).
 __global__ void k_adj_scatter(const double* __restrict__ L, int64_t ldl,
                               const double* __restrict__ X, int64_t ldx, int p,
-                              const int32_t* __restrict__ order, double* __restrict__ B) {
+                              const int32_t* __restrict__ order, double* __restrict__ B,
+                              const Ctrl* ctrl, size_t wz) {
   const int64_t total = (int64_t)p * p;
+  if (refused(job_at(ctrl, wz))) return;
+  L = job_at(L, wz);
+  X = job_at(X, wz);
+  order += (int64_t)blockIdx.z * p;
+  B += blockIdx.z * total;
   for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < total;
        e += (int64_t)gridDim.x * blockDim.x) {
     const int i = (int)(e / p), k = (int)(e - (int64_t)i * p);
@@ -380,8 +398,10 @@ __global__ void k_perm_scale(const double* __restrict__ rho, int64_t ldr,
 
 // mu[v] = mean of row v of Xd over its first n entries (one workgroup per row).
 __global__ __launch_bounds__(256) void k_row_mean(const double* __restrict__ Xd, int64_t ldx, int n,
-                                                  double* __restrict__ mu) {
+                                                  double* __restrict__ mu, size_t wz) {
   __shared__ double sh[256];
+  Xd = job_at(Xd, wz);
+  mu = job_at(mu, wz);
   const double* x = Xd + (int64_t)blockIdx.x * ldx;
   double s = 0.0;
   for (int k = threadIdx.x; k < n; k += 256) s += x[k];
@@ -408,8 +428,15 @@ __global__ __launch_bounds__(256) void k_cov_perm(const double* __restrict__ Xd,
                                                   const int32_t* __restrict__ order,
                                                   const double* __restrict__ mu, int nb,
                                                   double* __restrict__ S,
-                                                  double* __restrict__ part) {
+                                                  double* __restrict__ part, const Ctrl* ctrl,
+                                                  size_t wz) {
   __shared__ Tile64 T;
+  if (refused(job_at(ctrl, wz))) return;
+  Xd = job_at(Xd, wz);
+  order += (int64_t)blockIdx.z * d;
+  mu = job_at(mu, wz);
+  S = job_at(S, wz);
+  part = job_at(part, wz);
   int bi, bj;
   decode_tile(blockIdx.x, nb, bi, bj);
   const int lv = threadIdx.x >> 3, ls = (threadIdx.x & 7) * 4;
@@ -428,7 +455,10 @@ __global__ __launch_bounds__(256) void k_cov_perm(const double* __restrict__ Xd,
 }
 
 __global__ __launch_bounds__(256) void k_cov_sum(const double* __restrict__ part, int nsplit,
-                                                 int d, int nb, double* __restrict__ S) {
+                                                 int d, int nb, double* __restrict__ S,
+                                                 size_t wz) {
+  part = job_at(part, wz);
+  S = job_at(S, wz);
   int bi, bj;
   decode_tile(blockIdx.x, nb, bi, bj);
   cov_store(S, d, bi, bj, tile_sum(part, nsplit, gridDim.x, blockIdx.x));
@@ -465,6 +495,7 @@ __global__ __launch_bounds__(256) void k_gather_f64(const float* __restrict__ X,
                                                     int d, int n_pad, double* __restrict__ Xd,
                                                     int64_t ldz, Ctrl* ctrl) {
   __shared__ float tile[64][65];
+  if (refused(ctrl)) return;
   const int s0 = blockIdx.x * 64, v0 = blockIdx.y * 64;
   const int tx = threadIdx.x & 63, ty = threadIdx.x >> 6;
   bool bad = false;
@@ -486,14 +517,17 @@ __global__ __launch_bounds__(256) void k_gather_f64(const float* __restrict__ X,
 }
 
 // sd[a] = sqrt(S[a][a] / n); R = S scaled to unit diagonal; L = R (to be
-// factored).  A zero variance sets the status.
+// factored), B = 0.  A zero variance sets the status.
 __global__ void k_corr(const double* __restrict__ S, int d, int n, double* __restrict__ sd,
-                       double* __restrict__ R, double* __restrict__ L, Ctrl* ctrl) {
+                       double* __restrict__ R, double* __restrict__ L, double* __restrict__ B,
+                       Ctrl* ctrl) {
   const int64_t total = (int64_t)d * d;
+  if (refused(ctrl)) return;
   for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < total;
        e += (int64_t)gridDim.x * blockDim.x) {
     const int a = (int)(e / d), b = (int)(e - (int64_t)a * d);
     const double saa = S[(int64_t)a * d + a], sbb = S[(int64_t)b * d + b];
+    B[e] = 0.0;
     if (!(saa > 0.0) || !(sbb > 0.0)) {
       set_status(ctrl, kStDegenerate);
       R[e] = L[e] = (a == b) ? 1.0 : 0.0;
@@ -503,12 +537,6 @@ __global__ void k_corr(const double* __restrict__ S, int d, int n, double* __res
     }
     if (a == b) sd[a] = sqrt(fmax(saa, 0.0) / (double)n);
   }
-}
-
-__global__ void k_zero_f64(double* __restrict__ p, int64_t n) {
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
-       i += (int64_t)gridDim.x * blockDim.x)
-    p[i] = 0.0;
 }
 
 // Path state of a target of at most this many predictors in LDS.
@@ -640,6 +668,7 @@ __global__ __launch_bounds__(256) void k_lars(const double* __restrict__ R,
                                               double* __restrict__ B, Ctrl* ctrl) {
   __shared__ LarsShared S;
   __shared__ double state[kLds ? 6 * kLarsLds : 1];
+  if (refused(ctrl)) return;
   const int t = blockIdx.x + 1;
   const int p = t;
   const int tid = threadIdx.x;
@@ -977,40 +1006,43 @@ unsigned grid_for(int64_t n) {
 
 // X's blocks below the diagonal from its diagonal blocks, level by level.
 static hipError_t tri_levels(const double* L, int64_t ldl, int p, double* X, int64_t ldx,
-                             hipStream_t st) {
+                             int count, size_t wz, hipStream_t st) {
   for (int b = kNb; b < p; b *= 2) {
     const int nt = b / kNb, pairs = (p - b + 2 * b - 1) / (2 * b);
-    const dim3 g((unsigned)(pairs * nt * nt));
-    hipLaunchKernelGGL(k_trinv_prod, g, dim3(256), 0, st, L, ldl, p, b, X, ldx);
-    hipLaunchKernelGGL(k_trinv_merge, g, dim3(256), 0, st, p, b, X, ldx);
+    const dim3 g((unsigned)(pairs * nt * nt), 1, (unsigned)count);
+    hipLaunchKernelGGL(k_trinv_prod, g, dim3(256), 0, st, L, ldl, p, b, X, ldx, wz);
+    hipLaunchKernelGGL(k_trinv_merge, g, dim3(256), 0, st, p, b, X, ldx, wz);
   }
   return hipGetLastError();
 }
 
 hipError_t launch_cholesky_inverse(double* A, int64_t lda, int p, double* X, int64_t ldx,
-                                   double* tol, Ctrl* ctrl, hipStream_t st) {
-  hipLaunchKernelGGL(k_chol_first, dim3((unsigned)((p + kNb - 1) / kNb)), dim3(256), 0, st, A,
-                     lda, p, X, ldx, tol, ctrl);
+                                   double* tol, Ctrl* ctrl, int count, size_t wz,
+                                   hipStream_t st) {
+  const unsigned z = (unsigned)count;
+  hipLaunchKernelGGL(k_chol_first, dim3((unsigned)((p + kNb - 1) / kNb), 1, z), dim3(256), 0, st,
+                     A, lda, p, X, ldx, tol, ctrl, wz);
   for (int k0 = 0; k0 + kNb < p; k0 += kNb) {
     const int nt = (p - k0 - 1) / kNb;  // blocks of rows below the diagonal block
-    hipLaunchKernelGGL(k_chol_step, dim3((unsigned)(nt * (nt + 1) / 2)), dim3(256), 0, st, A, lda,
-                       p, k0, nt, X, ldx, (const double*)tol, ctrl);
+    hipLaunchKernelGGL(k_chol_step, dim3((unsigned)(nt * (nt + 1) / 2), 1, z), dim3(256), 0, st,
+                       A, lda, p, k0, nt, X, ldx, (const double*)tol, ctrl, wz);
   }
-  return tri_levels(A, lda, p, X, ldx, st);
+  return tri_levels(A, lda, p, X, ldx, count, wz, st);
 }
 
 hipError_t launch_unit_inverse(const double* L, int64_t ldl, int p, double* X, int64_t ldx,
-                              hipStream_t st) {
+                               hipStream_t st) {
   hipLaunchKernelGGL(k_trinv_diag, dim3((unsigned)((p + kNb - 1) / kNb)), dim3(64), 0, st, L, ldl,
                      p, X, ldx);
-  return tri_levels(L, ldl, p, X, ldx, st);
+  return tri_levels(L, ldl, p, X, ldx, 1, 0, st);
 }
 
 hipError_t launch_tri_adjacency(double* A, int p, const int32_t* order, double* B, double* Y,
-                                double* tol, Ctrl* ctrl, hipStream_t st) {
-  LG_HIP(launch_cholesky_inverse(A, p, p, Y, p, tol, ctrl, st));
-  hipLaunchKernelGGL(k_adj_scatter, dim3(grid_for((int64_t)p * p)), dim3(256), 0, st,
-                     (const double*)A, (int64_t)p, Y, (int64_t)p, p, order, B);
+                                double* tol, Ctrl* ctrl, int count, size_t wz, hipStream_t st) {
+  LG_HIP(launch_cholesky_inverse(A, p, p, Y, p, tol, ctrl, count, wz, st));
+  hipLaunchKernelGGL(k_adj_scatter, dim3(grid_for((int64_t)p * p), 1, (unsigned)count), dim3(256),
+                     0, st, (const double*)A, (int64_t)p, Y, (int64_t)p, p, order, B,
+                     (const Ctrl*)ctrl, wz);
   return hipGetLastError();
 }
 
@@ -1029,15 +1061,17 @@ hipError_t launch_perm_scale(const double* rho, int64_t ldr, const double* sig,
 }
 
 hipError_t launch_cov_perm(const double* Xd, int64_t ldx, int n, int d, const int32_t* order,
-                           double* mu, double* S, int nsplit, double* part, hipStream_t st) {
-  hipLaunchKernelGGL(k_row_mean, dim3((unsigned)d), dim3(256), 0, st, Xd, ldx, n, mu);
+                           double* mu, double* S, int nsplit, double* part, const Ctrl* ctrl,
+                           int count, size_t wz, hipStream_t st) {
+  const unsigned z = (unsigned)count;
+  hipLaunchKernelGGL(k_row_mean, dim3((unsigned)d, 1, z), dim3(256), 0, st, Xd, ldx, n, mu, wz);
   const int nb = (d + 31) / 32;
   const unsigned tiles = (unsigned)(nb * (nb + 1) / 2);
-  hipLaunchKernelGGL(k_cov_perm, dim3(tiles, (unsigned)nsplit), dim3(256), 0, st, Xd, ldx, n, d,
-                     order, mu, nb, S, part);
+  hipLaunchKernelGGL(k_cov_perm, dim3(tiles, (unsigned)nsplit, z), dim3(256), 0, st, Xd, ldx, n,
+                     d, order, (const double*)mu, nb, S, part, ctrl, wz);
   if (nsplit > 1)
-    hipLaunchKernelGGL(k_cov_sum, dim3(tiles), dim3(256), 0, st, (const double*)part, nsplit, d,
-                       nb, S);
+    hipLaunchKernelGGL(k_cov_sum, dim3(tiles, 1, z), dim3(256), 0, st, (const double*)part, nsplit,
+                       d, nb, S, wz);
   return hipGetLastError();
 }
 
@@ -1093,22 +1127,23 @@ hipError_t launch_adjacency_pruned(const PruneLayout& A, char* ws, const float* 
   // partial tiles lie in the regions from the correlation matrix on (7 d^2
   // doubles), which are written later
   LG_HIP(launch_cov_perm(Xd, A.ldx, n, d, order, at<double>(ws, A.mu), Sm,
-                         gram_splits(n, d, 7 * (int64_t)d * d / kTileElems), Rm, st));
+                         gram_splits(n, d, 7 * (int64_t)d * d / kTileElems), Rm, ctrl, 1, 0, st));
   const int64_t dd = (int64_t)d * d;
   hipLaunchKernelGGL(k_corr, dim3(grid_for(dd)), dim3(256), 0, st, (const double*)Sm, d, n,
-                     at<double>(ws, A.sd), Rm, Lm, ctrl);
-  LG_HIP(launch_cholesky_inverse(Lm, d, d, Ym, d, at<double>(ws, A.tol), ctrl, st));
-  hipLaunchKernelGGL(k_zero_f64, dim3(grid_for(dd)), dim3(256), 0, st, B, dd);
+                     at<double>(ws, A.sd), Rm, Lm, B, ctrl);
+  LG_HIP(launch_cholesky_inverse(Lm, d, d, Ym, d, at<double>(ws, A.tol), ctrl, 1, 0, st));
   if (d < 2) return hipGetLastError();
   const int cap = max_active < kLassoMaxActive ? max_active : kLassoMaxActive;
   // registers hold a predictor's row entries a thread; LDS the path state (d = 1024:
   // 48 KB beside M's 34, two workgroups a CU as in memory's case by registers)
+  // a thread a predictor: its rows' entries fit in registers; the path state in LDS
+  // (1024: 48 KB beside the inverse's 34, two workgroups a CU, as registers allow)
   const auto lars = d - 1 <= 256        ? k_lars<true, true>
                     : d - 1 <= kLarsLds ? k_lars<true, false>
                                         : k_lars<false, false>;
-  hipLaunchKernelGGL(lars, dim3((unsigned)(d - 1)), dim3(256), 0, st, (const double*)Rm, (const double*)Lm, (const double*)Ym,
-                     (const double*)at<double>(ws, A.sd), order, d, n, cap,
-                     at<double>(ws, A.st), B, ctrl);
+  hipLaunchKernelGGL(lars, dim3((unsigned)(d - 1)), dim3(256), 0, st, (const double*)Rm,
+                     (const double*)Lm, (const double*)Ym, (const double*)at<double>(ws, A.sd),
+                     order, d, n, cap, at<double>(ws, A.st), B, ctrl);
   return hipGetLastError();
 }
 

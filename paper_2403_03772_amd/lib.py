@@ -215,6 +215,11 @@ def load():
         lib.lingam_adjacency_workspace_size.argtypes = [i64, i64]
         lib.lingam_adjacency_workspace_size.restype = sz
         lib.lingam_adjacency.argtypes = [P, i64, i64, P, i64, i64, P, P, P, sz, P]
+        lib.lingam_bootstrap_regress_workspace_size.argtypes = [i64, i64, i32]
+        lib.lingam_bootstrap_regress_workspace_size.restype = sz
+        lib.lingam_bootstrap_regress.argtypes = [P, i64, i64, P, i64, i64, P, i32,
+                                                 ctypes.c_double, P, P, P, P, sz, P]
+        lib.lingam_bootstrap_regress.restype = ctypes.c_int
         lib.lingam_adjacency_pruned_workspace_size.argtypes = [i64, i64]
         lib.lingam_adjacency_pruned_workspace_size.restype = sz
         lib.lingam_adjacency_pruned.argtypes = [P, i64, i64, P, i64, i64, P, i32, P, P, sz, P]
@@ -566,17 +571,47 @@ def bootstrap(X, resamples, *, threshold: float = 0.0, graph: bool = False,
     order_count = torch.zeros((d, d), dtype=torch.int32, device=dev)
     edge_count = torch.zeros((d, d), dtype=torch.int32, device=dev)
     coef_sum = torch.zeros((d, d), dtype=torch.float64, device=dev)
-    size_of = (lib.lingam_adjacency_pruned_workspace_size if prune
-               else lib.lingam_adjacency_workspace_size)
-    need = max(int(size_of(r.numel(), d)) for r in rows)
-    ws = torch.empty(max(need, 1), dtype=torch.uint8, device=dev)
-    fit = adjacency_pruned if prune else adjacency
-    for r, o in zip(rows, out["orders"]):
-        B = fit(X, o, rows=r, workspace=ws)
-        bootstrap_accumulate(o, B, threshold, order_count, edge_count, coef_sum)
+    if prune:
+        need = max(int(lib.lingam_adjacency_pruned_workspace_size(r.numel(), d)) for r in rows)
+        ws = torch.empty(max(need, 1), dtype=torch.uint8, device=dev)
+        for r, o in zip(rows, out["orders"]):
+            B = adjacency_pruned(X, o, rows=r, workspace=ws)
+            bootstrap_accumulate(o, B, threshold, order_count, edge_count, coef_sum)
+    else:
+        _regress(torch, lib, X, rows, out["orders"], float(threshold), order_count, edge_count,
+                 coef_sum)
     probs = bootstrap_finalize(order_count, edge_count, coef_sum, len(rows))
     return {"orders": out["orders"], **probs, "n": len(rows),
             "order_count": order_count, "edge_count": edge_count}
+
+
+# Workspace of the regressions that run together (one at least).
+_REGRESS_BYTES = 1 << 30
+
+
+def _regress(torch, lib, X, rows, orders, threshold, order_count, edge_count, coef_sum):
+    """Regressions and counts of the resamples, in runs of equal size that fit
+    ``_REGRESS_BYTES`` (lingam_bootstrap_regress)."""
+    n_rows, d = X.shape
+    i, ws = 0, None
+    while i < len(rows):
+        n = rows[i].numel()
+        one = int(lib.lingam_bootstrap_regress_workspace_size(n, d, 1))
+        if one == 0:
+            raise LingamError(E_INVALID, f"unsupported size n={n} d={d}")
+        k = i + 1
+        while (k < len(rows) and rows[k].numel() == n and k - i < 65535
+               and (k - i + 1) * one <= _REGRESS_BYTES):
+            k += 1
+        need = int(lib.lingam_bootstrap_regress_workspace_size(n, d, k - i))
+        if ws is None or ws.numel() < need:
+            ws = torch.empty(need, dtype=torch.uint8, device=X.device)
+        r, o = torch.stack([v.reshape(-1) for v in rows[i:k]]), torch.stack(orders[i:k])
+        _check(lib.lingam_bootstrap_regress(_ptr(X), n_rows, X.stride(0), _ptr(r), n, d, _ptr(o),
+                                            k - i, threshold, _ptr(order_count),
+                                            _ptr(edge_count), _ptr(coef_sum), _ptr(ws),
+                                            ws.numel(), _stream_ptr(torch, X.device)))
+        i = k
 
 
 def bootstrap_finalize(order_count, edge_count, coef_sum, n_resamples: int) -> dict:
