@@ -83,32 +83,97 @@ __device__ inline void dither_float(double c, float& lo, float& hi, int& n_hi) {
   n_hi = (int)rint(ldexp(c - (double)lo, 6 - ilogb(gap)));
 }
 
-// e^x in FP64 for x <= 0, the exponentials of the FP64 paths (their arguments
-// are -2|u| and -u^2/2).  Cody and Waite's reduction x = k ln2 + r, |r| <=
-// ln2 / 2, with ln2 split into a 32-bit head (so k * head is exact for |k| <
-// 2^21) and the rest; e^r from its Taylor series to degree 12 (the remainder
-// is below 2.5e-16 of e^r); 2^k applied exactly by ldexp, which takes results
-// below the normal range through the subnormals to 0.  No range checks: the
-// arguments are never positive, infinite or NaN.
-__host__ __device__ inline double exp_nonpos(double x) {
-  constexpr double kLn2Head = 0x1.62e42ffp-1;            // ln 2 to 32 bits
-  constexpr double kLn2Rest = -0x1.718432a1b0e26p-35;    // ln 2 - kLn2Head
-  const double k = rint(x * kLog2e);
-  const double r = fma(-k, kLn2Rest, fma(-k, kLn2Head, x));
-  double p = 1.0 / 479001600.0;  // 1/12!
-  p = fma(p, r, 1.0 / 39916800.0);
-  p = fma(p, r, 1.0 / 3628800.0);
-  p = fma(p, r, 1.0 / 362880.0);
-  p = fma(p, r, 1.0 / 40320.0);
-  p = fma(p, r, 1.0 / 5040.0);
-  p = fma(p, r, 1.0 / 720.0);
+// 2^(j / 64), rounded to FP64.
+constexpr int kExpTable = 64;
+__device__ constexpr double kExp2[kExpTable] = {
+    0x1.0000000000000p+0, 0x1.02c9a3e778061p+0, 0x1.059b0d3158574p+0, 0x1.0874518759bc8p+0,
+    0x1.0b5586cf9890fp+0, 0x1.0e3ec32d3d1a2p+0, 0x1.11301d0125b51p+0, 0x1.1429aaea92de0p+0,
+    0x1.172b83c7d517bp+0, 0x1.1a35beb6fcb75p+0, 0x1.1d4873168b9aap+0, 0x1.2063b88628cd6p+0,
+    0x1.2387a6e756238p+0, 0x1.26b4565e27cddp+0, 0x1.29e9df51fdee1p+0, 0x1.2d285a6e4030bp+0,
+    0x1.306fe0a31b715p+0, 0x1.33c08b26416ffp+0, 0x1.371a7373aa9cbp+0, 0x1.3a7db34e59ff7p+0,
+    0x1.3dea64c123422p+0, 0x1.4160a21f72e2ap+0, 0x1.44e086061892dp+0, 0x1.486a2b5c13cd0p+0,
+    0x1.4bfdad5362a27p+0, 0x1.4f9b2769d2ca7p+0, 0x1.5342b569d4f82p+0, 0x1.56f4736b527dap+0,
+    0x1.5ab07dd485429p+0, 0x1.5e76f15ad2148p+0, 0x1.6247eb03a5585p+0, 0x1.6623882552225p+0,
+    0x1.6a09e667f3bcdp+0, 0x1.6dfb23c651a2fp+0, 0x1.71f75e8ec5f74p+0, 0x1.75feb564267c9p+0,
+    0x1.7a11473eb0187p+0, 0x1.7e2f336cf4e62p+0, 0x1.82589994cce13p+0, 0x1.868d99b4492edp+0,
+    0x1.8ace5422aa0dbp+0, 0x1.8f1ae99157736p+0, 0x1.93737b0cdc5e5p+0, 0x1.97d829fde4e50p+0,
+    0x1.9c49182a3f090p+0, 0x1.a0c667b5de565p+0, 0x1.a5503b23e255dp+0, 0x1.a9e6b5579fdbfp+0,
+    0x1.ae89f995ad3adp+0, 0x1.b33a2b84f15fbp+0, 0x1.b7f76f2fb5e47p+0, 0x1.bcc1e904bc1d2p+0,
+    0x1.c199bdd85529cp+0, 0x1.c67f12e57d14bp+0, 0x1.cb720dcef9069p+0, 0x1.d072d4a07897cp+0,
+    0x1.d5818dcfba487p+0, 0x1.da9e603db3285p+0, 0x1.dfc97337b9b5fp+0, 0x1.e502ee78b3ff6p+0,
+    0x1.ea4afa2a490dap+0, 0x1.efa1bee615a27p+0, 0x1.f50765b6e4540p+0, 0x1.fa7c1819e90d8p+0};
+
+// The table in LDS (as many threads as it has entries at least); the caller's next
+// barrier orders it.
+__device__ inline void stage_exp(double (&tab)[kExpTable]) {
+  if (threadIdx.x < kExpTable) tab[threadIdx.x] = kExp2[threadIdx.x];
+}
+
+// e^x in FP64 for x <= 0, the exponentials of the FP64 paths (their arguments are
+// -2|u| and -u^2/2), after Tang's table method: x = (k / 64) ln2 + r, |r| <= ln2 /
+// 128, with ln2 / 64 split into a 32-bit head (so k * head is exact) and the
+// rest; e^r from its Taylor series to degree 6 (the remainder is below 3e-20);
+// 2^((k mod 64) / 64) from the table; the rest of k is added to the exponent. k
+// is the low word of x 64 / ln2 + 1.5 2^52.  Against FP80 over [-700, 0]: at
+// most 0.87 ulp off, 1.57 for the series to degree 12 without a table, and
+// 12 FP64 instructions for its 18.  Below -707 the result is e^-707 (3e-308);
+// the arguments are never positive, infinite or NaN.
+__device__ __forceinline__ double exp_nonpos(const double (&tab)[kExpTable], double x) {
+  constexpr double kScale = 0x1.71547652b82fep+6;    // 64 / ln 2
+  constexpr double kHead = 0x1.62e42feep-7;          // ln 2 / 64 to 32 bits
+  constexpr double kRest = 0x1.a39ef35793c76p-39;    // ln 2 / 64 - kHead
+  constexpr double kShift = 0x1.8p52;
+  x = fmax(x, -707.0);
+  const double t = fma(x, kScale, kShift);
+  const int k = __double2loint(t);
+  const double kd = t - kShift;
+  const double r = fma(-kd, kRest, fma(-kd, kHead, x));
+  double p = 1.0 / 720.0;
   p = fma(p, r, 1.0 / 120.0);
   p = fma(p, r, 1.0 / 24.0);
   p = fma(p, r, 1.0 / 6.0);
   p = fma(p, r, 0.5);
-  p = fma(p, r, 1.0);
-  p = fma(p, r, 1.0);
-  return ldexp(p, (int)k);
+  const double q = fma(p * r, r, r);
+  const double w = tab[k & (kExpTable - 1)];
+  const double v = fma(w, q, w);
+  return __hiloint2double(__double2hiint(v) + ((k >> 6) << 20), __double2loint(v));
+}
+
+// Pointers read from the job table are generic; the hot loops cast row bases
+// to the global address space so loads use global_load with a scalar base.
+typedef __attribute__((address_space(1))) const char gchar_t;
+typedef __attribute__((address_space(1))) const float gfloat_t;
+typedef __attribute__((address_space(1))) const double gdouble_t;
+
+__device__ __forceinline__ double lane_of(double v, int l) {
+  const int lo = __builtin_amdgcn_readlane(__double2loint(v), l);
+  const int hi = __builtin_amdgcn_readlane(__double2hiint(v), l);
+  return __hiloint2double(hi, lo);
+}
+
+// Reductions within a wave: the lanes of a row of 16 exchange by DPP (a few cycles
+// a step, where a shuffle goes through LDS: a lasso path's eight reductions of six
+// shuffles took 0.7 us of each join), the four rows' results by readlane.
+template <int kCtrl>
+__device__ __forceinline__ int dpp(int v) {
+  return __builtin_amdgcn_update_dpp(0, v, kCtrl, 0xF, 0xF, true);
+}
+template <int kCtrl>
+__device__ __forceinline__ double dpp(double v) {
+  return __hiloint2double(dpp<kCtrl>(__double2hiint(v)), dpp<kCtrl>(__double2loint(v)));
+}
+constexpr int kXor1 = 0xB1, kXor2 = 0x4E, kHalfMirror = 0x141, kMirror = 0x140;
+template <class Op>
+__device__ __forceinline__ double wave_reduce(double v, Op op) {
+  v = op(v, dpp<kXor1>(v));
+  v = op(v, dpp<kXor2>(v));
+  v = op(v, dpp<kHalfMirror>(v));
+  v = op(v, dpp<kMirror>(v));
+  return op(op(lane_of(v, 0), lane_of(v, 16)), op(lane_of(v, 32), lane_of(v, 48)));
+}
+
+__device__ __forceinline__ double wave_sum(double v) {
+  return wave_reduce(v, [](double a, double b) { return a + b; });
 }
 
 // FP64 log cosh and Gaussian-weighted term (marginals and the FP64 pair path).
@@ -126,26 +191,33 @@ __device__ inline double gauss64(double u) { return u * exp(-0.5 * u * u); }
 // are taken as the log of their product (each factor is in (1, 2], so 512 of
 // them stay below 2^512), one FP64 log per 512 samples.
 __device__ inline void pair_sums64(const JobDev& J, int si, int sj, int lane, int first,
-                                   int stride, double (&v)[4]) {
+                                   int stride, const double (&tab)[kExpTable], double (&v)[4]) {
   double r = J.rho[(int64_t)si * J.d + sj];
   const double lim = 1.0 - kCollinear;
   r = r > lim ? lim : (r < -lim ? -lim : r);
   const double al = 1.0 / sqrt(1.0 - r * r);
-  const double* zi = J.zd + (int64_t)si * J.ldz;
-  const double* zj = J.zd + (int64_t)sj * J.ldz;
+  gdouble_t* zi = (gdouble_t*)(J.zd + (int64_t)si * J.ldz);
+  gdouble_t* zj = (gdouble_t*)(J.zd + (int64_t)sj * J.ldz);
+  const int n = J.n, step = stride * 64;
   double a1 = 0.0, a2 = 0.0, b1 = 0.0, b2 = 0.0;
   double pa = 1.0, pb = 1.0;
   int cnt = 0, tot = 0;
-  for (int s = first * 64 + lane; s < J.n; s += stride * 64) {
-    const double xi = zi[s], xj = zj[s];
+  int s = first * 64 + lane;
+  double yi = s < n ? zi[s] : 0.0, yj = s < n ? zj[s] : 0.0;  // fetched one block ahead
+  for (; s < n; s += step) {
+    const double xi = yi, xj = yj;
+    if (s + step < n) {
+      yi = zi[s + step];
+      yj = zj[s + step];
+    }
     const double u = al * (xi - r * xj), w = al * (xj - r * xi);
     const double au = fabs(u), aw = fabs(w);
     a1 += au;
     b1 += aw;
-    pa = fma(pa, exp_nonpos(-2.0 * au), pa);
-    pb = fma(pb, exp_nonpos(-2.0 * aw), pb);
-    a2 += u * exp_nonpos(-0.5 * u * u);
-    b2 += w * exp_nonpos(-0.5 * w * w);
+    pa = fma(pa, exp_nonpos(tab, -2.0 * au), pa);
+    pb = fma(pb, exp_nonpos(tab, -2.0 * aw), pb);
+    a2 += u * exp_nonpos(tab, -0.5 * u * u);
+    b2 += w * exp_nonpos(tab, -0.5 * w * w);
     ++tot;
     if (++cnt == 512) {
       a1 += log(pa);
@@ -159,9 +231,7 @@ __device__ inline void pair_sums64(const JobDev& J, int si, int sj, int lane, in
   v[2] = b1 + (log(pb) - (double)tot * kLn2);
   v[3] = b2;
 #pragma unroll
-  for (int k = 0; k < 4; ++k)
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) v[k] += __shfl_xor(v[k], off);
+  for (int k = 0; k < 4; ++k) v[k] = wave_sum(v[k]);
 }
 
 // R from the sums of pair_sums64 over all samples.
@@ -172,10 +242,6 @@ __device__ inline double measure64(const JobDev& J, int si, int sj, const double
   return (J.hm[sj] + h_ij) - (J.hm[si] + h_ji);
 }
 
-// Pointers read from the job table are generic; the hot loop casts row bases
-// to the global address space so loads use global_load with a scalar base.
-typedef __attribute__((address_space(1))) const char gchar_t;
-typedef __attribute__((address_space(1))) const float gfloat_t;
 
 __device__ __forceinline__ float readlane_f(float v, int l) {
   return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), l));
@@ -205,13 +271,15 @@ struct MomAcc {
   double abs_sum = 0.0, log_sum = 0.0, g = 0.0, z3 = 0.0, z4 = 0.0, prod = 1.0;
   double top = 0.0, copy = 0.0;
   int cnt = 0, tot = 0;
+  const double (&tab)[kExpTable];
+  __device__ inline explicit MomAcc(const double (&t)[kExpTable]) : tab(t) {}
   __device__ inline double add(double z) {  // returns exp(-z^2 / 2)
     const double a = fabs(z), z2 = z * z;
-    const double e = exp_nonpos(-0.5 * z2);
+    const double e = exp_nonpos(tab, -0.5 * z2);
     abs_sum += a;
     top = fmax(top, a);
     copy += (double)(float)z;
-    prod *= 1.0 + exp_nonpos(-2.0 * a);
+    prod *= 1.0 + exp_nonpos(tab, -2.0 * a);
     g += z * e;
     z3 += z2 * z;
     z4 += z2 * z2;
@@ -236,17 +304,14 @@ struct MomAcc {
 };
 
 // Block-wide deterministic sums (256 threads; of value kMomTop the maximum):
-// wave butterflies, then the four wave totals in order.  `sh` holds 28
+// within waves, then the four wave totals in order.  `sh` holds 28
 // doubles.  The result is valid in thread 0.
 __device__ inline void block_moments(double (&v)[7], double* sh) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
 #pragma unroll
   for (int k = 0; k < 7; ++k)
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) {
-      const double o = __shfl_xor(v[k], off);
-      v[k] = k == kMomTop ? fmax(v[k], o) : v[k] + o;
-    }
+    v[k] = k == kMomTop ? wave_reduce(v[k], [](double a, double b) { return fmax(a, b); })
+                        : wave_sum(v[k]);
   if (lane == 0)
 #pragma unroll
     for (int k = 0; k < 7; ++k) sh[k * 4 + wave] = v[k];
@@ -499,6 +564,26 @@ __device__ __forceinline__ void for_blocks(const int32_t* __restrict__ pre, int 
   }
 }
 
+// Item of workgroup b of g when every XCD is to get a contiguous range of them:
+// workgroups are dispatched round-robin over the 8 XCDs.  A permutation of 0 .. g - 1.
+__device__ __forceinline__ int xcd_item(int b, int g) {
+  const int Q = g >> 3, R = g & 7, x = b & 7;
+  return x * Q + (x < R ? x : R) + (b >> 3);
+}
+
+// for_blocks with neighbouring items on one XCD, so that their rows are shared in
+// its L2.
+template <typename F>
+__device__ __forceinline__ void for_blocks_xcd(const int32_t* __restrict__ pre, int njobs, F f) {
+  const int total = pre[njobs];
+  for (int b0 = 0; b0 + (int)blockIdx.x < total; b0 += gridDim.x) {
+    int jb, lb;
+    const int at = xcd_item(blockIdx.x, min((int)gridDim.x, total - b0));
+    if (!locate(pre, njobs, b0 + at, jb, lb)) break;
+    f(jb, lb);
+  }
+}
+
 // Pair moments (the hot loop), shared by the all-pairs kernel and the row
 // kernels of the learned form.  Grid: per job ntiles * nsplit * (4 / W)
 // workgroups of W waves (all pairs: upper-triangular 8 x 8 tiles of positions;
@@ -605,8 +690,7 @@ __device__ __forceinline__ void pair_tiles(const JobDev* __restrict__ jobs, int 
   // contiguous range of (job, tile, split) work so that the rows a tile reads
   // are shared in that XCD's L2.
   const int b = blockIdx.x;
-  const int Q = G >> 3, R = G & 7, x = b & 7, idx = b >> 3;
-  const int p = x * Q + (x < R ? x : R) + idx;
+  const int p = xcd_item(b, G);
   auto run = [&](int jb, int local) {
     const int item = local / kQ;
     pair_item<kMode, W>(jobs[jb], js[jb], item, (local - item * kQ) * W + lw, lane);

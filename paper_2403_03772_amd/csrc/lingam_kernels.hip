@@ -386,16 +386,18 @@ __global__ __launch_bounds__(256) void k_gram_sum(const JobDev* __restrict__ job
 // entropy H(z) of every variable (FP64).
 __global__ __launch_bounds__(256) void k_standardize(const JobDev* __restrict__ jobs, int njobs,
                                                      const int32_t* __restrict__ spre) {
-  __shared__ double sh[7 * 4];
+  __shared__ double sh[7 * 4], tab[kExpTable];
   int j, v;
   if (!locate(spre, njobs, blockIdx.x, j, v)) return;
+  stage_exp(tab);
+  __syncthreads();
   const JobDev& J = jobs[j];
   double* zd = J.zd + (int64_t)v * J.ldz;
   float* zf = J.z + (int64_t)v * J.ldz;
   float* zg = J.g ? J.g + (int64_t)v * J.ldz : nullptr;
   const double m = J.mu[v], is = 1.0 / J.sig[v];
   const int n = J.n;
-  MomAcc ma;
+  MomAcc ma(tab);
   for (int k = threadIdx.x; k < J.n_pad; k += 256) {
     if (k < n) {
       const double z = (zd[k] - m) * is;
@@ -469,13 +471,18 @@ __global__ __launch_bounds__(256) void k_combine(const JobDev* __restrict__ jobs
 // The same measure entirely in FP64 from the FP64 residuals, for steps with few
 // active variables.  w64 waves per unordered pair (both directions), 4 / w64
 // pairs a workgroup, lanes over samples, the waves' sums added in order; writes
-// R(i,j) and R(j,i) = -R(i,j).  About 90 FP64 instructions a sample and pair, 72
-// of them the four exponentials: bound by their issue once the device is full.
+// R(i,j) and R(j,i) = -R(i,j).  About 63 FP64 instructions a sample and pair, 48
+// of them the four exponentials, at 5.3 cycles each, and 25 others: bound by
+// their issue once the device is full (samples are fetched a block ahead, a job's
+// pairs lie on one XCD).  First step of 50 jobs of 50 x 1000: 271 -> 243 us with
+// the table's exponential (90 FP64 instructions before), of 10 x 10000: 105 -> 90.
 __global__ __launch_bounds__(256) void k_pair64(const JobDev* __restrict__ jobs, int njobs,
                                                 const JobStep* __restrict__ js,
                                                 const int32_t* __restrict__ pre) {
-  __shared__ double part[4][4];
-  for_blocks(pre, njobs, [&](int jb, int lb) {
+  __shared__ double part[4][4], tab[kExpTable];
+  stage_exp(tab);
+  __syncthreads();
+  for_blocks_xcd(pre, njobs, [&](int jb, int lb) {
   const JobDev& J = jobs[jb];
   const int m = js[jb].m, W = js[jb].w64;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -490,7 +497,7 @@ __global__ __launch_bounds__(256) void k_pair64(const JobDev* __restrict__ jobs,
       ++pi;
     }
     pj = pi + 1 + rem;
-    pair_sums64(J, J.act[pi], J.act[pj], lane, sub, W, v);
+    pair_sums64(J, J.act[pi], J.act[pj], lane, sub, W, tab, v);
   }
   if (W > 1) {  // workgroup-uniform
     if (lane == 0)
@@ -684,6 +691,8 @@ __device__ void tie_commit(const JobDev& J, int m, int nt, int t) {
 __global__ __launch_bounds__(256) void k_tie(const JobDev* __restrict__ jobs, int njobs,
                                              const JobStep* __restrict__ js, int t) {
   __shared__ int64_t spre[256];  // inclusive prefix of pair counts, this chunk of jobs
+  __shared__ double tab[kExpTable];
+  stage_exp(tab);
   const int tid = threadIdx.x, lane = tid & 63;
   const int64_t gw = (int64_t)blockIdx.x * 4 + (tid >> 6), nw = (int64_t)gridDim.x * 4;
   int64_t base = 0;  // pairs of the jobs before this chunk
@@ -725,7 +734,7 @@ __global__ __launch_bounds__(256) void k_tie(const JobDev* __restrict__ jobs, in
       if (pi != pj) {
         double v[4];
         const int si = J.act[pi], sj = J.act[pj];
-        pair_sums64(J, si, sj, lane, 0, 1, v);
+        pair_sums64(J, si, sj, lane, 0, 1, tab, v);
         Rv = measure64(J, si, sj, v);
       }
       if (lane == 0) *out = Rv;
@@ -757,9 +766,11 @@ __global__ __launch_bounds__(256) void k_tie(const JobDev* __restrict__ jobs, in
 __global__ __launch_bounds__(256) void k_resid(const JobDev* __restrict__ jobs, int njobs,
                                                const JobStep* __restrict__ js,
                                                const int32_t* __restrict__ pre) {
-  __shared__ double sh[7 * 4];
+  __shared__ double sh[7 * 4], tab[kExpTable];
   int jb, p;
   if (!locate(pre, njobs, blockIdx.x, jb, p)) return;
+  stage_exp(tab);
+  __syncthreads();
   const JobDev& J = jobs[jb];
   const int m_after = js[jb].m - 1;
   const int64_t ldz = J.ldz, ldr = J.d;
@@ -777,7 +788,7 @@ __global__ __launch_bounds__(256) void k_resid(const JobDev* __restrict__ jobs, 
   float* zf = J.z + (int64_t)sp * ldz;
   float* zg = J.g ? J.g + (int64_t)sp * ldz : nullptr;
   const int n = J.n;
-  MomAcc ma;
+  MomAcc ma(tab);
   // four samples per thread in flight: all loads are issued before the stores
   // (the rows of p and e are distinct), the samples are added in index order
   constexpr int kU = 4;

@@ -27,12 +27,6 @@ constexpr int kNb = 32;  // Cholesky panel width and update tile
 
 typedef double Block[kNb][kNb + 1];
 
-__device__ inline double lane_of(double v, int l) {
-  const int lo = __builtin_amdgcn_readlane(__double2loint(v), l);
-  const int hi = __builtin_amdgcn_readlane(__double2hiint(v), l);
-  return __hiloint2double(hi, lo);
-}
-
 // v[k] -= m col_k for k > j, col_k being lane k's value of col: all lanes are
 // read first, so that no product waits for its own, and fenced, or the compiler
 // would put every update of a column off to its turn, a chain as long as the
@@ -555,27 +549,6 @@ struct LarsShared {
   double rv[8][4];
   int ri[8][4];
 };
-
-// Reductions within a wave: the lanes of a row of 16 exchange by DPP (a few cycles
-// a step, where a shuffle goes through LDS: eight reductions of six shuffles were
-// half of a join), the four rows' results by readlane.
-template <int kCtrl>
-__device__ __forceinline__ int dpp(int v) {
-  return __builtin_amdgcn_update_dpp(0, v, kCtrl, 0xF, 0xF, true);
-}
-template <int kCtrl>
-__device__ __forceinline__ double dpp(double v) {
-  return __hiloint2double(dpp<kCtrl>(__double2hiint(v)), dpp<kCtrl>(__double2loint(v)));
-}
-constexpr int kXor1 = 0xB1, kXor2 = 0x4E, kHalfMirror = 0x141, kMirror = 0x140;
-template <class Op>
-__device__ __forceinline__ double wave_reduce(double v, Op op) {
-  v = op(v, dpp<kXor1>(v));
-  v = op(v, dpp<kXor2>(v));
-  v = op(v, dpp<kHalfMirror>(v));
-  v = op(v, dpp<kMirror>(v));
-  return op(op(lane_of(v, 0), lane_of(v, 16)), op(lane_of(v, 32), lane_of(v, 48)));
-}
 
 // (v, i) against (b, ib): the smaller value, ties to the smaller index; index -1 =
 // none.
