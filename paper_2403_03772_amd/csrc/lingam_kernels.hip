@@ -692,7 +692,6 @@ __global__ __launch_bounds__(256) void k_tie(const JobDev* __restrict__ jobs, in
                                              const JobStep* __restrict__ js, int t) {
   __shared__ int64_t spre[256];  // inclusive prefix of pair counts, this chunk of jobs
   __shared__ double tab[kExpTable];
-  stage_exp(tab);
   const int tid = threadIdx.x, lane = tid & 63;
   const int64_t gw = (int64_t)blockIdx.x * 4 + (tid >> 6), nw = (int64_t)gridDim.x * 4;
   int64_t base = 0;  // pairs of the jobs before this chunk
@@ -704,6 +703,9 @@ __global__ __launch_bounds__(256) void k_tie(const JobDev* __restrict__ jobs, in
       const int nt = C->ntie;
       if (C->tie_t == t && nt >= 2) c = (int64_t)nt * js[jc].m;
     }
+    // most steps have no near-ties: no prefix sums then (11 -> 5 us)
+    if (!__syncthreads_or(c != 0)) continue;
+    stage_exp(tab);
     spre[tid] = c;
     __syncthreads();
     for (int off = 1; off < 256; off <<= 1) {
