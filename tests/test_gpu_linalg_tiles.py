@@ -72,3 +72,23 @@ def test_split_correlations_of_a_job(lib, d, n):
     _, ref, _ = oracle.causal_order(X32.astype(np.float64), forced=[first], mode="table",
                                     with_measures=True)
     assert measure_close(out["measures"][0].cpu().numpy(), ref[0]).all()
+
+
+@pytest.mark.parametrize("p,n", [(5, 3000), (40, 1111)])
+def test_workspace_without_partial_tiles(lib, p, n):
+    """A workspace a byte short of the query holds all but the partial covariance
+    tiles: accepted, one range of samples, the same coefficients."""
+    import torch
+    from paper_2403_03772_amd import lib as binding
+    L = binding.load()
+    print(f"case p={p} n={n}", flush=True)
+    X32, order = _data(p, n, seed=3 * p + n)
+    X, o = torch.as_tensor(X32).cuda(), torch.as_tensor(order).cuda()
+    need = int(L.lingam_adjacency_workspace_size(n, p))
+    ws = torch.empty(need, dtype=torch.uint8, device="cuda")
+    B = torch.empty((p, p), dtype=torch.float64, device="cuda")
+    code = L.lingam_adjacency(binding._ptr(X), n, p, None, n, p, binding._ptr(o), binding._ptr(B),
+                              binding._ptr(ws), need - 1, binding._stream_ptr(torch, X.device))
+    assert code == 0
+    ref = _reference(X32, order)
+    assert np.abs(B.cpu().numpy() - ref).max() <= 1e-8 * max(1.0, np.abs(ref).max())
