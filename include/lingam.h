@@ -396,7 +396,8 @@ int lingam_bootstrap_accumulate(const int32_t* order, const double* B, int64_t d
  * once, and lingam_bootstrap_accumulate of each in turn.
  *   rows    device int32[count * n]: the resamples' row indices into X.
  *   orders  device int32[count * d]: their causal orders.
- * The other arguments as in those calls.  Synchronizes.  The first resample
+ * The other arguments as in those calls.  Synchronizes: the counts are complete on
+ * return, and orders, rows and ws may be reused.  The first resample
  * that lingam_adjacency would refuse gives its code, and nothing is counted.
  * count <= 65535.
  */

@@ -1210,14 +1210,13 @@ int lingam_bootstrap_regress(const float* X, int64_t n_rows, int64_t ldx, const 
   LG_TRY(lg::launch_adj_check(A, w, orders, rows, n_rows, count, st), "adjacency check");
   LG_TRY(lg::launch_adjacency(A, w, X, ldx, rows, orders, B, count, st), "adjacency launch");
   LG_TRY(lg::launch_first_status(A, w, count, first, st), "adjacency status");
+  LG_TRY(lg::launch_boot_accumulate(first, orders, B, (int)d, count, threshold, order_count,
+                                    edge_count, coef_sum, st),
+         "bootstrap accumulate");
   LG_TRY(hipMemcpyAsync(s, first, sizeof(s), hipMemcpyDeviceToHost, st),
          "hipMemcpyAsync(status)");
   LG_TRY(hipStreamSynchronize(st), "hipStreamSynchronize");
-  if (s[0] >= 0) return adjacency_status(s[1]);
-  LG_TRY(lg::launch_boot_accumulate(orders, B, (int)d, count, threshold, order_count, edge_count,
-                                    coef_sum, st),
-         "bootstrap accumulate");
-  return LINGAM_OK;
+  return s[0] >= 0 ? adjacency_status(s[1]) : LINGAM_OK;
 }
 
 size_t lingam_adjacency_pruned_workspace_size(int64_t n, int64_t d) {
@@ -1310,7 +1309,7 @@ int lingam_bootstrap_accumulate(const int32_t* order, const double* B, int64_t d
   if (d < 1) return fail(LINGAM_E_INVALID, "need d >= 1 (got %lld)", (long long)d);
   if (d > kMaxD) return fail(LINGAM_E_UNSUPPORTED, "d <= %lld supported", (long long)kMaxD);
   if (!(threshold >= 0.0)) return fail(LINGAM_E_INVALID, "threshold must be >= 0");
-  LG_TRY(lg::launch_boot_accumulate(order, B, (int)d, 1, threshold, order_count, edge_count,
+  LG_TRY(lg::launch_boot_accumulate(nullptr, order, B, (int)d, 1, threshold, order_count, edge_count,
                                     coef_sum, (hipStream_t)stream),
          "bootstrap accumulate");
   return LINGAM_OK;

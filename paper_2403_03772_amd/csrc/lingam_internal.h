@@ -688,10 +688,11 @@ hipError_t launch_adjacency(const AdjLayout& A, char* ws, const float* X, int64_
 // out[0] = the first job whose status is not 0, or -1; out[1] = that status.
 hipError_t launch_first_status(const AdjLayout& A, const char* ws, int count, int32_t* out,
                                hipStream_t st);
-// Bootstrap counts of `count` resamples (see lingam_bootstrap_accumulate).
-hipError_t launch_boot_accumulate(const int32_t* order, const double* B, int d, int count,
-                                  double thr, int32_t* order_count, int32_t* edge_count,
-                                  double* coef_sum, hipStream_t st);
+// Bootstrap counts of `count` resamples (see lingam_bootstrap_accumulate); nothing if
+// `first` (out of launch_first_status, or NULL) says that one was refused.
+hipError_t launch_boot_accumulate(const int32_t* first, const int32_t* order, const double* B,
+                                  int d, int count, double thr, int32_t* order_count,
+                                  int32_t* edge_count, double* coef_sum, hipStream_t st);
 // The counts divided by the number of resamples (see lingam_bootstrap_finalize).
 hipError_t launch_boot_finalize(const int32_t* order_count, const int32_t* edge_count,
                                 const double* coef_sum, int d, int32_t n_resamples,

@@ -1071,29 +1071,35 @@ __global__ __launch_bounds__(1024) void k_check_perm(const int32_t* __restrict__
 }
 
 // out[0] = the first job of `count` whose status is not 0, or -1; out[1] = it.
-__global__ void k_first_status(const Ctrl* __restrict__ ctrl, size_t wz, int count,
-                               int32_t* __restrict__ out) {
-  int32_t job = -1, status = 0;
-  for (int z = 0; z < count && job < 0; ++z) {
-    const Ctrl* c = (const Ctrl*)((const char*)ctrl + z * wz);
-    if (c->status != 0) {
-      job = z;
-      status = c->status;
+__global__ __launch_bounds__(256) void k_first_status(const Ctrl* __restrict__ ctrl, size_t wz,
+                                                      int count, int32_t* __restrict__ out) {
+  __shared__ int32_t first;
+  auto status = [&](int z) { return ((const Ctrl*)((const char*)ctrl + z * wz))->status; };
+  if (threadIdx.x == 0) first = count;
+  __syncthreads();
+  for (int z = threadIdx.x; z < count; z += 256)
+    if (status(z) != 0) {
+      atomicMin(&first, z);
+      break;
     }
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    out[0] = first < count ? first : -1;
+    out[1] = first < count ? status(first) : 0;
   }
-  out[0] = job;
-  out[1] = status;
 }
 
 // Bootstrap counts of `count` resamples: order_count[i][j] += 1 when x_j precedes
 // x_i; edge_count[i][j] += 1 when |B[i][j]| > thr; coef_sum += B (if given), in
-// the resamples' order.
-__global__ void k_boot_accumulate(const int32_t* __restrict__ order,
+// the resamples' order.  Nothing if `first` (k_first_status) names a refused one.
+__global__ void k_boot_accumulate(const int32_t* __restrict__ first,
+                                  const int32_t* __restrict__ order,
                                   const double* __restrict__ B, int d, int count, double thr,
                                   int32_t* __restrict__ order_count,
                                   int32_t* __restrict__ edge_count,
                                   double* __restrict__ coef_sum) {
   const int64_t total = (int64_t)d * d;
+  if (first && first[0] >= 0) return;
   for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < total;
        e += (int64_t)gridDim.x * blockDim.x) {
     const int a = (int)(e / d), b = (int)(e - (int64_t)a * d);  // positions a > b
@@ -1553,17 +1559,17 @@ hipError_t launch_adjacency(const AdjLayout& A, char* ws, const float* X, int64_
 
 hipError_t launch_first_status(const AdjLayout& A, const char* ws, int count, int32_t* out,
                                hipStream_t st) {
-  hipLaunchKernelGGL(k_first_status, dim3(1), dim3(1), 0, st,
+  hipLaunchKernelGGL(k_first_status, dim3(1), dim3(256), 0, st,
                      reinterpret_cast<const Ctrl*>(ws + A.ctrl), A.total, count, out);
   return hipGetLastError();
 }
 
-hipError_t launch_boot_accumulate(const int32_t* order, const double* B, int d, int count,
-                                  double thr, int32_t* order_count, int32_t* edge_count,
-                                  double* coef_sum, hipStream_t st) {
+hipError_t launch_boot_accumulate(const int32_t* first, const int32_t* order, const double* B,
+                                  int d, int count, double thr, int32_t* order_count,
+                                  int32_t* edge_count, double* coef_sum, hipStream_t st) {
   const int64_t g = ((int64_t)d * d + 255) / 256;
   hipLaunchKernelGGL(k_boot_accumulate, dim3((unsigned)(g < 4096 ? g : 4096)), dim3(256), 0, st,
-                     order, B, d, count, thr, order_count, edge_count, coef_sum);
+                     first, order, B, d, count, thr, order_count, edge_count, coef_sum);
   return hipGetLastError();
 }
 
