@@ -180,6 +180,7 @@ Learn learn_of(const lingam_opts* o) {
 struct Plan {
   int njobs = 0;
   int cu = 0;
+  bool ahead = true;  // a step's selection plans the next step (two schedules)
   size_t table_off = 0, sched_off = 0, prop_off = 0, total = 0;
   std::vector<lg::Layout> L;
   std::vector<size_t> job_off;
@@ -189,22 +190,25 @@ struct Plan {
 
 size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
 
-Plan make_plan(const std::vector<HostJob>& jobs, int cu, const Learn& lc, bool share = true) {
+// lean 1 leaves out the regions that the pair kernels can do without, lean 2 the
+// second schedule too: what is left is as large as it was before there was either.
+Plan make_plan(const std::vector<HostJob>& jobs, int cu, const Learn& lc, int lean = 0) {
   Plan P;
   P.njobs = (int)jobs.size();
   P.cu = cu;
   P.lc = lc;
+  P.ahead = lean < 2;
   size_t off = 0;
   P.table_off = off;
   off = align256(off + sizeof(lg::JobDev) * (size_t)P.njobs);
   P.sched_off = off;
-  off = align256(off + lg::sched_bytes(P.njobs));
+  off = align256(off + lg::sched_bytes(P.njobs, P.ahead));
   if (lc.proposer) {
     P.prop_off = off;
     off = align256(off + sizeof(lg::PropDev));
   }
   for (const HostJob& j : jobs) {
-    P.L.push_back(lg::make_layout(j.n, j.d, cu, lc.proposer ? lc.K : 0, share));
+    P.L.push_back(lg::make_layout(j.n, j.d, cu, lc.proposer ? lc.K : 0, lean == 0));
     P.job_off.push_back(off);
     off = align256(off + P.L.back().total);
     P.max_d = std::max(P.max_d, (int)j.d);
@@ -213,14 +217,18 @@ Plan make_plan(const std::vector<HostJob>& jobs, int cu, const Learn& lc, bool s
   return P;
 }
 
-// The plan for a workspace of `avail` bytes: without the regions the pair
-// kernels can do without where only that fits (never larger than avail says,
-// if either does).
+// The plan for a workspace of `avail` bytes: the least lean that fits, the
+// largest if none does.
 Plan plan_for(const std::vector<HostJob>& jobs, int cu, const Learn& lc, size_t avail) {
-  Plan P = make_plan(jobs, cu, lc);
-  if (P.total <= avail) return P;
-  Plan lean = make_plan(jobs, cu, lc, false);
-  return lean.total <= avail ? lean : P;
+  for (int lean = 0; lean < 3; ++lean) {
+    Plan P = make_plan(jobs, cu, lc, lean);
+    if (P.total <= avail) return P;
+  }
+  return make_plan(jobs, cu, lc);
+}
+
+lg::SchedDev sched_of(const Plan& P, char* ws, int t) {
+  return lg::sched_at(ws + P.sched_off, P.njobs, t, P.ahead);
 }
 
 std::vector<lg::JobDev> device_jobs(const Plan& P, const std::vector<HostJob>& jobs, char* ws,
@@ -350,7 +358,7 @@ template <typename AfterGram>
 int enqueue_setup(const Plan& P, const std::vector<lg::JobDev>& dj, char* ws, hipStream_t st,
                   Prof* pf, AfterGram after_gram) {
   lg::JobDev* table = reinterpret_cast<lg::JobDev*>(ws + P.table_off);
-  const lg::SchedDev sc = lg::sched_at(ws + P.sched_off, P.njobs, 0);
+  const lg::SchedDev sc = sched_of(P, ws, 0);
   for (int k = 0; k < P.njobs; k += lg::kJobsPerLaunch)
     LG_TRY(lg::launch_set_jobs(table, k, dj.data() + k,
                                std::min(lg::kJobsPerLaunch, P.njobs - k), st),
@@ -387,8 +395,8 @@ int enqueue_steps(const Plan& P, const std::vector<HostJob>& jobs, char* ws, hip
   for (int t = 0; t + 1 < P.max_d; ++t) {
     const StepTotals T = step_totals(jobs, P, t, tu, ties);
     if (T.g[lg::kKSel] == 0) break;  // every job finished
-    const lg::SchedDev sc = lg::sched_at(ws + P.sched_off, P.njobs, t);
-    if (t == 0)  // later steps are planned by the selection before them
+    const lg::SchedDev sc = sched_of(P, ws, t);
+    if (t == 0 || !P.ahead)  // other steps are planned by the selection before them
       LG_TRY(lg::launch_step_schedule(table, P.njobs, t, P.cu, tu, sc, st), "step schedule");
     if (T.g[lg::kKFeat] > 0 || T.g[lg::kKMlp] > 0)
       LG_TRY(lg::launch_learned_front(table, P.njobs, t, sc, T.g, st), "features / scores");
@@ -453,9 +461,9 @@ int enqueue_steps(const Plan& P, const std::vector<HostJob>& jobs, char* ws, hip
     }
     LG_TRY(lg::launch_pair64(table, P.njobs, sc, T.g[lg::kKP64], st), "pair64");
     LG_TRY(lg::launch_rowk(table, P.njobs, sc, capped(T.g[lg::kKRowk], 8), st), "rowk");
-    const lg::NextStep next{lg::sched_at(ws + P.sched_off, P.njobs, t + 1), P.cu, tu};
+    const lg::NextStep next{sched_of(P, ws, t + 1), P.cu, tu};
     LG_TRY(lg::launch_select(table, P.njobs, t, sc, T.g[lg::kKSel],
-                             t + 2 < P.max_d ? &next : nullptr, st),
+                             P.ahead && t + 2 < P.max_d ? &next : nullptr, st),
            "select");
     // near-ties of FP32-path steps (full or learned) decided in FP64
     if (ties && (T.g[lg::kKPair] > 0 || gated))
@@ -553,7 +561,7 @@ void save_tune_file(const DevState& ds) {
 int autotune(const Plan& P, const std::vector<HostJob>& jobs, char* ws, hipStream_t st,
              bool ties, lg::Tune* out) {
   lg::JobDev* table = reinterpret_cast<lg::JobDev*>(ws + P.table_off);
-  const lg::SchedDev sc = lg::sched_at(ws + P.sched_off, P.njobs, 0);
+  const lg::SchedDev sc = sched_of(P, ws, 0);
   std::vector<int> steps;
   const int dmax = P.max_d;
   for (double f : {0.0, 0.25, 0.5, 0.7, 0.85}) {

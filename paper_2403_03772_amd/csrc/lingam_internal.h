@@ -534,15 +534,15 @@ __host__ __device__ inline int32_t setup_count(int32_t n_pad, int32_t d, int kin
 Layout make_layout(int64_t n, int64_t d, int num_cu, int K = 0, bool share = true);
 
 // Schedule buffers of a batch (device): JobStep[njobs] and kNumKinds prefix
-// arrays of njobs + 1 entries, twice (a step's selection plans the next step
-// in the other buffer); for the set-up, kNumSetupKinds prefix arrays.
+// arrays of njobs + 1 entries, twice where a step's selection plans the next step
+// in the other buffer (ahead); for the set-up, kNumSetupKinds prefix arrays.
 struct SchedDev {
   JobStep* js;
   int32_t* pre;   // [kNumKinds][njobs + 1]
   int32_t* spre;  // [kNumSetupKinds][njobs + 1]
 };
-size_t sched_bytes(int njobs);
-SchedDev sched_at(char* base, int njobs, int t);  // the buffer of step t
+size_t sched_bytes(int njobs, bool ahead);
+SchedDev sched_at(char* base, int njobs, int t, bool ahead);  // the buffer of step t
 
 // Kernel launchers (all asynchronous on `st`).  `grid` is the host's total of
 // the matching prefix array.

@@ -1237,13 +1237,27 @@ Layout make_layout(int64_t n, int64_t d, int num_cu, int K, bool share) {
 
 static size_t sched_js_bytes(int njobs) { return align256(2 * sizeof(JobStep) * (size_t)njobs); }
 
-size_t sched_bytes(int njobs) {
+// Alone, a schedule takes what it took when a plan held one word less and the set-up
+// had three prefix arrays of its own: the arrays lie side by side, the set-up's where
+// the steps' go once the set-up is done.
+size_t sched_bytes(int njobs, bool ahead) {
+  const size_t ints = sizeof(int32_t) * (size_t)(njobs + 1);
+  if (!ahead)
+    return align256((sizeof(JobStep) - sizeof(int32_t)) * (size_t)njobs) +
+           align256(kNumKinds * ints) + align256(3 * ints);
   return sched_js_bytes(njobs) +
-         align256(sizeof(int32_t) * (size_t)(2 * kNumKinds + kNumSetupKinds) * (size_t)(njobs + 1));
+         align256((2 * kNumKinds + kNumSetupKinds) * ints);
 }
 
-SchedDev sched_at(char* base, int njobs, int t) {
+SchedDev sched_at(char* base, int njobs, int t, bool ahead) {
+  static_assert((int)kNumSetupKinds <= (int)kNumKinds, "the set-up's arrays fit the steps'");
+  static_assert(sizeof(JobStep) % sizeof(int32_t) == 0, "prefix arrays follow the plans");
   SchedDev s;
+  if (!ahead) {
+    s.js = reinterpret_cast<JobStep*>(base);
+    s.pre = s.spre = reinterpret_cast<int32_t*>(s.js + njobs);
+    return s;
+  }
   const size_t kinds = (size_t)kNumKinds * (size_t)(njobs + 1);
   int32_t* p = reinterpret_cast<int32_t*>(base + sched_js_bytes(njobs));
   s.js = reinterpret_cast<JobStep*>(base) + (size_t)(t & 1) * (size_t)njobs;
