@@ -83,6 +83,10 @@ typedef enum {
                                    if set) */
 #define LINGAM_FLAG_FP32_TIES 8u /* decide near-ties from the FP32 measures alone (no FP64
                                     tie resolution; see lingam_causal_order) */
+#define LINGAM_FLAG_LEAST_WORKSPACE 16u /* lingam_workspace_size, lingam_batch_workspace_size
+                                    and varlingam_workspace_size give the least size that
+                                    the calls accept, not the one they are fastest with (a
+                                    quarter to a third less); the calls go by ws_bytes */
 
 /* Per-call profile, filled when opts->profile is non-NULL (forces a sync). */
 typedef struct lingam_profile {
@@ -304,8 +308,10 @@ size_t lingam_residualize_workspace_size(int64_t n, int64_t d);
 int lingam_residualize(float* X, int64_t n, int64_t d, int64_t ldx, const int32_t* active,
                        int32_t n_active, int32_t exo, void* ws, size_t ws_bytes, void* stream);
 
-/* Workspace bytes for lingam_adjacency on n samples of d variables (0 if unsupported). */
+/* Workspace bytes for lingam_adjacency on n samples of d variables (0 if unsupported),
+ * and the least that it accepts (the covariance is then not split over samples). */
 size_t lingam_adjacency_workspace_size(int64_t n, int64_t d);
+size_t lingam_adjacency_least_workspace_size(int64_t n, int64_t d);
 
 /*
  * Weighted adjacency matrix from a causal order: every variable is regressed

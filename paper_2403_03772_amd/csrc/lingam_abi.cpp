@@ -227,6 +227,11 @@ Plan plan_for(const std::vector<HostJob>& jobs, int cu, const Learn& lc, size_t 
   return make_plan(jobs, cu, lc);
 }
 
+// What a workspace query asks for.
+int lean_of(const lingam_opts* opts) {
+  return opts && (opts->flags & LINGAM_FLAG_LEAST_WORKSPACE) ? 2 : 0;
+}
+
 lg::SchedDev sched_of(const Plan& P, char* ws, int t) {
   return lg::sched_at(ws + P.sched_off, P.njobs, t, P.ahead);
 }
@@ -932,7 +937,7 @@ size_t lingam_workspace_size(int64_t n, int64_t d, const lingam_opts* opts) {
   HostJob j{};
   j.n = n;
   j.d = d;
-  return make_plan({j}, cu, learn_of(opts)).total;
+  return make_plan({j}, cu, learn_of(opts), lean_of(opts)).total;
 }
 
 }  // extern "C"
@@ -1032,7 +1037,7 @@ size_t lingam_batch_workspace_size(const lingam_job* jobs, int32_t n_jobs,
   if (batch_jobs(jobs, n_jobs, &hj) != LINGAM_OK) return 0;
   int cu = 0;
   if (num_cu_of_current(&cu) != LINGAM_OK) cu = 256;
-  return make_plan(hj, cu, learn_of(opts)).total;
+  return make_plan(hj, cu, learn_of(opts), lean_of(opts)).total;
 }
 
 int lingam_batch_causal_order(const lingam_job* jobs, int32_t n_jobs, int32_t* job_status,
@@ -1077,7 +1082,7 @@ size_t varlingam_workspace_size(int64_t T, int64_t d, int32_t lags, const lingam
   HostJob j{};
   j.n = T - lags;
   j.d = d;
-  const Plan P = make_plan({j}, cu, learn_of(opts));
+  const Plan P = make_plan({j}, cu, learn_of(opts), lean_of(opts));
   return align256(P.total) + lg::make_var_layout(T, d, lags, cu).total;
 }
 
@@ -1155,6 +1160,11 @@ constexpr int32_t kMaxRegress = 65535;
 size_t lingam_adjacency_workspace_size(int64_t n, int64_t d) {
   if (n < 2 || d < 1 || n > kMaxN || d > kMaxD) return 0;
   return lg::make_adj_layout(n, d).total;
+}
+
+size_t lingam_adjacency_least_workspace_size(int64_t n, int64_t d) {
+  if (n < 2 || d < 1 || n > kMaxN || d > kMaxD) return 0;
+  return lg::make_adj_layout(n, d, false).total;
 }
 
 int lingam_adjacency(const float* X, int64_t n_rows, int64_t ldx, const int32_t* rows, int64_t n,

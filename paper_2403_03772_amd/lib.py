@@ -17,7 +17,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(HERE, "liblingam_mi355x.so")
 
 OK, E_INVALID, E_DEGENERATE, E_HIP, E_WORKSPACE, E_UNSUPPORTED = 0, -1, -2, -3, -4, -5
-FLAG_NO_SYNC, FLAG_GRAPH, FLAG_AUTOTUNE, FLAG_FP32_TIES = 1, 2, 4, 8
+FLAG_NO_SYNC, FLAG_GRAPH, FLAG_AUTOTUNE, FLAG_FP32_TIES, FLAG_LEAST_WORKSPACE = 1, 2, 4, 8, 16
 
 # proposer network (include/lingam.h)
 N_FEATURES = 16
@@ -214,6 +214,8 @@ def load():
         lib.lingam_proposer_adam.restype = ctypes.c_int
         lib.lingam_adjacency_workspace_size.argtypes = [i64, i64]
         lib.lingam_adjacency_workspace_size.restype = sz
+        lib.lingam_adjacency_least_workspace_size.argtypes = [i64, i64]
+        lib.lingam_adjacency_least_workspace_size.restype = sz
         lib.lingam_adjacency.argtypes = [P, i64, i64, P, i64, i64, P, P, P, sz, P]
         lib.lingam_bootstrap_regress_workspace_size.argtypes = [i64, i64, i32]
         lib.lingam_bootstrap_regress_workspace_size.restype = sz
@@ -313,6 +315,33 @@ def _new_opts(lib, *, sync=True, graph=False, autotune=False, learned=None, prof
     return opts, prof, stats
 
 
+def _workspace(torch, given, need, least, dev):
+    """Workspace of ``need`` bytes: the one given if it is as large, or a new one.
+    Where the device has no room for that, one of ``least()`` bytes at least (the
+    calls accept it and are slower)."""
+    if given is not None and given.numel() >= need:
+        return given
+    try:
+        return torch.empty(need, dtype=torch.uint8, device=dev)
+    except torch.OutOfMemoryError:
+        less = int(least())
+        if given is not None and given.numel() >= less:
+            return given
+        if less >= need:
+            raise
+    return torch.empty(less, dtype=torch.uint8, device=dev)
+
+
+def _least(query, opts):
+    """The size query ``query(opts)`` asked for the least size."""
+    flags = opts.flags
+    opts.flags |= FLAG_LEAST_WORKSPACE
+    try:
+        return query(ctypes.byref(opts))
+    finally:
+        opts.flags = flags
+
+
 def _profile_of(prof):
     return Profile(**{k: getattr(prof, k) for k, _ in _Profile._fields_})
 
@@ -396,8 +425,9 @@ def causal_order(X, *, forced=None, with_measures: bool = False, profile: bool =
         need = int(lib.lingam_workspace_size(n, d, ctypes.byref(opts)))
         if need == 0:
             raise LingamError(E_UNSUPPORTED, last_error() or f"unsupported size n={n} d={d}")
-        if workspace is None or workspace.numel() < need:
-            workspace = torch.empty(need, dtype=torch.uint8, device=dev)
+        workspace = _workspace(
+            torch, workspace, need,
+            lambda: _least(lambda o: lib.lingam_workspace_size(n, d, o), opts), dev)
         code = lib.lingam_causal_order(_ptr(X), n, d, ldx, _ptr(order), ctypes.byref(opts),
                                        _ptr(workspace), workspace.numel(),
                                        _stream_ptr(torch, dev))
@@ -466,9 +496,8 @@ def adjacency(X, order, *, rows=None, workspace=None):
     need = int(lib.lingam_adjacency_workspace_size(n, d))
     if need == 0:
         raise LingamError(E_INVALID, f"unsupported size n={n} d={d}")
-    ws = workspace
-    if ws is None or ws.numel() < need:
-        ws = torch.empty(need, dtype=torch.uint8, device=X.device)
+    ws = _workspace(torch, workspace, need,
+                    lambda: lib.lingam_adjacency_least_workspace_size(n, d), X.device)
     B = torch.empty((d, d), dtype=torch.float64, device=X.device)
     code = lib.lingam_adjacency(_ptr(X), n_rows, X.stride(0), _ptr(r), n, d, _ptr(o), _ptr(B),
                                 _ptr(ws), ws.numel(), _stream_ptr(torch, X.device))
@@ -591,22 +620,37 @@ _REGRESS_BYTES = 1 << 30
 
 def _regress(torch, lib, X, rows, orders, threshold, order_count, edge_count, coef_sum):
     """Regressions and counts of the resamples, in runs of equal size that fit
-    ``_REGRESS_BYTES`` (lingam_bootstrap_regress)."""
+    ``_REGRESS_BYTES`` (lingam_bootstrap_regress) and the device's free memory; one by
+    one as :func:`adjacency` where that holds no run."""
     n_rows, d = X.shape
     i, ws = 0, None
+    most = len(rows)
     while i < len(rows):
         n = rows[i].numel()
         one = int(lib.lingam_bootstrap_regress_workspace_size(n, d, 1))
         if one == 0:
             raise LingamError(E_INVALID, f"unsupported size n={n} d={d}")
         k = i + 1
-        while (k < len(rows) and rows[k].numel() == n and k - i < 65535
+        while (k < len(rows) and rows[k].numel() == n and k - i < min(65535, most)
                and (k - i + 1) * one <= _REGRESS_BYTES):
             k += 1
         need = int(lib.lingam_bootstrap_regress_workspace_size(n, d, k - i))
-        if ws is None or ws.numel() < need:
-            ws = torch.empty(need, dtype=torch.uint8, device=X.device)
-        r, o = torch.stack([v.reshape(-1) for v in rows[i:k]]), torch.stack(orders[i:k])
+        try:
+            if ws is None or ws.numel() < need:
+                ws = None
+                ws = torch.empty(need, dtype=torch.uint8, device=X.device)
+            r, o = rows[i], orders[i]
+            if k - i > 1:
+                r = torch.stack([v.reshape(-1) for v in rows[i:k]])
+                o = torch.stack(orders[i:k])
+        except torch.OutOfMemoryError:
+            ws, r, most = None, None, (k - i) // 2
+            if most == 0:
+                B = adjacency(X, orders[i], rows=rows[i])
+                bootstrap_accumulate(orders[i], B, threshold, order_count, edge_count, coef_sum)
+                del B
+                i, most = i + 1, 1
+            continue
         _check(lib.lingam_bootstrap_regress(_ptr(X), n_rows, X.stride(0), _ptr(r), n, d, _ptr(o),
                                             k - i, threshold, _ptr(order_count),
                                             _ptr(edge_count), _ptr(coef_sum), _ptr(ws),
@@ -687,7 +731,9 @@ def varlingam_fit(X, lags: int = 1, *, forced=None, with_measures: bool = False,
     need = int(lib.varlingam_workspace_size(T, d, int(lags), ctypes.byref(opts)))
     if need == 0:
         raise LingamError(E_INVALID, f"unsupported size T={T} d={d} lags={lags}")
-    ws = torch.empty(need, dtype=torch.uint8, device=dev)
+    ws = _workspace(
+        torch, None, need,
+        lambda: _least(lambda o: lib.varlingam_workspace_size(T, d, int(lags), o), opts), dev)
     code = lib.varlingam_fit(_ptr(X), T, d, X.stride(0), int(lags), _ptr(out["M"]),
                              _ptr(out["resid"]), _ptr(out["order"]), _ptr(out["B0"]),
                              ctypes.byref(opts), _ptr(ws), ws.numel(), _stream_ptr(torch, dev))
@@ -754,8 +800,9 @@ def batch_causal_order(jobs, *, graph: bool = False, autotune: bool = False,
     need = int(lib.lingam_batch_workspace_size(arr, njobs, ctypes.byref(opts)))
     if need == 0:
         raise LingamError(E_INVALID, last_error() or "invalid batch")
-    if workspace is None or workspace.numel() < need:
-        workspace = torch.empty(need, dtype=torch.uint8, device=dev)
+    workspace = _workspace(
+        torch, workspace, need,
+        lambda: _least(lambda o: lib.lingam_batch_workspace_size(arr, njobs, o), opts), dev)
     status = torch.zeros(njobs, dtype=torch.int32, device=dev)
     code = lib.lingam_batch_causal_order(arr, njobs, _ptr(status), ctypes.byref(opts),
                                          _ptr(workspace), workspace.numel(),
