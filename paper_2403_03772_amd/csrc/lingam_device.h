@@ -342,22 +342,38 @@ __device__ inline void store_moments(const JobDev& J, int slot, const double (&a
 // measure_from_sums adds for the whole sample.
 __device__ inline bool shared_job(const JobDev& J) { return J.g != nullptr && J.tie_on; }
 
+constexpr double kShareTop = 13.0;  // largest |x| of the shared form's x side
+
+// Largest |z| of active position p (m: padding).
+__device__ inline double top_at(const JobDev& J, int m, int p) {
+  return p < m ? J.mom[(int64_t)J.act[p] * 8 + kMomTop] : 0.0;
+}
+
+// Of the 16 lanes of a 4 x 4 sub-block (lane q: ti of row q / 4, tj of column q % 4):
+// both sides hold a variable past kShareTop, so the sub-block's waves took the
+// separate form over all samples.  Lanes that do not call it count as below.
+__device__ inline bool both_far(double ti, double tj) {
+  const uint64_t i = __ballot(!(ti <= kShareTop));
+  const uint64_t j = __ballot(!(tj <= kShareTop));
+  const int at = threadIdx.x & 48;
+  return ((i >> at) & 0xffff) != 0 && ((j >> at) & 0xffff) != 0;
+}
+
 // R(si, sj) from the pair kernels' sums over all samples: s[0], s[1] of the
-// residual of si on sj, s[2], s[3] of sj on si.  diag: a pair of one 4 x 4
-// sub-block of the all-pairs kernel, whose sums are complete.
+// residual of si on sj, s[2], s[3] of sj on si.  whole: the sums leave nothing
+// out (a sub-block of the all-pairs kernel on the diagonal, or both_far).
 __device__ inline double measure_from_sums(const JobDev& J, int si, int sj,
-                                           const double (&s)[4], bool diag = false) {
+                                           const double (&s)[4], bool whole) {
   const double inv_n = 1.0 / (double)J.n;
   double r = J.rho[(int64_t)si * J.d + sj];
   const double lim = 1.0 - kCollinear;
   r = r > lim ? lim : (r < -lim ? -lim : r);
   const double al = 1.0 / sqrt(1.0 - r * r);
-  double ui = 0.0, uj = 0.0;  // sums of either residual over the FP32 copies
-  if (shared_job(J) && !diag) {
-    const double zi = J.mom[(int64_t)si * 8 + kMomSum], zj = J.mom[(int64_t)sj * 8 + kMomSum];
-    ui = al * (zi - r * zj);
-    uj = al * (zj - r * zi);
-  }
+  // sums of either residual over the FP32 copies, where they were left out
+  const double zi = J.mom[(int64_t)si * 8 + kMomSum], zj = J.mom[(int64_t)sj * 8 + kMomSum];
+  const bool left_out = shared_job(J) && !whole;
+  const double ui = left_out ? al * (zi - r * zj) : 0.0;
+  const double uj = left_out ? al * (zj - r * zi) : 0.0;
   const double h_ij = entropy_from_moments((kLn2 * s[0] + ui) * inv_n, al * s[1] * inv_n);
   const double h_ji = entropy_from_moments((kLn2 * s[2] + uj) * inv_n, al * s[3] * inv_n);
   return (J.hm[sj] + h_ij) - (J.hm[si] + h_ji);
@@ -602,7 +618,8 @@ __device__ __forceinline__ void for_blocks_xcd(const int32_t* __restrict__ pre, 
 // Separate (pair_dir, one direction at a time): 7 VALU instructions and 2
 // v_exp_f32 an evaluation (see the header).  It holds for any data.  Its sum of
 // |u| log2(e) runs over kSumBlock samples at a time, from -kS1Start, so its
-// rounding stays that of values below 16.
+// rounding stays that of values below 16.  Its loop takes two blocks a turn: 170
+// instructions each, 187 with the next block's rows moved into place.
 //
 // Shared (pair_both, both directions of a pair at once): 12 VALU and 3
 // v_exp_f32 for the two evaluations.
@@ -610,12 +627,14 @@ __device__ __forceinline__ void for_blocks_xcd(const int32_t* __restrict__ pre, 
 //     log2(e): no |u|, whose sum would cost an instruction.  sum u over all
 //     samples follows from the rows' sums, which are kept with the moments (of
 //     the FP32 copies: next to 0, but their rounding would otherwise count), so
-//     this form leaves it out and measure_from_sums adds it; a wave of such a
-//     job that takes the separate form takes its range's share out.  P = prod
+//     this form leaves it out and measure_from_sums adds it (not for a sub-block
+//     with variables past kShareTop on both sides: no wave of it takes this form,
+//     and the rows need not be read again for each range's share of the sum, which
+//     made 512 x 16384 samples of t4 noise 290 ms for 249).  P = prod
 //     (1 + 2^m) is unbounded then: every kRenorm samples its exponent is moved
 //     to an integer, which is exact and needs no log in the loop, and a P that
-//     has overflowed is noticed there; the wave then measures its pairs again
-//     in the separate form.
+//     has overflowed is noticed there; the wave then measures its range again
+//     in the separate form and takes the share of its signed sum out.
 //   * u^2 + y^2 = w^2 + x^2 for the residuals u = (x - rho y) alpha and w =
 //     (y - rho x) alpha: with E = e^{(x^2 - u^2) / 2} and the stored g = e^{-z^2
 //     / 2}, e^{-u^2 / 2} = E g(x) and e^{-w^2 / 2} = E g(y): one exponential
@@ -665,7 +684,6 @@ __device__ __forceinline__ void exp_done() {
   __builtin_amdgcn_s_setprio(0);
 }
 
-constexpr double kShareTop = 13.0;  // largest |x| of the shared form's x side
 constexpr int kRenorm = 16;         // samples per lane between renormalisations
 // most samples per lane of the shared form: the exponents of P and Q share a
 // 32-bit register, 16 bits each, and add at most 254 every kRenorm samples
@@ -785,28 +803,7 @@ __device__ __forceinline__ void pair_dir(const JobDev& J, const PairWave& w, int
   pair_rows(J, J.z, dir == 0 ? w.sj : w.si, zx);
   // each lane lost 1.5 a sample, of which the log2 of the halved cosh accounts
   // for 1
-  double bias = 32.0 * (double)w.nk;
-  if (shared_job(J) && !w.diag) {
-    // the other waves of this pair may take the shared form, whose sums leave
-    // out the signed residuals': take this range's out too (al (sum of a - rho
-    // sum of c), the eight rows summed in FP64 by eight lanes each)
-    const float4* z = reinterpret_cast<const float4*>(J.z + (int64_t)w.row * J.ldz + w.s_begin) +
-                      (w.lane & 7);
-    double v = 0.0;
-#pragma unroll 8
-    for (int k = 0; k < 2 * w.nk; ++k) {
-      const float4 f = z[8 * k];
-      v += ((double)f.x + (double)f.y) + ((double)f.z + (double)f.w);
-    }
-#pragma unroll
-    for (int off = 4; off >= 1; off >>= 1) v += __shfl_xor(v, off);
-    const int a = (w.lane >> 3) & 3, c = (w.lane >> 1) & 3;
-    const double sa = __shfl(v, dir == 0 ? a * 8 : 32 + a * 8);
-    const double sc = __shfl(v, dir == 0 ? 32 + c * 8 : c * 8);
-    const int from = dir == 0 ? a * 4 + c : c * 4 + a;
-    // w.lo = -2 log2(e) al to a float's precision
-    bias += 0.5 * (double)__shfl(w.lo, from) * (sa - (double)__shfl(w.r, from) * sc);
-  }
+  const double bias = 32.0 * (double)w.nk;
   float kr[16], kc[16];
 #pragma unroll
   for (int q = 0; q < 16; ++q) {
@@ -823,32 +820,28 @@ __device__ __forceinline__ void pair_dir(const JobDev& J, const PairWave& w, int
     A[q] = -kS1Start;
     S1[q] = S2[q] = 0.f;
   }
+  struct Rows {
+    float a[4], c[4];
+  };
   uint32_t voff = (uint32_t)(w.s_begin + w.lane) * 4u;
-  float xa[4], xb[4];
-#pragma unroll
-  for (int a = 0; a < 4; ++a) {
-    xa[a] = *(gfloat_t*)(zr[a] + voff);
-    xb[a] = *(gfloat_t*)(zx[a] + voff);
-  }
-  int kb = 0;
-  for (int k = 0; k < w.nk; ++k) {
-    // prefetch the next sample of every row; on the last iteration the stride
-    // is 0 and the current sample is re-read (always in bounds, no branch)
-    const bool more = k + 1 < w.nk;
-    voff += more ? 256u : 0u;
-    float na[4], nb[4];
+  const uint32_t vlast = voff + (uint32_t)(w.nk - 1) * 256u;
+  auto load = [&](Rows& x) {  // past the last block: the last one again
+    const uint32_t v = voff < vlast ? voff : vlast;
 #pragma unroll
     for (int a = 0; a < 4; ++a) {
-      na[a] = *(gfloat_t*)(zr[a] + voff);
-      nb[a] = *(gfloat_t*)(zx[a] + voff);
+      x.a[a] = *(gfloat_t*)(zr[a] + v);
+      x.c[a] = *(gfloat_t*)(zx[a] + v);
     }
+    voff += 256u;
+  };
+  auto eval = [&](const Rows& x) {
 #pragma unroll
     for (int a = 0; a < 4; ++a) {
       float t[4], m1[4], e1[4], e2[4];
 #pragma unroll
       for (int c = 0; c < 4; ++c) {
         const int q = a * 4 + c;
-        t[c] = fmaf(-kr[q], xb[c], xa[a]);
+        t[c] = fmaf(-kr[q], x.c[c], x.a[a]);
         m1[c] = kc[q] * fabsf(t[c]);
         e2[c] = (kM2 * m1[c]) * m1[c];
       }
@@ -868,23 +861,54 @@ __device__ __forceinline__ void pair_dir(const JobDev& J, const PairWave& w, int
       }
       __builtin_amdgcn_sched_barrier(0);
     }
-    if (++kb == kSumBlock || !more) {
-      const float off = 1.5f * (float)kb - kS1Start;  // exact
-#pragma unroll
-      for (int q = 0; q < 16; ++q) {
-        S1[q] += (A[q] - off) + __builtin_amdgcn_logf(P[q]);
-        P[q] = 1.f;
-        A[q] = -kS1Start;
-      }
-      kb = 0;
+  };
+  // two blocks a turn, each loaded while the other is evaluated
+  Rows r0, r1;
+  load(r0);
+  for (int left = w.nk; left > 0; left -= kSumBlock) {
+    const int cnt = left < kSumBlock ? left : kSumBlock;
+    for (int k = 0; k + 1 < cnt; k += 2) {
+      load(r1);
+      eval(r0);
+      load(r0);
+      eval(r1);
     }
+    if (cnt & 1) eval(r0);  // the last block of the range (kSumBlock is even)
+    const float off = 1.5f * (float)cnt - kS1Start;  // exact
 #pragma unroll
-    for (int a = 0; a < 4; ++a) {
-      xa[a] = na[a];
-      xb[a] = nb[a];
+    for (int q = 0; q < 16; ++q) {
+      S1[q] += (A[q] - off) + __builtin_amdgcn_logf(P[q]);
+      P[q] = 1.f;
+      A[q] = -kS1Start;
     }
   }
   pair_store(w, S1, S2, bias, dir == 1, dir == 1);
+}
+
+// The sums that pair_dir stored made those of the shared form, which leave out the
+// signed residuals' share of the range: al (sum of a - rho sum of c) of either
+// direction, the eight rows summed in FP64 by eight lanes each.
+__device__ __forceinline__ void pair_part(const JobDev& J, const PairWave& w) {
+  const float4* z = reinterpret_cast<const float4*>(J.z + (int64_t)w.row * J.ldz + w.s_begin) +
+                    (w.lane & 7);
+  double v = 0.0;
+#pragma unroll 8
+  for (int k = 0; k < 2 * w.nk; ++k) {
+    const float4 f = z[8 * k];
+    v += ((double)f.x + (double)f.y) + ((double)f.z + (double)f.w);
+  }
+#pragma unroll
+  for (int off = 4; off >= 1; off >>= 1) v += __shfl_xor(v, off);
+  const int a = (w.lane >> 3) & 3, c = (w.lane >> 1) & 3;  // the walk of pair_store
+#pragma unroll
+  for (int dir = 0; dir < 2; ++dir) {
+    const int q = dir == 0 ? a * 4 + c : c * 4 + a;
+    const double sa = __shfl(v, dir == 0 ? a * 8 : 32 + a * 8);
+    const double sc = __shfl(v, dir == 0 ? 32 + c * 8 : c * 8);
+    // w.lo = -2 log2(e) al to a float's precision
+    const double share = 0.5 * (double)__shfl(w.lo, q) * (sa - (double)__shfl(w.r, q) * sc);
+    if (w.lane < 32 && (w.lane & 1) == 0) w.out[q * 4 + dir * 2] += share;  // its own store
+  }
 }
 
 // Both residual directions, the shared form; side 0 takes the i variables as
@@ -1063,12 +1087,15 @@ __device__ __forceinline__ void pair_item(const JobDev& J, const JobStep& S, int
     w.si[a] = __builtin_amdgcn_readlane(w.row, a * 8);
     w.sj[a] = __builtin_amdgcn_readlane(w.row, 32 + a * 8);
   }
-  if (!w.diag && shared_job(J) && w.nk <= kShareMaxIters) {
-    // does either side (i: the lower lanes) reach past kShareTop?
+  bool partial = false;  // the shared form holds, but not over this range
+  if (!w.diag && shared_job(J)) {
+    // does either side (i: the lower lanes) reach past kShareTop?  The combining
+    // kernels ask the same of the whole sub-block (both_far)
     const double top = w.row < J.d ? J.mom[(int64_t)w.row * 8 + kMomTop] : 0.0;
     const uint64_t far = __ballot(!(top <= kShareTop));
     const int side = (uint32_t)far == 0 ? 0 : (far >> 32 == 0 ? 1 : -1);
-    if (side >= 0 && pair_both(J, w, side)) return;
+    partial = side >= 0;
+    if (partial && w.nk <= kShareMaxIters && pair_both(J, w, side)) return;
   }
   // A quadrant on the diagonal has the same variables on both sides, so its
   // direction-0 walk (a, c) with a != c already holds both residual
@@ -1076,6 +1103,7 @@ __device__ __forceinline__ void pair_item(const JobDev& J, const JobStep& S, int
   const int ndir = w.diag ? 1 : 2;
 #pragma clang loop unroll(disable)
   for (int dir = 0; dir < ndir; ++dir) pair_dir(J, w, dir);
+  if (partial) pair_part(J, w);
 }
 
 }  // namespace

@@ -462,7 +462,9 @@ __global__ __launch_bounds__(256) void k_combine(const JobDev* __restrict__ jobs
 #pragma unroll
     for (int c = 0; c < 4; ++c) s[c] += src[c];
   }
-  const double Rv = measure_from_sums(J, J.act[pi], J.act[pj], s, bi == bj && wi == wj);
+  // off the diagonal every pair without padding is here
+  const bool whole = both_far(top_at(J, m, pi), top_at(J, m, pj)) || (bi == bj && wi == wj);
+  const double Rv = measure_from_sums(J, J.act[pi], J.act[pj], s, whole);
   J.rmat[(int64_t)pi * J.d + pj] = Rv;
   J.rmat[(int64_t)pj * J.d + pi] = -Rv;
   });

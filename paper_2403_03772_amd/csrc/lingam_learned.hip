@@ -788,8 +788,9 @@ __global__ __launch_bounds__(256) void k_combine_cand(const JobDev* __restrict__
   const int m = S.m;
   const int ci = bi * kTileVars + wi * kWaveVars + (q >> 2);
   const int pj = bj * kTileVars + wj * kWaveVars + (q & 3);
-  if (pj >= m) return;
   const int pi = J.cand[ci];
+  const bool whole = both_far(top_at(J, m, pi), top_at(J, m, pj));
+  if (pj >= m) return;
   double* out = J.rc + (int64_t)ci * J.d + pj;
   if (pi == pj) {
     *out = 0.0;
@@ -801,7 +802,7 @@ __global__ __launch_bounds__(256) void k_combine_cand(const JobDev* __restrict__
 #pragma unroll
     for (int c = 0; c < 4; ++c) s[c] += src[c];
   }
-  *out = measure_from_sums(J, J.act[pi], J.act[pj], s);
+  *out = measure_from_sums(J, J.act[pi], J.act[pj], s, whole);
 }
 
 // Exact k of every candidate (kc[c] = sum_j min(0, R(c, j))^2, one wave per
@@ -1119,10 +1120,17 @@ __global__ __launch_bounds__(256) void k_ext_bound(const JobDev* __restrict__ jo
     int wl[kWit];
 #pragma unroll
     for (int q = 0; q < kWit; ++q) wl[q] = J.wit[(int64_t)l * kWit + q];
+    // measured over all samples in the separate form: variables far out among the
+    // suspects of l's sub-block and among the columns of e's (four lanes)
+    const int by = J.cand2[(ci & ~3) + (lane & 3)];  // m past nsus
+    const bool far_l = __any(!(top_at(J, S.m, by) <= kShareTop));
     double acc = 0.0;
-    for (int e = lane; e < S.ne; e += 64) {
-      const int j = J.ext[e];
-      bool skip = j == l;
+    for (int e0 = 0; e0 < S.ne; e0 += 64) {
+      const int e = e0 + lane;
+      const int j = e < S.ne ? J.ext[e] : S.m;
+      const uint64_t far_j = __ballot(!(top_at(J, S.m, j) <= kShareTop));
+      const bool whole = far_l && ((far_j >> (lane & 60)) & 15) != 0;
+      bool skip = j == l || j >= S.m;
 #pragma unroll
       for (int q = 0; q < kWit; ++q) skip |= j == wl[q];
       if (skip) continue;
@@ -1136,7 +1144,7 @@ __global__ __launch_bounds__(256) void k_ext_bound(const JobDev* __restrict__ jo
 #pragma unroll
         for (int c = 0; c < 4; ++c) sm[c] += src[c];
       }
-      const double R = measure_from_sums(J, sl, J.act[j], sm);
+      const double R = measure_from_sums(J, sl, J.act[j], sm, whole);
       if (R < 0.0) acc += R * R;
     }
 #pragma unroll
@@ -1232,8 +1240,9 @@ __global__ __launch_bounds__(256) void k_combine_susp(const JobDev* __restrict__
     const int m = S.m;
     const int ci = bi * kTileVars + wi * kWaveVars + (q >> 2);
     const int pj = bj * kTileVars + wj * kWaveVars + (q & 3);
+    const int pi = J.cand2[ci];  // m past nsus
+    const bool whole = both_far(top_at(J, m, pi), top_at(J, m, pj));
     if (ci >= S.nsus || pj >= m) return;
-    const int pi = J.cand2[ci];
     double* out = J.rc2 + (int64_t)ci * J.d + pj;
     if (pi == pj) {
       *out = 0.0;
@@ -1245,7 +1254,7 @@ __global__ __launch_bounds__(256) void k_combine_susp(const JobDev* __restrict__
 #pragma unroll
       for (int c = 0; c < 4; ++c) sm[c] += src[c];
     }
-    *out = measure_from_sums(J, J.act[pi], J.act[pj], sm);
+    *out = measure_from_sums(J, J.act[pi], J.act[pj], sm, whole);
   });
 }
 
