@@ -324,7 +324,7 @@ StepTotals step_totals(const std::vector<HostJob>& jobs, const Plan& P, int t, l
     pairs += lg::pairs64(js[k]);
   }
   for (int k = 0; k < P.njobs; ++k) {
-    lg::job_split(js[k], (int32_t)P.L[k].n_pad, items, P.cu, tu);
+    lg::job_split(js[k], (int32_t)P.L[k].n_pad, items, P.cu, tu, P.L[k].g != 0 && ties);
     lg::job_split_cand(js[k], (int32_t)P.L[k].n_pad, items_c, P.cu, tu, ties);
     lg::job_split64(js[k], pairs, P.cu);
     for (int kind = 0; kind < lg::kNumKinds; ++kind)

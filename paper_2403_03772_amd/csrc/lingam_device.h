@@ -690,12 +690,12 @@ constexpr int kRenorm = 16;         // samples per lane between renormalisations
 constexpr int kShareMaxIters = 4096;
 
 template <int kMode, int W>
-__device__ __forceinline__ void pair_item(const JobDev& J, const JobStep& S, int local,
+__device__ __forceinline__ void pair_item(const JobDev& J, const JobStep& S, int local, int half,
                                           int wave, int lane);
 
-// W waves per workgroup (1, 2 or 4): every (tile, split) item is cut into
-// 4 / W consecutive workgroup items, and the wave's quadrant of the tile is
-// (workgroup item mod 4 / W) * W + its wave in the workgroup.
+// W waves per workgroup (1, 2 or 4): every (tile, split) item of item_dirs halves is
+// cut into 4 / W consecutive workgroup items a half, and the wave's quadrant of the
+// tile is (workgroup item mod 4 / W) * W + its wave in the workgroup.
 template <int kMode, bool kLoop, int W>
 __device__ __forceinline__ void pair_tiles(const JobDev* __restrict__ jobs, int njobs,
                                            const JobStep* __restrict__ js,
@@ -710,8 +710,8 @@ __device__ __forceinline__ void pair_tiles(const JobDev* __restrict__ jobs, int 
   const int b = blockIdx.x;
   const int p = xcd_item(b, G);
   auto run = [&](int jb, int local) {
-    const int item = local / kQ;
-    pair_item<kMode, W>(jobs[jb], js[jb], item, (local - item * kQ) * W + lw, lane);
+    const PairItem it = pair_item_at(local, kQ, shared_job(jobs[jb]));
+    pair_item<kMode, W>(jobs[jb], js[jb], it.item, it.half, it.part * W + lw, lane);
   };
   int jb, local;
   if (!kLoop) {  // the grid is the schedule: one item per workgroup
@@ -1018,7 +1018,7 @@ __device__ __forceinline__ bool pair_both(const JobDev& J, const PairWave& w, in
 }
 
 template <int kMode, int W>
-__device__ __forceinline__ void pair_item(const JobDev& J, const JobStep& S, int local,
+__device__ __forceinline__ void pair_item(const JobDev& J, const JobStep& S, int local, int half,
                                           int wave, int lane) {
   constexpr bool kCand = kMode != kModeAll;
   const int m = S.m;
@@ -1100,9 +1100,9 @@ __device__ __forceinline__ void pair_item(const JobDev& J, const JobStep& S, int
   // A quadrant on the diagonal has the same variables on both sides, so its
   // direction-0 walk (a, c) with a != c already holds both residual
   // directions of each of its 6 pairs.
-  const int ndir = w.diag ? 1 : 2;
+  const int end = w.diag || (half == 0 && !shared_job(J)) ? 1 : 2;  // half: one direction
 #pragma clang loop unroll(disable)
-  for (int dir = 0; dir < ndir; ++dir) pair_dir(J, w, dir);
+  for (int dir = half; dir < end; ++dir) pair_dir(J, w, dir);
   if (partial) pair_part(J, w);
 }
 

@@ -256,7 +256,8 @@ struct JobStep {
   int32_t k;          // candidates of this step's learned pass
   int32_t ne;         // extension columns (set with the suspect plan)
   int32_t nct3;       // extension tiles ceil(nsus / 8) * ceil(ne / 8)
-  int32_t q_all;      // workgroups per tile item of the all-pairs kernel (4 / w_all)
+  int32_t q_all;      // workgroups per tile and split of the all-pairs kernel (4 / w_all, a
+                      // direction each or for both)
   int32_t q_rows;     // ... of the learned row kernels (4 / w_rows)
   int32_t w64;        // waves per pair of the FP64 pair kernel (1, 2 or 4)
 };
@@ -416,11 +417,28 @@ __host__ __device__ inline void split_for(int64_t items_total, int32_t n_pad, in
   nsplit = (int32_t)((iters + per - 1) / per);
 }
 
+// Work items of a tile and sample split: both residual directions in one where the
+// job may take the shared form, one each where it may not, or its passes of few rows
+// have half the workgroups, twice as long (learned order of 512 x 8192 under
+// fp32_ties: 115 ms with both directions in one, 89 with one each).
+__host__ __device__ inline int32_t item_dirs(bool shared) { return shared ? 1 : 2; }
+
+// Workgroup `local` of a job's pair pass, `parts` of them for a tile's quadrants.
+struct PairItem {
+  int32_t item;  // tile and split
+  int32_t half;  // direction (0 where an item holds both)
+  int32_t part;  // quadrants
+};
+__host__ __device__ inline PairItem pair_item_at(int32_t local, int32_t parts, bool shared) {
+  const int32_t at = local / parts, two = item_dirs(shared) - 1;
+  return PairItem{at >> two, at & two, local % parts};
+}
+
 // Split of one FP32-path job given the batch's number of (tile, direction) items.
 __host__ __device__ inline void job_split(JobStep& s, int32_t n_pad, int64_t items_total,
-                                          int32_t num_cu, Tune tu) {
-  s.q_all = valid_waves(tu.w_all) ? 4 / tu.w_all : 1;
-  s.q_rows = valid_waves(tu.w_rows) ? 4 / tu.w_rows : 1;
+                                          int32_t num_cu, Tune tu, bool shared = true) {
+  s.q_all = (valid_waves(tu.w_all) ? 4 / tu.w_all : 1) * item_dirs(shared);
+  s.q_rows = (valid_waves(tu.w_rows) ? 4 / tu.w_rows : 1) * item_dirs(shared);
   if (s.m < 2 || s.fp64) return;
   split_for(items_total, n_pad, num_cu, tu, s.nsplit, s.split_len);
 }

@@ -101,7 +101,7 @@ __device__ void step_schedule_wave(const JobDev* __restrict__ jobs, int njobs, i
   }
   if (lane < njobs) {
     const JobDev& J = jobs[lane];
-    job_split(s, J.n_pad, items, num_cu, tu);
+    job_split(s, J.n_pad, items, num_cu, tu, shared_job(J));
     job_split_cand(s, J.n_pad, items_c, num_cu, tu, J.tie_on != 0);
     job_split64(s, pairs, num_cu);
     if (wave == 0) js[lane] = s;
@@ -145,7 +145,7 @@ __device__ void step_schedule(const JobDev* __restrict__ jobs, int njobs, int t,
   for (int j = tid; j < njobs; j += 1024) {
     JobStep s = js[j];
     const JobDev& J = jobs[j];
-    job_split(s, J.n_pad, items, num_cu, tu);
+    job_split(s, J.n_pad, items, num_cu, tu, shared_job(J));
     job_split_cand(s, J.n_pad, items_c, num_cu, tu, J.tie_on != 0);
     job_split64(s, pairs, num_cu);
     js[j] = s;
