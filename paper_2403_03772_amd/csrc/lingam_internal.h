@@ -28,10 +28,13 @@ constexpr int kTileVars = 8;
 constexpr int kWaveVars = 4;
 // Samples are padded to a multiple of this (one wavefront of samples).
 constexpr int kSampleQuantum = 64;
-// The bounded grids of the gated full step and of the suspect and extension
-// passes launch kPairWavesPerCu / w workgroups of w waves per CU (the pair
-// kernels hold 12 waves a CU: 3 a SIMD by their registers).
-constexpr int kPairWavesPerCu = 16;
+// Waves a SIMD that the pair kernels are compiled for (up to 168 registers).  The
+// bounded grids of the gated full step and of the suspect and extension passes
+// launch as many workgroups as are resident then: their static chunks run in one
+// round, where a fourth workgroup a CU waits for the first three to end (k_pair_susp
+// at 512 x 8192 with t4 noise: 56 us, 39 so).
+constexpr int kPairWavesPerSimd = 3;
+constexpr int kPairWavesPerCu = 4 * kPairWavesPerSimd;
 // Steps with at most this many active variables run the FP64 pair kernel.
 constexpr int kFp64MaxM = 64;
 // Most aggressive split policy the workspace is sized for (see Tune).

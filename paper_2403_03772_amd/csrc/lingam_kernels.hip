@@ -421,20 +421,18 @@ __global__ __launch_bounds__(256) void k_standardize(const JobDev* __restrict__ 
 // ---------------------------------------------------------------------------
 
 template <int W>
-__global__ __launch_bounds__(64 * W, 3) void k_pair(const JobDev* __restrict__ jobs, int njobs,
-                                                 const JobStep* __restrict__ js,
-                                                 const int32_t* __restrict__ pre, int G) {
+__global__ __launch_bounds__(64 * W, kPairWavesPerSimd) void k_pair(
+    const JobDev* __restrict__ jobs, int njobs, const JobStep* __restrict__ js,
+    const int32_t* __restrict__ pre, int G) {
   pair_tiles<kModeAll, false, W>(jobs, njobs, js, pre, G);
 }
 
 // The same kernel for gated launches (learned form): a bounded grid walks the
 // step's items.
 template <int W>
-__global__ __launch_bounds__(64 * W, 3) void k_pair_loop(const JobDev* __restrict__ jobs,
-                                                         int njobs,
-                                                         const JobStep* __restrict__ js,
-                                                         const int32_t* __restrict__ pre,
-                                                         int G) {
+__global__ __launch_bounds__(64 * W, kPairWavesPerSimd) void k_pair_loop(
+    const JobDev* __restrict__ jobs, int njobs, const JobStep* __restrict__ js,
+    const int32_t* __restrict__ pre, int G) {
   pair_tiles<kModeAll, true, W>(jobs, njobs, js, pre, G);
 }
 

@@ -604,9 +604,9 @@ __global__ __launch_bounds__(1024) void k_topk(const JobDev* __restrict__ jobs, 
 // ---------------------------------------------------------------------------
 
 template <int W>
-__global__ __launch_bounds__(64 * W, 3) void k_pair_cand(const JobDev* __restrict__ jobs, int njobs,
-                                                      const JobStep* __restrict__ js,
-                                                      const int32_t* __restrict__ pre, int G) {
+__global__ __launch_bounds__(64 * W, kPairWavesPerSimd) void k_pair_cand(
+    const JobDev* __restrict__ jobs, int njobs, const JobStep* __restrict__ js,
+    const int32_t* __restrict__ pre, int G) {
   pair_tiles<kModeCand, false, W>(jobs, njobs, js, pre, G);
 }
 
@@ -1084,20 +1084,16 @@ __global__ __launch_bounds__(1024) void k_susp_schedule(const JobDev* __restrict
 // The bounded-grid pair kernels (suspect and extension rows) walk their items
 // in a loop.
 template <int W>
-__global__ __launch_bounds__(64 * W, 3) void k_pair_susp(const JobDev* __restrict__ jobs,
-                                                         int njobs,
-                                                         const JobStep* __restrict__ js,
-                                                         const int32_t* __restrict__ pre,
-                                                         int G) {
+__global__ __launch_bounds__(64 * W, kPairWavesPerSimd) void k_pair_susp(
+    const JobDev* __restrict__ jobs, int njobs, const JobStep* __restrict__ js,
+    const int32_t* __restrict__ pre, int G) {
   pair_tiles<kModeSusp, true, W>(jobs, njobs, js, pre, G);
 }
 
 template <int W>
-__global__ __launch_bounds__(64 * W, 3) void k_pair_ext(const JobDev* __restrict__ jobs,
-                                                        int njobs,
-                                                        const JobStep* __restrict__ js,
-                                                        const int32_t* __restrict__ pre,
-                                                        int G) {
+__global__ __launch_bounds__(64 * W, kPairWavesPerSimd) void k_pair_ext(
+    const JobDev* __restrict__ jobs, int njobs, const JobStep* __restrict__ js,
+    const int32_t* __restrict__ pre, int G) {
   pair_tiles<kModeExt, true, W>(jobs, njobs, js, pre, G);
 }
 
