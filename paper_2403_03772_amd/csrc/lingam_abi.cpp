@@ -307,6 +307,7 @@ std::vector<lg::JobDev> device_jobs(const Plan& P, const std::vector<HostJob>& j
 struct StepTotals {
   int32_t g[lg::kNumKinds] = {0};
   double pair_evals = 0.0, resid_bytes = 0.0, cand_evals = 0.0;
+  int64_t n64_lo = INT64_MAX, n64_hi = 0;  // samples of the FP64-path jobs
 };
 
 // `ties`: the FP64 resolution of near-ties is on (the learned passes then
@@ -321,7 +322,12 @@ StepTotals step_totals(const std::vector<HostJob>& jobs, const Plan& P, int t, l
     js[k] = lg::job_step_base((int32_t)jobs[k].d, t, K, P.lc.min_m, jobs[k].record != nullptr);
     if (js[k].m >= 2 && !js[k].fp64) items += 2LL * js[k].ntiles;
     if (js[k].learned) items_c += 2LL * js[k].nct;
-    pairs += lg::pairs64(js[k]);
+    const int64_t p64 = lg::pairs64(js[k]);
+    pairs += p64;
+    if (p64 > 0) {
+      T.n64_lo = std::min(T.n64_lo, jobs[k].n);
+      T.n64_hi = std::max(T.n64_hi, jobs[k].n);
+    }
   }
   for (int k = 0; k < P.njobs; ++k) {
     lg::job_split(js[k], (int32_t)P.L[k].n_pad, items, P.cu, tu, P.L[k].g != 0 && ties);
@@ -464,7 +470,9 @@ int enqueue_steps(const Plan& P, const std::vector<HostJob>& jobs, char* ws, hip
       LG_TRY(lg::launch_combine(table, P.njobs, sc, capped(T.g[lg::kKComb], 8), st),
              "combine");
     }
-    LG_TRY(lg::launch_pair64(table, P.njobs, sc, T.g[lg::kKP64], st), "pair64");
+    LG_TRY(lg::launch_pair64(table, P.njobs, sc, T.g[lg::kKP64],
+                             T.n64_hi > 0 && lg::xcd_ranges64(T.n64_lo, T.n64_hi), st),
+           "pair64");
     LG_TRY(lg::launch_rowk(table, P.njobs, sc, capped(T.g[lg::kKRowk], 8), st), "rowk");
     const lg::NextStep next{sched_of(P, ws, t + 1), P.cu, tu};
     LG_TRY(lg::launch_select(table, P.njobs, t, sc, T.g[lg::kKSel],

@@ -580,13 +580,6 @@ __device__ __forceinline__ void for_blocks(const int32_t* __restrict__ pre, int 
   }
 }
 
-// Item of workgroup b of g when every XCD is to get a contiguous range of them:
-// workgroups are dispatched round-robin over the 8 XCDs.  A permutation of 0 .. g - 1.
-__device__ __forceinline__ int xcd_item(int b, int g) {
-  const int Q = g >> 3, R = g & 7, x = b & 7;
-  return x * Q + (x < R ? x : R) + (b >> 3);
-}
-
 // for_blocks with neighbouring items on one XCD, so that their rows are shared in
 // its L2.
 template <typename F>

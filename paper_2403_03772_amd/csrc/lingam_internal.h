@@ -446,6 +446,22 @@ __host__ __device__ inline void job_split(JobStep& s, int32_t n_pad, int64_t ite
   split_for(items_total, n_pad, num_cu, tu, s.nsplit, s.split_len);
 }
 
+// Item of workgroup b of g when every XCD is to get a contiguous range of them:
+// workgroups are dispatched round-robin over the 8 XCDs.  A permutation of 0 .. g - 1.
+__host__ __device__ inline int xcd_item(int b, int g) {
+  const int Q = g >> 3, R = g & 7, x = b & 7;
+  return x * Q + (x < R ? x : R) + (b >> 3);
+}
+
+// Whether the FP64 pair kernel gives every XCD a range of its items, for jobs of
+// n_lo to n_hi samples.  The ranges hold equal numbers of items, and an item is as
+// long as its job: 50 resamples of 50 x 1000 take 6.61 ms without ranges and 6.47
+// with, but 64 jobs of 30 to 64 variables, one in eight of 20000 samples and the
+// others of 500, 21.1 without and 29.4 with; 40 jobs of 500 to 5000 samples 7.2 and 7.9.
+__host__ __device__ inline bool xcd_ranges64(int64_t n_lo, int64_t n_hi) {
+  return n_hi * 10 <= n_lo * 11;
+}
+
 // Waves per pair of one FP64-path job given the batch's number of such pairs:
 // with a wave a pair the last steps leave most of the device idle behind a few
 // long waves, so as many as keep the waves at 4 per SIMD, up to a workgroup.
@@ -583,7 +599,9 @@ hipError_t launch_gate_schedule(const JobDev* jobs, int njobs, SchedDev sc, hipS
 hipError_t launch_pair(const JobDev* jobs, int njobs, SchedDev sc, int grid, int waves,
                        hipStream_t st, bool loop = false);
 hipError_t launch_combine(const JobDev* jobs, int njobs, SchedDev sc, int grid, hipStream_t st);
-hipError_t launch_pair64(const JobDev* jobs, int njobs, SchedDev sc, int grid, hipStream_t st);
+// ranges: xcd_ranges64 of the step's FP64-path jobs.
+hipError_t launch_pair64(const JobDev* jobs, int njobs, SchedDev sc, int grid, bool ranges,
+                         hipStream_t st);
 hipError_t launch_rowk(const JobDev* jobs, int njobs, SchedDev sc, int grid, hipStream_t st);
 // next: where to plan step t + 1 (NULL: no further step).
 struct NextStep {

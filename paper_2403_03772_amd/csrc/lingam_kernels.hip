@@ -473,16 +473,17 @@ __global__ __launch_bounds__(256) void k_combine(const JobDev* __restrict__ jobs
 // pairs a workgroup, lanes over samples, the waves' sums added in order; writes
 // R(i,j) and R(j,i) = -R(i,j).  About 63 FP64 instructions a sample and pair, 48
 // of them the four exponentials, at 5.3 cycles each, and 25 others: bound by
-// their issue once the device is full (samples are fetched a block ahead, a job's
-// pairs lie on one XCD).  First step of 50 jobs of 50 x 1000: 271 -> 243 us with
+// their issue once the device is full (samples are fetched a block ahead; kRanges: a
+// job's pairs lie on one XCD).  First step of 50 jobs of 50 x 1000: 271 -> 243 us with
 // the table's exponential (90 FP64 instructions before), of 10 x 10000: 105 -> 90.
+template <bool kRanges>
 __global__ __launch_bounds__(256) void k_pair64(const JobDev* __restrict__ jobs, int njobs,
                                                 const JobStep* __restrict__ js,
                                                 const int32_t* __restrict__ pre) {
   __shared__ double part[4][4], tab[kExpTable];
   stage_exp(tab);
   __syncthreads();
-  for_blocks_xcd(pre, njobs, [&](int jb, int lb) {
+  auto measure = [&](int jb, int lb) {
   const JobDev& J = jobs[jb];
   const int m = js[jb].m, W = js[jb].w64;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -515,7 +516,9 @@ __global__ __launch_bounds__(256) void k_pair64(const JobDev* __restrict__ jobs,
     J.rmat[(int64_t)pi * J.d + pj] = Rv;
     J.rmat[(int64_t)pj * J.d + pi] = -Rv;
   }
-  });
+  };
+  if (kRanges) for_blocks_xcd(pre, njobs, measure);
+  else for_blocks(pre, njobs, measure);
 }
 
 // k_p = sum_{q != p} min(0, R(p, q))^2 by one wave; mvec[p] = -k_p.
@@ -1370,10 +1373,11 @@ hipError_t launch_combine(const JobDev* jobs, int njobs, SchedDev sc, int grid, 
   return hipGetLastError();
 }
 
-hipError_t launch_pair64(const JobDev* jobs, int njobs, SchedDev sc, int grid, hipStream_t st) {
+hipError_t launch_pair64(const JobDev* jobs, int njobs, SchedDev sc, int grid, bool ranges,
+                         hipStream_t st) {
   if (grid <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_pair64, dim3((unsigned)grid), dim3(256), 0, st, jobs, njobs,
-                     (const JobStep*)sc.js, pre_of(sc, njobs, kKP64));
+  hipLaunchKernelGGL(ranges ? k_pair64<true> : k_pair64<false>, dim3((unsigned)grid), dim3(256),
+                     0, st, jobs, njobs, (const JobStep*)sc.js, pre_of(sc, njobs, kKP64));
   return hipGetLastError();
 }
 
