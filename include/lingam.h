@@ -98,7 +98,8 @@ typedef struct lingam_profile {
   double gram_ms;         /* duration of the Gram (correlation) kernel */
   double gram_flops;      /* algorithmic flops of that Gram: 2 * n * d * d */
   double resid_ms;        /* summed duration of the residualize kernels */
-  double resid_bytes;     /* algorithmic HBM bytes of those: 28 * n * (m - 1) per step */
+  double resid_bytes;     /* bytes those move: 32 n (m - 1) per step (28 in a workspace
+                             without the pair kernels' exponentials) */
   double cand_ms;         /* learned form: summed duration of the candidate, extension
                              and suspect-row pair kernels */
   int64_t cand_launches;  /* ... its launches */

@@ -351,7 +351,9 @@ StepTotals step_totals(const std::vector<HostJob>& jobs, const Plan& P, int t, l
       for (int kind = lg::kKPairE; kind <= lg::kKLsel2; ++kind)
         T.g[kind] += lg::kind_count(b, kind);
     }
-    if (m > 2) T.resid_bytes += 28.0 * (double)jobs[k].n * (double)(m - 1);
+    // FP64 residuals read and written, of the chosen variable read; FP32 copy and, if
+    // kept, exponential written
+    if (m > 2) T.resid_bytes += (P.L[k].g ? 32.0 : 28.0) * (double)jobs[k].n * (double)(m - 1);
   }
   return T;
 }
