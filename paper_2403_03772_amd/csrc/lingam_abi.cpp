@@ -181,6 +181,7 @@ struct Plan {
   int njobs = 0;
   int cu = 0;
   bool ahead = true;  // a step's selection plans the next step (two schedules)
+  bool share = true;  // with the regions of the pair kernels' shared form
   size_t table_off = 0, sched_off = 0, prop_off = 0, total = 0;
   std::vector<lg::Layout> L;
   std::vector<size_t> job_off;
@@ -198,6 +199,7 @@ Plan make_plan(const std::vector<HostJob>& jobs, int cu, const Learn& lc, int le
   P.cu = cu;
   P.lc = lc;
   P.ahead = lean < 2;
+  P.share = lean == 0;
   size_t off = 0;
   P.table_off = off;
   off = align256(off + sizeof(lg::JobDev) * (size_t)P.njobs);
@@ -208,7 +210,7 @@ Plan make_plan(const std::vector<HostJob>& jobs, int cu, const Learn& lc, int le
     off = align256(off + sizeof(lg::PropDev));
   }
   for (const HostJob& j : jobs) {
-    P.L.push_back(lg::make_layout(j.n, j.d, cu, lc.proposer ? lc.K : 0, lean == 0));
+    P.L.push_back(lg::make_layout(j.n, j.d, cu, lc.proposer ? lc.K : 0, P.share));
     P.job_off.push_back(off);
     off = align256(off + P.L.back().total);
     P.max_d = std::max(P.max_d, (int)j.d);
@@ -330,7 +332,7 @@ StepTotals step_totals(const std::vector<HostJob>& jobs, const Plan& P, int t, l
     }
   }
   for (int k = 0; k < P.njobs; ++k) {
-    lg::job_split(js[k], (int32_t)P.L[k].n_pad, items, P.cu, tu, P.L[k].g != 0 && ties);
+    lg::job_split(js[k], (int32_t)P.L[k].n_pad, items, P.cu, tu, P.share && ties);
     lg::job_split_cand(js[k], (int32_t)P.L[k].n_pad, items_c, P.cu, tu, ties);
     lg::job_split64(js[k], pairs, P.cu);
     for (int kind = 0; kind < lg::kNumKinds; ++kind)
@@ -353,7 +355,7 @@ StepTotals step_totals(const std::vector<HostJob>& jobs, const Plan& P, int t, l
     }
     // FP64 residuals read and written, of the chosen variable read; FP32 copy and, if
     // kept, exponential written
-    if (m > 2) T.resid_bytes += (P.L[k].g ? 32.0 : 28.0) * (double)jobs[k].n * (double)(m - 1);
+    if (m > 2) T.resid_bytes += (P.share ? 32.0 : 28.0) * (double)jobs[k].n * (double)(m - 1);
   }
   return T;
 }
@@ -404,7 +406,8 @@ int enqueue_steps(const Plan& P, const std::vector<HostJob>& jobs, char* ws, hip
                   lg::Tune tu, Prof* pf, bool ties) {
   lg::JobDev* table = reinterpret_cast<lg::JobDev*>(ws + P.table_off);
   // bounded grids: one workgroup of w waves per resident slot
-  auto resident = [&](int w) { return P.cu * (lg::kPairWavesPerCu / w); };
+  const bool shared = P.share && ties;
+  auto resident = [&](int w) { return P.cu * (lg::pair_waves_per_cu(shared) / w); };
   for (int t = 0; t + 1 < P.max_d; ++t) {
     const StepTotals T = step_totals(jobs, P, t, tu, ties);
     if (T.g[lg::kKSel] == 0) break;  // every job finished
@@ -415,7 +418,7 @@ int enqueue_steps(const Plan& P, const std::vector<HostJob>& jobs, char* ws, hip
       LG_TRY(lg::launch_learned_front(table, P.njobs, t, sc, T.g, st), "features / scores");
     if (T.g[lg::kKPairC] > 0) {
       if (pf && pf->tm.on) pf->cand_ev.push_back(pf->tm.take(st));
-      LG_TRY(lg::launch_pair_cand(table, P.njobs, sc, T.g[lg::kKPairC], tu.w_rows, st),
+      LG_TRY(lg::launch_pair_cand(table, P.njobs, sc, T.g[lg::kKPairC], tu.w_rows, shared, st),
              "pair cand");
       if (pf && pf->tm.on) pf->cand_ev.push_back(pf->tm.take(st));
       if (pf) pf->cand_evals += T.cand_evals;
@@ -435,7 +438,7 @@ int enqueue_steps(const Plan& P, const std::vector<HostJob>& jobs, char* ws, hip
         if (pf && pf->tm.on) pf->cand_ev.push_back(pf->tm.take(st));
         LG_TRY(lg::launch_pair_ext(table, P.njobs, sc,
                                    std::min<int32_t>(T.g[lg::kKPairE], resident(tu.w_rows)),
-                                   tu.w_rows, st),
+                                   tu.w_rows, shared, st),
                "pair ext");
         if (pf && pf->tm.on) pf->cand_ev.push_back(pf->tm.take(st));
         LG_TRY(lg::launch_ext_back(table, P.njobs, t, sc,
@@ -449,7 +452,7 @@ int enqueue_steps(const Plan& P, const std::vector<HostJob>& jobs, char* ws, hip
         if (pf && pf->tm.on) pf->cand_ev.push_back(pf->tm.take(st));
         LG_TRY(lg::launch_pair_susp(table, P.njobs, sc,
                                     std::min<int32_t>(T.g[lg::kKPairS], resident(tu.w_rows)),
-                                    tu.w_rows, st),
+                                    tu.w_rows, shared, st),
                "pair susp");
         if (pf && pf->tm.on) pf->cand_ev.push_back(pf->tm.take(st));
       }
@@ -465,7 +468,7 @@ int enqueue_steps(const Plan& P, const std::vector<HostJob>& jobs, char* ws, hip
       LG_TRY(lg::launch_pair(table, P.njobs, sc,
                              gated ? std::min<int32_t>(T.g[lg::kKPair], resident(tu.w_all))
                                    : T.g[lg::kKPair],
-                             tu.w_all, st, gated),
+                             tu.w_all, shared, st, gated),
              "pair");
       if (pf && pf->tm.on) pf->pair_ev.push_back(pf->tm.take(st));
       if (pf) pf->pair_evals += T.pair_evals;
@@ -599,9 +602,12 @@ int autotune(const Plan& P, const std::vector<HostJob>& jobs, char* ws, hipStrea
         LG_TRY(lg::launch_learned_front(table, P.njobs, t, sc, T.g, st), "tune front");
       const int a = tm.take(st);
       if (rows)
-        LG_TRY(lg::launch_pair_cand(table, P.njobs, sc, T.g[kind], c.w_rows, st), "tune cand");
+        LG_TRY(lg::launch_pair_cand(table, P.njobs, sc, T.g[kind], c.w_rows, P.share && ties,
+                                    st),
+               "tune cand");
       else
-        LG_TRY(lg::launch_pair(table, P.njobs, sc, T.g[kind], c.w_all, st), "tune pair");
+        LG_TRY(lg::launch_pair(table, P.njobs, sc, T.g[kind], c.w_all, P.share && ties, st),
+               "tune pair");
       ev.emplace_back(a, tm.take(st));
     }
     LG_TRY(hipStreamSynchronize(st), "tune sync");

@@ -653,7 +653,11 @@ __device__ __forceinline__ void for_blocks_xcd(const int32_t* __restrict__ pre, 
 //
 // Without FP64 tie resolution (tie_on 0) every kernel takes the separate
 // form, which gives a pair the same bits whatever tile it falls in.  So does a
-// job without the g region (a workspace too small for it).
+// job without the g region (a workspace too small for it).  These calls run
+// kernels without the shared form (kShared false), a direction a workgroup: four
+// waves a SIMD for three, and the others' kernels without the choice, which cost
+// k_pair 0.5%.  Order of 1024 x 8192 under fp32_ties: 735 ms (882 before the shared
+// form's kernels, 846 in them).
 //
 // Work items of the pair kernels.  With kLoop false the grid is the schedule
 // and workgroup p (after the XCD remap) takes item p.  With kLoop true (gated
@@ -682,14 +686,14 @@ constexpr int kRenorm = 16;         // samples per lane between renormalisations
 // 32-bit register, 16 bits each, and add at most 254 every kRenorm samples
 constexpr int kShareMaxIters = 4096;
 
-template <int kMode, int W>
+template <int kMode, int W, bool kShared>
 __device__ __forceinline__ void pair_item(const JobDev& J, const JobStep& S, int local, int half,
                                           int wave, int lane);
 
 // W waves per workgroup (1, 2 or 4): every (tile, split) item of item_dirs halves is
 // cut into 4 / W consecutive workgroup items a half, and the wave's quadrant of the
 // tile is (workgroup item mod 4 / W) * W + its wave in the workgroup.
-template <int kMode, bool kLoop, int W>
+template <int kMode, bool kLoop, int W, bool kShared>
 __device__ __forceinline__ void pair_tiles(const JobDev* __restrict__ jobs, int njobs,
                                            const JobStep* __restrict__ js,
                                            const int32_t* __restrict__ pre, int G) {
@@ -703,8 +707,8 @@ __device__ __forceinline__ void pair_tiles(const JobDev* __restrict__ jobs, int 
   const int b = blockIdx.x;
   const int p = xcd_item(b, G);
   auto run = [&](int jb, int local) {
-    const PairItem it = pair_item_at(local, kQ, shared_job(jobs[jb]));
-    pair_item<kMode, W>(jobs[jb], js[jb], it.item, it.half, it.part * W + lw, lane);
+    const PairItem it = pair_item_at(local, kQ, kShared);
+    pair_item<kMode, W, kShared>(jobs[jb], js[jb], it.item, it.half, it.part * W + lw, lane);
   };
   int jb, local;
   if (!kLoop) {  // the grid is the schedule: one item per workgroup
@@ -1010,7 +1014,7 @@ __device__ __forceinline__ bool pair_both(const JobDev& J, const PairWave& w, in
   return true;
 }
 
-template <int kMode, int W>
+template <int kMode, int W, bool kShared>
 __device__ __forceinline__ void pair_item(const JobDev& J, const JobStep& S, int local, int half,
                                           int wave, int lane) {
   constexpr bool kCand = kMode != kModeAll;
@@ -1080,8 +1084,15 @@ __device__ __forceinline__ void pair_item(const JobDev& J, const JobStep& S, int
     w.si[a] = __builtin_amdgcn_readlane(w.row, a * 8);
     w.sj[a] = __builtin_amdgcn_readlane(w.row, 32 + a * 8);
   }
+  // A quadrant on the diagonal has the same variables on both sides, so its
+  // direction-0 walk (a, c) with a != c already holds both residual
+  // directions of each of its 6 pairs.
+  if (!kShared) {
+    if (half == 0 || !w.diag) pair_dir(J, w, half);
+    return;
+  }
   bool partial = false;  // the shared form holds, but not over this range
-  if (!w.diag && shared_job(J)) {
+  if (!w.diag) {
     // does either side (i: the lower lanes) reach past kShareTop?  The combining
     // kernels ask the same of the whole sub-block (both_far)
     const double top = w.row < J.d ? J.mom[(int64_t)w.row * 8 + kMomTop] : 0.0;
@@ -1090,12 +1101,9 @@ __device__ __forceinline__ void pair_item(const JobDev& J, const JobStep& S, int
     partial = side >= 0;
     if (partial && w.nk <= kShareMaxIters && pair_both(J, w, side)) return;
   }
-  // A quadrant on the diagonal has the same variables on both sides, so its
-  // direction-0 walk (a, c) with a != c already holds both residual
-  // directions of each of its 6 pairs.
-  const int end = w.diag || (half == 0 && !shared_job(J)) ? 1 : 2;  // half: one direction
+  const int ndir = w.diag ? 1 : 2;
 #pragma clang loop unroll(disable)
-  for (int dir = half; dir < end; ++dir) pair_dir(J, w, dir);
+  for (int dir = 0; dir < ndir; ++dir) pair_dir(J, w, dir);
   if (partial) pair_part(J, w);
 }
 

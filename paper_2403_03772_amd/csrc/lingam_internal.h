@@ -28,13 +28,13 @@ constexpr int kTileVars = 8;
 constexpr int kWaveVars = 4;
 // Samples are padded to a multiple of this (one wavefront of samples).
 constexpr int kSampleQuantum = 64;
-// Waves a SIMD that the pair kernels are compiled for (up to 168 registers).  The
-// bounded grids of the gated full step and of the suspect and extension passes
-// launch as many workgroups as are resident then: their static chunks run in one
-// round, where a fourth workgroup a CU waits for the first three to end (k_pair_susp
-// at 512 x 8192 with t4 noise: 56 us, 39 so).
-constexpr int kPairWavesPerSimd = 3;
-constexpr int kPairWavesPerCu = 4 * kPairWavesPerSimd;
+// Waves a SIMD that the pair kernels are compiled for (up to 168 registers; 128 with
+// the separate form alone).  The bounded grids of the gated full step and of the
+// suspect and extension passes launch as many workgroups as are resident then: their
+// static chunks run in one round, where a fourth workgroup a CU waits for the first
+// three to end (k_pair_susp at 512 x 8192 with t4 noise: 56 us, 39 so).
+constexpr int pair_waves_per_simd(bool shared) { return shared ? 3 : 4; }
+constexpr int pair_waves_per_cu(bool shared) { return 4 * pair_waves_per_simd(shared); }
 // Steps with at most this many active variables run the FP64 pair kernel.
 constexpr int kFp64MaxM = 64;
 // Most aggressive split policy the workspace is sized for (see Tune).
@@ -423,7 +423,7 @@ __host__ __device__ inline void split_for(int64_t items_total, int32_t n_pad, in
 // Work items of a tile and sample split: both residual directions in one where the
 // job may take the shared form, one each where it may not, or its passes of few rows
 // have half the workgroups, twice as long (learned order of 512 x 8192 under
-// fp32_ties: 115 ms with both directions in one, 89 with one each).
+// fp32_ties: 115 ms with both directions in one, 90 with one each).
 __host__ __device__ inline int32_t item_dirs(bool shared) { return shared ? 1 : 2; }
 
 // Workgroup `local` of a job's pair pass, `parts` of them for a tile's quadrants.
@@ -595,9 +595,10 @@ hipError_t launch_standardize(const JobDev* jobs, int njobs, SchedDev sc, int gr
 hipError_t launch_step_schedule(const JobDev* jobs, int njobs, int t, int num_cu, Tune tu,
                                 SchedDev sc, hipStream_t st);
 hipError_t launch_gate_schedule(const JobDev* jobs, int njobs, SchedDev sc, hipStream_t st);
-// loop: grid smaller than the schedule (gated launches), workgroups walk items
+// shared: the call's jobs may take the shared form (in the row passes too); loop: grid
+// smaller than the schedule (gated launches), workgroups walk items
 hipError_t launch_pair(const JobDev* jobs, int njobs, SchedDev sc, int grid, int waves,
-                       hipStream_t st, bool loop = false);
+                       bool shared, hipStream_t st, bool loop = false);
 hipError_t launch_combine(const JobDev* jobs, int njobs, SchedDev sc, int grid, hipStream_t st);
 // ranges: xcd_ranges64 of the step's FP64-path jobs.
 hipError_t launch_pair64(const JobDev* jobs, int njobs, SchedDev sc, int grid, bool ranges,
@@ -630,7 +631,7 @@ hipError_t launch_prop_prep(const float* in, PropDev* out, const JobDev* jobs, i
 hipError_t launch_learned_front(const JobDev* jobs, int njobs, int t, SchedDev sc,
                                 const int32_t* grid, hipStream_t st);
 hipError_t launch_pair_cand(const JobDev* jobs, int njobs, SchedDev sc, int grid, int waves,
-                            hipStream_t st);
+                            bool shared, hipStream_t st);
 hipError_t launch_learned_back(const JobDev* jobs, int njobs, int t, SchedDev sc,
                                const int32_t* grid, hipStream_t st);
 // The second (suspect) pass: its schedule, its pair kernel (a bounded grid that
@@ -639,11 +640,11 @@ hipError_t launch_susp_schedule(const JobDev* jobs, int njobs, SchedDev sc, int 
                                 int num_cu, Tune tu,
                                 hipStream_t st);
 hipError_t launch_pair_ext(const JobDev* jobs, int njobs, SchedDev sc, int grid, int waves,
-                           hipStream_t st);
+                           bool shared, hipStream_t st);
 hipError_t launch_ext_back(const JobDev* jobs, int njobs, int t, SchedDev sc, int g_bound,
                            int g_comp, hipStream_t st);
 hipError_t launch_pair_susp(const JobDev* jobs, int njobs, SchedDev sc, int grid, int waves,
-                            hipStream_t st);
+                            bool shared, hipStream_t st);
 hipError_t launch_susp_back(const JobDev* jobs, int njobs, int t, SchedDev sc, int g_comb,
                             int g_rowk, int g_sel, hipStream_t st);
 
@@ -772,6 +773,17 @@ hipError_t launch_cov_perm(const double* Xd, int64_t ldx, int n, int d, const in
 // theta[t] = (I - B0) M[t], t < lags (d x d each, row-major).
 hipError_t launch_lagged_effects(const double* M, const double* B0, int d, int lags,
                                  double* theta, hipStream_t st);
+
+// A pair kernel at 1, 2 or 4 waves per workgroup, with the shared form or without.
+#define LG_LAUNCH_PAIR_W(kern, W, shared, grid, st, ...)                                       \
+  hipLaunchKernelGGL((shared) ? (kern<W, true>) : (kern<W, false>), dim3((unsigned)(grid)),    \
+                     dim3(64 * W), 0, st, __VA_ARGS__)
+#define LG_LAUNCH_PAIR(kern, waves, shared, grid, st, ...)                                     \
+  do {                                                                                         \
+    if ((waves) == 1) LG_LAUNCH_PAIR_W(kern, 1, shared, grid, st, __VA_ARGS__);                \
+    else if ((waves) == 2) LG_LAUNCH_PAIR_W(kern, 2, shared, grid, st, __VA_ARGS__);           \
+    else LG_LAUNCH_PAIR_W(kern, 4, shared, grid, st, __VA_ARGS__);                             \
+  } while (0)
 
 #define LG_HIP(call)                    \
   do {                                  \

@@ -420,20 +420,20 @@ __global__ __launch_bounds__(256) void k_standardize(const JobDev* __restrict__ 
 // the step kernels
 // ---------------------------------------------------------------------------
 
-template <int W>
-__global__ __launch_bounds__(64 * W, kPairWavesPerSimd) void k_pair(
+template <int W, bool kShared>
+__global__ __launch_bounds__(64 * W, pair_waves_per_simd(kShared)) void k_pair(
     const JobDev* __restrict__ jobs, int njobs, const JobStep* __restrict__ js,
     const int32_t* __restrict__ pre, int G) {
-  pair_tiles<kModeAll, false, W>(jobs, njobs, js, pre, G);
+  pair_tiles<kModeAll, false, W, kShared>(jobs, njobs, js, pre, G);
 }
 
 // The same kernel for gated launches (learned form): a bounded grid walks the
 // step's items.
-template <int W>
-__global__ __launch_bounds__(64 * W, kPairWavesPerSimd) void k_pair_loop(
+template <int W, bool kShared>
+__global__ __launch_bounds__(64 * W, pair_waves_per_simd(kShared)) void k_pair_loop(
     const JobDev* __restrict__ jobs, int njobs, const JobStep* __restrict__ js,
     const int32_t* __restrict__ pre, int G) {
-  pair_tiles<kModeAll, true, W>(jobs, njobs, js, pre, G);
+  pair_tiles<kModeAll, true, W, kShared>(jobs, njobs, js, pre, G);
 }
 
 // Sum the sample splits (FP64, fixed order), form both residual entropies and
@@ -1349,23 +1349,15 @@ hipError_t launch_gate_schedule(const JobDev* jobs, int njobs, SchedDev sc, hipS
   return hipGetLastError();
 }
 
-template <int W>
-static void launch_pair_w(const JobDev* jobs, int njobs, SchedDev sc, int grid, hipStream_t st,
-                          bool loop) {
-  if (loop)
-    hipLaunchKernelGGL(k_pair_loop<W>, dim3((unsigned)grid), dim3(64 * W), 0, st, jobs, njobs,
-                       (const JobStep*)sc.js, pre_of(sc, njobs, kKPair), grid);
-  else
-    hipLaunchKernelGGL(k_pair<W>, dim3((unsigned)grid), dim3(64 * W), 0, st, jobs, njobs,
-                       (const JobStep*)sc.js, pre_of(sc, njobs, kKPair), grid);
-}
-
 hipError_t launch_pair(const JobDev* jobs, int njobs, SchedDev sc, int grid, int waves,
-                       hipStream_t st, bool loop) {
+                       bool shared, hipStream_t st, bool loop) {
   if (grid <= 0) return hipSuccess;
-  if (waves == 1) launch_pair_w<1>(jobs, njobs, sc, grid, st, loop);
-  else if (waves == 2) launch_pair_w<2>(jobs, njobs, sc, grid, st, loop);
-  else launch_pair_w<4>(jobs, njobs, sc, grid, st, loop);
+  if (loop)
+    LG_LAUNCH_PAIR(k_pair_loop, waves, shared, grid, st, jobs, njobs, (const JobStep*)sc.js,
+                   pre_of(sc, njobs, kKPair), grid);
+  else
+    LG_LAUNCH_PAIR(k_pair, waves, shared, grid, st, jobs, njobs, (const JobStep*)sc.js,
+                   pre_of(sc, njobs, kKPair), grid);
   return hipGetLastError();
 }
 

@@ -603,11 +603,11 @@ __global__ __launch_bounds__(1024) void k_topk(const JobDev* __restrict__ jobs, 
 // candidate rows of the measure
 // ---------------------------------------------------------------------------
 
-template <int W>
-__global__ __launch_bounds__(64 * W, kPairWavesPerSimd) void k_pair_cand(
+template <int W, bool kShared>
+__global__ __launch_bounds__(64 * W, pair_waves_per_simd(kShared)) void k_pair_cand(
     const JobDev* __restrict__ jobs, int njobs, const JobStep* __restrict__ js,
     const int32_t* __restrict__ pre, int G) {
-  pair_tiles<kModeCand, false, W>(jobs, njobs, js, pre, G);
+  pair_tiles<kModeCand, false, W, kShared>(jobs, njobs, js, pre, G);
 }
 
 // Witness pairs: one workgroup per non-candidate position l whose candidate
@@ -1083,18 +1083,18 @@ __global__ __launch_bounds__(1024) void k_susp_schedule(const JobDev* __restrict
 
 // The bounded-grid pair kernels (suspect and extension rows) walk their items
 // in a loop.
-template <int W>
-__global__ __launch_bounds__(64 * W, kPairWavesPerSimd) void k_pair_susp(
+template <int W, bool kShared>
+__global__ __launch_bounds__(64 * W, pair_waves_per_simd(kShared)) void k_pair_susp(
     const JobDev* __restrict__ jobs, int njobs, const JobStep* __restrict__ js,
     const int32_t* __restrict__ pre, int G) {
-  pair_tiles<kModeSusp, true, W>(jobs, njobs, js, pre, G);
+  pair_tiles<kModeSusp, true, W, kShared>(jobs, njobs, js, pre, G);
 }
 
-template <int W>
-__global__ __launch_bounds__(64 * W, kPairWavesPerSimd) void k_pair_ext(
+template <int W, bool kShared>
+__global__ __launch_bounds__(64 * W, pair_waves_per_simd(kShared)) void k_pair_ext(
     const JobDev* __restrict__ jobs, int njobs, const JobStep* __restrict__ js,
     const int32_t* __restrict__ pre, int G) {
-  pair_tiles<kModeExt, true, W>(jobs, njobs, js, pre, G);
+  pair_tiles<kModeExt, true, W, kShared>(jobs, njobs, js, pre, G);
 }
 
 // The extension columns' share of every listed suspect's k: one wave per
@@ -1705,22 +1705,11 @@ hipError_t launch_learned_front(const JobDev* jobs, int njobs, int t, SchedDev s
   return hipGetLastError();
 }
 
-// The row kernels at 1, 2 or 4 waves per workgroup.
-#define LG_LAUNCH_W(kern, waves, grid, st, ...)                                          \
-  do {                                                                                   \
-    if ((waves) == 1)                                                                    \
-      hipLaunchKernelGGL(kern<1>, dim3((unsigned)(grid)), dim3(64), 0, st, __VA_ARGS__);  \
-    else if ((waves) == 2)                                                               \
-      hipLaunchKernelGGL(kern<2>, dim3((unsigned)(grid)), dim3(128), 0, st, __VA_ARGS__); \
-    else                                                                                 \
-      hipLaunchKernelGGL(kern<4>, dim3((unsigned)(grid)), dim3(256), 0, st, __VA_ARGS__); \
-  } while (0)
-
 hipError_t launch_pair_cand(const JobDev* jobs, int njobs, SchedDev sc, int grid, int waves,
-                            hipStream_t st) {
+                            bool shared, hipStream_t st) {
   if (grid <= 0) return hipSuccess;
-  LG_LAUNCH_W(k_pair_cand, waves, grid, st, jobs, njobs, (const JobStep*)sc.js,
-              pre_kind(sc, njobs, kKPairC), grid);
+  LG_LAUNCH_PAIR(k_pair_cand, waves, shared, grid, st, jobs, njobs, (const JobStep*)sc.js,
+                 pre_kind(sc, njobs, kKPairC), grid);
   return hipGetLastError();
 }
 
@@ -1750,10 +1739,10 @@ hipError_t launch_susp_schedule(const JobDev* jobs, int njobs, SchedDev sc, int 
 }
 
 hipError_t launch_pair_ext(const JobDev* jobs, int njobs, SchedDev sc, int grid, int waves,
-                           hipStream_t st) {
+                           bool shared, hipStream_t st) {
   if (grid <= 0) return hipSuccess;
-  LG_LAUNCH_W(k_pair_ext, waves, grid, st, jobs, njobs, (const JobStep*)sc.js,
-              pre_kind(sc, njobs, kKPairE), grid);
+  LG_LAUNCH_PAIR(k_pair_ext, waves, shared, grid, st, jobs, njobs, (const JobStep*)sc.js,
+                 pre_kind(sc, njobs, kKPairE), grid);
   return hipGetLastError();
 }
 
@@ -1769,10 +1758,10 @@ hipError_t launch_ext_back(const JobDev* jobs, int njobs, int t, SchedDev sc, in
 }
 
 hipError_t launch_pair_susp(const JobDev* jobs, int njobs, SchedDev sc, int grid, int waves,
-                            hipStream_t st) {
+                            bool shared, hipStream_t st) {
   if (grid <= 0) return hipSuccess;
-  LG_LAUNCH_W(k_pair_susp, waves, grid, st, jobs, njobs, (const JobStep*)sc.js,
-              pre_kind(sc, njobs, kKPairS), grid);
+  LG_LAUNCH_PAIR(k_pair_susp, waves, shared, grid, st, jobs, njobs, (const JobStep*)sc.js,
+                 pre_kind(sc, njobs, kKPairS), grid);
   return hipGetLastError();
 }
 

@@ -1,5 +1,5 @@
 """The pair kernels' registers and LDS against the residency that their bounded grids
-are sized for (kPairWavesPerCu), and no spilled registers: their loops are bound by
+are sized for (pair_waves_per_cu), and no spilled registers: their loops are bound by
 instruction issue, and a spill doubles their time without a wrong result."""
 import os
 import re
@@ -41,7 +41,7 @@ def kernels(hipcc, tmp_path_factory):
                     "max_flat_workgroup_size", "vgpr_count", "vgpr_spill_count",
                     "group_segment_fixed_size")]
                 found[name.group(1)] = (v[0] // 64, *v[1:])
-    assert len(found) == 15, sorted(found)  # five kernels of 1, 2 and 4 waves
+    assert len(found) == 30, sorted(found)  # five kernels of 1, 2 and 4 waves, two forms
     return found
 
 
@@ -53,10 +53,12 @@ def test_bounded_grids_match_the_residency(hipcc, kernels, tmp_path):
     h, b = hipcc
     src, exe = tmp_path / "waves.cpp", tmp_path / "waves"
     src.write_text('#include <cstdio>\n#include "lingam_internal.h"\n'
-                   'int main() { std::printf("%d", lg::kPairWavesPerCu); }\n')
+                   'int main() { std::printf("%d %d", lg::pair_waves_per_cu(false),'
+                   ' lg::pair_waves_per_cu(true)); }\n')
     subprocess.run([h, "-std=c++17", "-I", b.INCLUDE, "-I", b.CSRC, str(src), "-o", str(exe)],
                    check=True, capture_output=True)
-    planned = int(subprocess.run([str(exe)], capture_output=True, text=True).stdout)
+    planned = subprocess.run([str(exe)], capture_output=True, text=True).stdout.split()
     for name, (waves, vgprs, _, lds) in kernels.items():
         resident = SIMDS * (SIMD_VGPRS // (-(-vgprs // 8) * 8)) // waves
-        assert min(resident, CU_LDS // lds) * waves == planned, name
+        want = int(planned["Lb1E" in name])  # kShared
+        assert min(resident, CU_LDS // lds) * waves == want, name
