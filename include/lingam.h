@@ -232,9 +232,9 @@ int lingam_causal_order(const float* X, int64_t n, int64_t d, int64_t ldx, int32
  * library runs on, held until the process ends; the call itself allocates
  * nothing.
  *   Arguments and results as for lingam_causal_order.
- *   A size whose workspace (lingam_workspace_size(n, d, opts)) exceeds
+ *   A size whose least workspace (LINGAM_FLAG_LEAST_WORKSPACE) exceeds
  *   LINGAM_NOALLOC_SCRATCH_BYTES returns LINGAM_E_UNSUPPORTED (64 MiB holds,
- *   for example, d = 512 at n = 8192 or d = 256 at n = 16384); so do
+ *   for example, d = 500 at n = 8192 or d = 256 at n = 16384); so do
  *   LINGAM_FLAG_GRAPH, LINGAM_FLAG_AUTOTUNE and a non-NULL opts->profile.
  * Every call on one GPU uses that GPU's array and leaves its contents behind
  * (the call initialises what it needs).  Calls that overlap in time on the

@@ -631,8 +631,10 @@ __device__ __forceinline__ void for_blocks_xcd(const int32_t* __restrict__ pre, 
 //   * u^2 + y^2 = w^2 + x^2 for the residuals u = (x - rho y) alpha and w =
 //     (y - rho x) alpha: with E = e^{(x^2 - u^2) / 2} and the stored g = e^{-z^2
 //     / 2}, e^{-u^2 / 2} = E g(x) and e^{-w^2 / 2} = E g(y): one exponential
-//     for both.  E stays below 2^122 while |x| <= kShareTop; past that in y,
-//     g(y) loses bits only where e^{-w^2 / 2} is below 1e-8.  So the wave
+//     for both.  E stays below 2^122 while |x| <= kShareTop.  Past 13.2 in y the
+//     stored g(y) is a subnormal, off by at most 2^-150, so E g(y) by 2^-28 =
+//     4e-9.  (Subnormals have to be kept, as they are by default: flushed to 0,
+//     g(y) would be off by 2^-126 and the weight by up to 0.06.)  So the wave
 //     takes as x the side whose four variables stay within kShareTop.
 // What bounds both is instruction issue.  Measured on the forms alone, cycles a
 // SIMD per evaluation of 64 samples: v_exp_f32 takes 8.2 and lets nothing else

@@ -137,7 +137,7 @@ struct Layout {
   size_t rmat;   // double [d * d]  pairwise measure R by position
   size_t mvec;   // double [d]      per-position measure -k
   size_t mom;    // double [d * 8]  moments of z by original id (E lc, E g, E z^3, E z^4, E|z|,
-                 // max |z|)
+                 // max |z|, sum of the FP32 copy)
   // learned form (K > 0 only)
   int32_t K;
   size_t feat;   // float  [d * kFeat] features by position

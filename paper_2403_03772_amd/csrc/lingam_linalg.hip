@@ -149,9 +149,12 @@ __global__ __launch_bounds__(256) void k_chol_first(double* __restrict__ A, int6
 // wave and saves the launch that would form them first; they are read from
 // raw_panel, so those of the first tile column store P_I in place and their tile,
 // the next panel, to the next raw_panel; the first workgroup's is the next
-// diagonal block, which it factors and inverts.  A launch of 13.8 us a step at d = 1024, where a
-// panel solve (32), an update (6) and a factorization with a barrier a column
-// (22) were three.
+// diagonal block, which it factors and inverts.  The product with the inverse
+// stands for a solve: against 80-bit arithmetic the panel's error is 1.1 to 1.3 of
+// the solve's for 64 x 64 correlation matrices of condition 1e2 to 2e14 (1e-16 to
+// 3e-12), the residual 2e-15 of the diagonal for 3e-16.  A launch of 13.8 us a
+// step at d = 1024, where a panel solve (32), an update (6) and a factorization with
+// a barrier a column (22) were three.
 __global__ __launch_bounds__(256) void k_chol_step(double* __restrict__ A, int64_t lda, int p,
                                                    int k0, int nt, double* __restrict__ X,
                                                    int64_t ldx, const double* __restrict__ tol,
@@ -1107,8 +1110,6 @@ hipError_t launch_adjacency_pruned(const PruneLayout& A, char* ws, const float* 
   LG_HIP(launch_cholesky_inverse(Lm, d, d, Ym, d, at<double>(ws, A.tol), ctrl, 1, 0, st));
   if (d < 2) return hipGetLastError();
   const int cap = max_active < kLassoMaxActive ? max_active : kLassoMaxActive;
-  // registers hold a predictor's row entries a thread; LDS the path state (d = 1024:
-  // 48 KB beside M's 34, two workgroups a CU as in memory's case by registers)
   // a thread a predictor: its rows' entries fit in registers; the path state in LDS
   // (1024: 48 KB beside the inverse's 34, two workgroups a CU, as registers allow)
   const auto lars = d - 1 <= 256        ? k_lars<true, true>
