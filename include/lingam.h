@@ -85,8 +85,8 @@ typedef enum {
                                     tie resolution; see lingam_causal_order) */
 #define LINGAM_FLAG_LEAST_WORKSPACE 16u /* lingam_workspace_size, lingam_batch_workspace_size
                                     and varlingam_workspace_size give the least size that
-                                    the calls accept, not the one they are fastest with (a
-                                    quarter to a third less); the calls go by ws_bytes */
+                                    the calls accept, not the one they are fastest with (up
+                                    to a quarter less); the calls go by ws_bytes */
 
 /* Per-call profile, filled when opts->profile is non-NULL (forces a sync). */
 typedef struct lingam_profile {
